@@ -5,8 +5,9 @@
  * 2608.01657): cutting token sequences into full 16-token KV blocks with
  * chained 64-bit block keys, and replaying many independent multi-tenant
  * prefix-cache instances (LRU, S3-FIFO, PrefixShield) over those keys, one
- * GPU workgroup (four wavefronts) per instance, with admission debt metered
- * per accounting group.
+ * wavefront per instance on runs of blocks, or one workgroup of four where
+ * an instance does not fit that form, with admission debt metered per
+ * accounting group.
  *
  * Conventions (every entry point):
  *   - Pointers named d_* are DEVICE pointers owned by the caller; they must
@@ -161,15 +162,18 @@ typedef struct {
  * n_inst * PC_STATS_RECORD_BYTES bytes. */
 #define PC_STATS_RECORD_BYTES (64 * 136 + 64)
 
-/* Workspace bytes pc_replay_batch needs for this batch (< 0: invalid input,
- * see pc_last_error). */
+/* Workspace bytes for this batch (< 0: invalid input, see pc_last_error).
+ * They include the trace analysis of the replay on runs: some 12 bytes per
+ * key of every distinct key buffer and 32 per request, where that is at most
+ * 16 GiB.  pc_replay_batch also takes a workspace that only lacks this part
+ * and then replays with the general kernels alone. */
 int64_t pc_replay_workspace_bytes(const pc_trace_desc *traces, int32_t n_traces,
                                   const pc_instance_desc *inst, int32_t n_inst);
 
 /* Per-instance replay state (the cache metadata: block keys and metadata,
  * stamps, the free-queue log, the block and ghost tables, per-request
- * scratch) that pc_replay_batch would use for this batch: bytes_out[i]
- * bytes, laid out as layout_out[i] says:
+ * scratch) that pc_replay_batch's general kernels would use for this batch:
+ * bytes_out[i] bytes, laid out as layout_out[i] says:
  *   PC_LAYOUT_LDS     all of it in LDS
  *   PC_LAYOUT_HYBRID  block keys and prefix ids in the workspace, the rest
  *                     in LDS (chosen when it lets more instances share a CU)
@@ -184,15 +188,16 @@ int32_t pc_replay_state_bytes(const pc_trace_desc *traces, int32_t n_traces,
                               const pc_instance_desc *inst, int32_t n_inst,
                               int64_t *bytes_out, int32_t *layout_out);
 
-/* Replay every instance over its trace, one workgroup per instance; queued
- * on `stream` (instances of different LDS footprints run as separate
+/* Replay every instance over its trace, one wavefront or workgroup per
+ * instance; queued on `stream` (instances of different LDS footprints run as separate
  * launches on library streams that fork from and join back into it).  Per request it runs the hooks of Alg. 1 (OnRequest, OnTouch
  * with the debt gate of Eq. 4, OnCacheFullBlocks metering Eqs. 1-3) and,
  * when the cache is full, the reclamation of Alg. 2 (PrefixShield: Eqs. 5-9;
  * LRU, S3-FIFO and StaticQuota: the baselines of Sec. V-A) under the same
  * debt accounting.
- *   d_workspace   device memory of at least pc_replay_workspace_bytes()
- *                 bytes, 256-byte aligned; its contents need not be zeroed.
+ *   d_workspace   device memory of pc_replay_workspace_bytes() bytes or more
+ *                 (see there), 256-byte aligned; its contents need not be
+ *                 zeroed.
  *   d_stats       n_inst * PC_STATS_RECORD_BYTES bytes, written at the end.
  *   d_per_request optional (NULL): per-request int32 quadruples (hits, new
  *                 blocks, evictions, orphans); instance i's block starts at
@@ -210,8 +215,9 @@ int32_t pc_replay_batch(const pc_trace_desc *traces, int32_t n_traces,
  * runs on, until the process ends.  The call allocates no device memory and
  * no pinned host memory; the caller still passes d_stats and d_per_request
  * (as for pc_replay_batch).
- *   - A batch whose workspace (pc_replay_workspace_bytes) exceeds
- *     PC_STATIC_WORKSPACE_BYTES is rejected with PC_ENOMEM, queuing nothing.
+ *   - A batch whose workspace exceeds PC_STATIC_WORKSPACE_BYTES even without
+ *     the trace analysis (see pc_replay_workspace_bytes) is rejected with
+ *     PC_ENOMEM, queuing nothing.
  *   - Every call on one GPU uses that GPU's one array.  The kernels clear
  *     what they need, so a call never depends on an earlier call's
  *     contents, but calls whose work overlaps on one GPU (other streams, or

@@ -24,7 +24,7 @@ LIB_PHASES = os.path.join(HERE, "libpcreplay_phases.so")
 LIB_JITTER = os.path.join(HERE, "libpcreplay_jitter.so")
 BUILD_DIR = os.path.join(ROOT, "_build")
 
-SOURCES = ["pc_hash.hip", "pc_replay.hip", "pc_replay_global.hip", "pc_abi.cpp"]
+SOURCES = ["pc_hash.hip", "pc_replay.hip", "pc_replay_global.hip", "pc_runs.hip", "pc_abi.cpp"]
 ARCH = os.environ.get("PC_OFFLOAD_ARCH", "gfx950")
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-I", INCLUDE, "-I", CSRC,
          # packed FP32 instructions stay off (none are needed: the path is integer)

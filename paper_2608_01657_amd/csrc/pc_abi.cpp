@@ -6,12 +6,18 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <functional>
+#include <map>
 #include <mutex>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "pc.h"
 #include "pc_internal.h"
+
+#define PC_RUNS_FN inline
+#include "pc_runs.h"
 
 namespace {
 
@@ -87,7 +93,26 @@ struct Launch {
     double est = 0;                  // estimated duration (cost units), see validate_and_plan
 };
 
+// The replay on runs of a batch (pc_runs.h): key buffers and traces to
+// analyse, regions in the workspace (byte offsets), launches.
+struct RunsPlan {
+    bool on = false;
+    std::vector<pcr::DevKeyBuf> kb;
+    std::vector<pcr::DevRunTrace> rt;
+    std::vector<int32_t> trace_run;   // per trace descriptor: index into rt, or -1
+    std::vector<int32_t> order;       // instances, launch by launch
+    std::vector<Launch> launches;
+    int64_t table_words = 0, id_words = 0, bit_words = 0, first_words = 0, n_req = 0;
+    uint32_t nb_pos = 0, nb_req = 0, nb_list = 0;
+    int32_t lds_bytes = 0;
+    int64_t o_kb = 0, o_rt = 0, o_order = 0;                              // header
+    int64_t o_table = 0, o_first = 0, ones = 0;                           // set to ones
+    int64_t o_start = 0, o_weak = 0, o_flags = 0, o_done = 0, zeros = 0;  // set to zeros
+    int64_t o_id = 0, o_req = 0;
+};
+
 struct Plan {
+    RunsPlan runs;
     std::vector<pcr::DevInst> di;
     std::vector<pcr::DevTrace> dt;
     std::vector<int32_t> order;      // instances, launch by launch, costliest first
@@ -100,8 +125,115 @@ struct Plan {
 constexpr int64_t kMaxRho = (int64_t)1 << 40;
 constexpr int64_t kMaxBeta = (int64_t)1 << 50;
 
+// The phase-counter and race-detection builds measure and test the general
+// kernel.
+#if defined(PC_PROFILE) || defined(PC_JITTER)
+constexpr bool kHaveRuns = false;
+#else
+constexpr bool kHaveRuns = true;
+#endif
+
+// What the replay on runs takes: positions and table slots below 2^31, and
+// prefix bitmaps and requests that one wavefront goes through in a moment.  A batch whose
+// longest trace is shorter than kRunsMinReq requests is over before the
+// analysis would have paid (about six launches against some 9 us a request).
+constexpr int64_t kRunsMaxKeys = (int64_t)1 << 30, kRunsMaxPrefix = (int64_t)1 << 22;
+constexpr int32_t kRunsMaxBlocks = 1 << 20;
+constexpr int64_t kRunsMinReq = 64;
+constexpr int64_t kRunsMaxBytes = (int64_t)16 << 30;
+
+// Which traces are analysed for the replay on runs, and the sizes of it.
+void plan_runs(const pc_trace_desc *traces, int32_t n_traces, const pc_instance_desc *inst, int32_t n_inst,
+               RunsPlan &R) {
+    R.trace_run.assign(n_traces, -1);
+    std::vector<char> used(n_traces, 0);
+    for (int i = 0; i < n_inst; ++i)
+        if (inst[i].trace >= 0 && inst[i].trace < n_traces) used[inst[i].trace] = 1;
+    std::map<std::pair<const uint64_t *, int64_t>, int32_t> bufs;
+    int64_t longest = 0, nb_pos = 0, nb_req = 0, nb_list = 0, bytes = 0;
+    for (int i = 0; i < n_traces; ++i) {
+        const pc_trace_desc &t = traces[i];
+        if (!used[i] || t.n_req < 1 || t.n_req > kRunsMaxKeys || t.n_keys > kRunsMaxKeys ||
+            t.n_prefix > kRunsMaxPrefix || t.max_req_blocks > kRunsMaxBlocks)
+            continue;
+        longest = std::max(longest, t.n_req);
+        const auto key = std::make_pair(t.d_keys, t.n_keys);
+        auto it = bufs.find(key);
+        if (it == bufs.end()) {
+            it = bufs.emplace(key, (int32_t)R.kb.size()).first;
+            pcr::DevKeyBuf b{};
+            b.keys = t.d_keys;
+            b.n = t.n_keys;
+            b.tab0 = R.table_words;
+            b.id0 = R.id_words;
+            b.bits0 = R.bit_words;
+            b.slots = (uint32_t)(2 * t.n_keys);
+            b.blk0 = (uint32_t)nb_pos;
+            R.table_words += align_up(2 * t.n_keys, 4);
+            R.id_words += align_up(t.n_keys, 4);
+            R.bit_words += align_up((t.n_keys + 31) / 32, 4);
+            nb_pos += (t.n_keys + pcr::kRunsBlock - 1) / pcr::kRunsBlock;
+            R.kb.push_back(b);
+        }
+        pcr::DevRunTrace d{};
+        d.trace = i;
+        d.buf = it->second;
+        d.req0 = R.n_req;
+        d.first0 = R.first_words;
+        d.blk0 = (uint32_t)nb_req;
+        d.blk1 = (uint32_t)nb_list;
+        R.n_req += t.n_req;
+        R.first_words += align_up(t.n_prefix, 4);
+        nb_req += (t.n_req + pcr::kRunsBlock - 1) / pcr::kRunsBlock;
+        nb_list += (t.n_req + pcr::kRunsListBlock - 1) / pcr::kRunsListBlock;
+        R.trace_run[i] = (int32_t)R.rt.size();
+        R.rt.push_back(d);
+        bytes = 4 * (R.table_words + R.id_words + 2 * R.bit_words + R.first_words) + 32 * R.n_req;
+        if (bytes > kRunsMaxBytes || nb_pos + nb_req > INT32_MAX || nb_list > INT32_MAX) break;
+    }
+    R.on = longest >= kRunsMinReq && bytes <= kRunsMaxBytes && nb_pos + nb_req <= INT32_MAX && nb_list <= INT32_MAX;
+    R.nb_pos = (uint32_t)nb_pos;
+    R.nb_req = (uint32_t)nb_req;
+    R.nb_list = (uint32_t)nb_list;
+}
+
+// Launches of the instances that are replayed on runs: one per class of LDS
+// (a wavefront of 16 KiB leaves room for ten on a CU, one of 40 KiB for
+// four, ...), the costliest instances and launches first.
+void plan_run_launches(Plan &P, const std::vector<double> &cost, int32_t n_inst) {
+    RunsPlan &R = P.runs;
+    static const int32_t kClass[] = {16 << 10, 40 << 10, 80 << 10, 160 << 10};
+    auto bytes_of = [&](int32_t i) { return pcr::runs_lds_bytes(P.di[i].policy, P.di[i].run_ring); };
+    auto class_of = [&](int32_t i) {
+        int c = 0;
+        while (c < 3 && bytes_of(i) > kClass[c]) ++c;
+        return c;
+    };
+    std::vector<int32_t> ids;
+    for (int i = 0; i < n_inst; ++i)
+        if (P.di[i].run_trace >= 0) ids.push_back(i);
+    std::sort(ids.begin(), ids.end(), [&](int32_t a, int32_t b) {
+        const int ca = class_of(a), cb = class_of(b);
+        return ca != cb ? ca > cb : cost[a] != cost[b] ? cost[a] > cost[b] : a < b;
+    });
+    for (size_t k = 0; k < ids.size();) {
+        Launch L;
+        L.first = (int32_t)k;
+        while (k < ids.size() && class_of(ids[k]) == class_of(ids[L.first])) {
+            L.lds_bytes = std::max(L.lds_bytes, bytes_of(ids[k]));
+            L.est += cost[ids[k]];
+            ++k;
+        }
+        L.count = (int32_t)k - L.first;
+        R.lds_bytes = std::max(R.lds_bytes, L.lds_bytes);
+        R.launches.push_back(L);
+    }
+    R.order = ids;
+}
+
 int32_t validate_and_plan(const pc_trace_desc *traces, int32_t n_traces, const pc_instance_desc *inst,
-                          int32_t n_inst, int64_t lds_cu, int64_t n_cu, Plan &P) {
+                          int32_t n_inst, int64_t lds_cu, int64_t n_cu, bool want_runs, Plan &P) {
+    P = Plan();
     if (n_traces < 0 || n_inst < 0) return fail(PC_EINVAL, "negative count");
     if ((n_traces > 0 && !traces) || (n_inst > 0 && !inst)) return fail(PC_EINVAL, "null descriptor array");
     P.dt.resize(n_traces);
@@ -136,6 +268,16 @@ int32_t validate_and_plan(const pc_trace_desc *traces, int32_t n_traces, const p
     off = align_up(off + (int64_t)sizeof(pcr::DevInst) * n_inst, 256);
     off = align_up(off + (int64_t)sizeof(pcr::DevTrace) * n_traces, 256);
     off = align_up(off + (int64_t)sizeof(int32_t) * n_inst, 256);
+    RunsPlan &R = P.runs;
+    if (want_runs && kHaveRuns) plan_runs(traces, n_traces, inst, n_inst, R);
+    if (R.on) {   // then the run plan's arrays
+        R.o_kb = off;
+        off = align_up(off + (int64_t)sizeof(pcr::DevKeyBuf) * R.kb.size(), 256);
+        R.o_rt = off;
+        off = align_up(off + (int64_t)sizeof(pcr::DevRunTrace) * R.rt.size(), 256);
+        R.o_order = off;
+        off = align_up(off + (int64_t)sizeof(int32_t) * n_inst, 256);
+    }
     P.hdr_bytes = off;
     int64_t per_req = 0;
     std::vector<double> cost(n_inst, 0.0);
@@ -194,6 +336,8 @@ int32_t validate_and_plan(const pc_trace_desc *traces, int32_t n_traces, const p
             d.move_thr == pcr::kFixMoveThr)
             maxn = pcr::kFixMaxn;
         d.maxn = (int32_t)maxn;
+        d.run_trace = R.on ? R.trace_run[s.trace] : -1;
+        d.run_ring = pcr::runs_ring(s.capacity);
         d.log_log2 = ceil_log2(s.capacity + maxn + 128);
         const bool ghost = s.policy == PC_S3FIFO && d.g_cap > 0;
         if (ghost) {
@@ -300,6 +444,20 @@ int32_t validate_and_plan(const pc_trace_desc *traces, int32_t n_traces, const p
             off = align_up(off + (8LL << d.gr_log2), 256);
         }
     }
+    if (R.on) {
+        auto take = [&off](int64_t bytes) { const int64_t o = off; off = align_up(off + bytes, 256); return o; };
+        R.o_table = take(4 * R.table_words);
+        R.o_first = take(4 * R.first_words);
+        R.ones = off - R.o_table;
+        R.o_start = take(4 * R.bit_words);
+        R.o_weak = take(4 * R.bit_words);
+        R.o_flags = take(4 * (int64_t)(R.rt.size() + 2 * R.kb.size()));
+        R.o_done = take(4 * (int64_t)n_inst);
+        R.zeros = off - R.o_start;
+        R.o_id = take(4 * R.id_words);
+        R.o_req = take((int64_t)sizeof(pcr::RunReq) * R.n_req);
+        plan_run_launches(P, cost, n_inst);
+    }
     P.ws_bytes = std::max<int64_t>(off, 256);
     // launches: one per (layout, instances per CU), each sized to its
     // largest LDS state; instances inside a launch costliest first, the
@@ -389,7 +547,7 @@ int32_t pc_hash_blocks(const int32_t *d_tokens, int64_t n_tokens, const int64_t 
 int64_t pc_replay_workspace_bytes(const pc_trace_desc *traces, int32_t n_traces, const pc_instance_desc *inst,
                                   int32_t n_inst) {
     Plan P;
-    int32_t rc = validate_and_plan(traces, n_traces, inst, n_inst, lds_per_cu(), cu_count(), P);
+    int32_t rc = validate_and_plan(traces, n_traces, inst, n_inst, lds_per_cu(), cu_count(), true, P);
     if (rc != PC_OK) return rc;
     ok();
     return P.ws_bytes;
@@ -399,7 +557,7 @@ int32_t pc_replay_state_bytes(const pc_trace_desc *traces, int32_t n_traces, con
                               int32_t n_inst, int64_t *bytes_out, int32_t *layout_out) {
     if (n_inst > 0 && (!bytes_out || !layout_out)) return fail(PC_EINVAL, "null output");
     Plan P;
-    int32_t rc = validate_and_plan(traces, n_traces, inst, n_inst, lds_per_cu(), cu_count(), P);
+    int32_t rc = validate_and_plan(traces, n_traces, inst, n_inst, lds_per_cu(), cu_count(), true, P);
     if (rc != PC_OK) return rc;
     for (int i = 0; i < n_inst; ++i) {
         bytes_out[i] = P.di[i].state_bytes;
@@ -425,6 +583,12 @@ void fill_header(const Plan &P, int32_t n_traces, int32_t n_inst, uint8_t *h) {
     std::memcpy(h, P.di.data(), sizeof(pcr::DevInst) * n_inst);
     if (n_traces) std::memcpy(h + o_tr, P.dt.data(), sizeof(pcr::DevTrace) * n_traces);
     std::memcpy(h + o_ord, P.order.data(), sizeof(int32_t) * n_inst);
+    const RunsPlan &R = P.runs;
+    if (R.on) {
+        std::memcpy(h + R.o_kb, R.kb.data(), sizeof(pcr::DevKeyBuf) * R.kb.size());
+        std::memcpy(h + R.o_rt, R.rt.data(), sizeof(pcr::DevRunTrace) * R.rt.size());
+        std::memcpy(h + R.o_order, R.order.data(), sizeof(int32_t) * R.order.size());
+    }
 }
 
 // Library streams (default priority) that the launches of one batch fork
@@ -454,30 +618,24 @@ int32_t fork_streams(int dev) {
     return PC_OK;
 }
 
-// Launches of a planned batch whose header is already queued for upload to
-// the start of `ws` on stream s.  With `fork`, launches go round-robin onto
-// the library streams (after s reaches this point) and s waits for all of
-// them; else they run one after another on s.
-int32_t launch_planned(const Plan &P, int32_t n_traces, int32_t n_inst, uint8_t *ws, void *d_stats,
-                       int32_t *d_per_request, hipStream_t s, bool fork) {
-    const size_t o_tr = align_up((int64_t)sizeof(pcr::DevInst) * n_inst, 256);
-    const size_t o_ord = align_up((int64_t)o_tr + (int64_t)sizeof(pcr::DevTrace) * n_traces, 256);
-    const pcr::DevInst *d_inst = (const pcr::DevInst *)ws;
-    const pcr::DevTrace *d_tr = (const pcr::DevTrace *)(ws + o_tr);
-    const int32_t *d_ord = (const int32_t *)(ws + o_ord);
+// Kernel launches that may run side by side, each with its estimated
+// duration: with `fork` and more than one they go onto the library streams
+// (after s reaches this point), each onto the one with the least estimated
+// work queued so far, and s waits for all of them; else one after another
+// on s.
+struct Task {
+    double est;
+    std::function<hipError_t(hipStream_t)> launch;
+};
+int32_t run_tasks(const std::vector<Task> &tasks, hipStream_t s, bool fork) {
+    const int nl = (int)tasks.size();
     hipError_t e;
-    if (P.lds_bytes > 0) {
-        e = pcr::replay_set_lds_limit(P.lds_bytes);
-        if (e != hipSuccess) return hip_fail(e, "replay LDS limit");
-    }
-    const int nl = (int)P.launches.size();
     if (!fork || nl < 2) {
-        for (const Launch &L : P.launches) {
-            e = pcr::launch_replay(d_inst, d_tr, d_ord + L.first, L.count, L.lds_bytes, L.layout, L.per_cu, ws,
-                                   (int64_t *)d_stats, d_per_request, s);
+        for (const Task &t : tasks) {
+            e = t.launch(s);
             if (e != hipSuccess) return hip_fail(e, "replay launch");
         }
-        return ok();
+        return PC_OK;
     }
     int dev = 0;
     e = hipGetDevice(&dev);
@@ -493,17 +651,13 @@ int32_t launch_planned(const Plan &P, int32_t n_traces, int32_t n_inst, uint8_t 
         e = hipStreamWaitEvent(g_fork.s[dev][k], g_fork.fork[dev], 0);
         if (e != hipSuccess) return hip_fail(e, "fork wait");
     }
-    // longest launch first, each onto the stream with the least estimated
-    // work queued so far
     double load[kForkStreams] = {};
-    for (int l = 0; l < nl; ++l) {
-        const Launch &L = P.launches[l];
+    for (const Task &t : tasks) {
         int k = 0;
         for (int j = 1; j < used; ++j)
             if (load[j] < load[k]) k = j;
-        load[k] += L.est;
-        e = pcr::launch_replay(d_inst, d_tr, d_ord + L.first, L.count, L.lds_bytes, L.layout, L.per_cu, ws,
-                               (int64_t *)d_stats, d_per_request, g_fork.s[dev][k]);
+        load[k] += t.est;
+        e = t.launch(g_fork.s[dev][k]);
         if (e != hipSuccess) return hip_fail(e, "replay launch");
     }
     for (int k = 0; k < used; ++k) {
@@ -512,7 +666,70 @@ int32_t launch_planned(const Plan &P, int32_t n_traces, int32_t n_inst, uint8_t 
         e = hipStreamWaitEvent(s, g_fork.join[dev][k], 0);
         if (e != hipSuccess) return hip_fail(e, "join wait");
     }
-    return ok();
+    return PC_OK;
+}
+
+// Launches of a planned batch whose header is already queued for upload to
+// the start of `ws` on stream s: the trace analysis and the replay on runs
+// where the plan has them, then the general kernels for every instance that
+// these left.
+int32_t launch_planned(const Plan &P, int32_t n_traces, int32_t n_inst, uint8_t *ws, void *d_stats,
+                       int32_t *d_per_request, hipStream_t s, bool fork) {
+    const size_t o_tr = align_up((int64_t)sizeof(pcr::DevInst) * n_inst, 256);
+    const size_t o_ord = align_up((int64_t)o_tr + (int64_t)sizeof(pcr::DevTrace) * n_traces, 256);
+    const pcr::DevInst *d_inst = (const pcr::DevInst *)ws;
+    const pcr::DevTrace *d_tr = (const pcr::DevTrace *)(ws + o_tr);
+    const int32_t *d_ord = (const int32_t *)(ws + o_ord);
+    int64_t *stats = (int64_t *)d_stats;
+    const int32_t *done = nullptr;
+    hipError_t e;
+    int32_t rc;
+    const RunsPlan &R = P.runs;
+    if (R.on) {
+        pcr::RunsArgs A{};
+        A.inst = d_inst;
+        A.tr = d_tr;
+        A.bufs = (const pcr::DevKeyBuf *)(ws + R.o_kb);
+        A.traces = (const pcr::DevRunTrace *)(ws + R.o_rt);
+        A.table = (uint32_t *)(ws + R.o_table);
+        A.id = (uint32_t *)(ws + R.o_id);
+        A.start = (uint32_t *)(ws + R.o_start);
+        A.weak = (uint32_t *)(ws + R.o_weak);
+        A.first = (uint32_t *)(ws + R.o_first);
+        A.req = (pcr::RunReq *)(ws + R.o_req);
+        A.tflag = (int32_t *)(ws + R.o_flags);
+        A.bflag = A.tflag + R.rt.size();
+        A.done = (int32_t *)(ws + R.o_done);
+        A.n_bufs = (int32_t)R.kb.size();
+        A.n_traces = (int32_t)R.rt.size();
+        A.nb_pos = R.nb_pos;
+        e = pcr::launch_runs_analysis(A, (uint4 *)(ws + R.o_table), R.ones / 16, (uint4 *)(ws + R.o_start),
+                                      R.zeros / 16, R.nb_req, R.nb_list, s);
+        if (e != hipSuccess) return hip_fail(e, "trace analysis launch");
+        e = pcr::runs_set_lds_limit(R.lds_bytes);
+        if (e != hipSuccess) return hip_fail(e, "replay LDS limit");
+        const int32_t *d_rord = (const int32_t *)(ws + R.o_order);
+        std::vector<Task> tasks;
+        for (const Launch &L : R.launches)
+            tasks.push_back({L.est, [=](hipStream_t q) {
+                return pcr::launch_runs_replay(A, d_rord + L.first, L.count, L.lds_bytes, ws, stats, d_per_request, q);
+            }});
+        rc = run_tasks(tasks, s, fork);
+        if (rc != PC_OK) return rc;
+        done = A.done;
+    }
+    if (P.lds_bytes > 0) {
+        e = pcr::replay_set_lds_limit(P.lds_bytes);
+        if (e != hipSuccess) return hip_fail(e, "replay LDS limit");
+    }
+    std::vector<Task> tasks;     // longest launch first
+    for (const Launch &L : P.launches)
+        tasks.push_back({L.est, [=](hipStream_t q) {
+            return pcr::launch_replay(d_inst, d_tr, d_ord + L.first, L.count, L.lds_bytes, L.layout, L.per_cu, ws,
+                                      stats, d_per_request, done, q);
+        }});
+    rc = run_tasks(tasks, s, fork);
+    return rc == PC_OK ? ok() : rc;
 }
 
 struct StaticScratch {
@@ -539,11 +756,16 @@ int32_t pc_replay_batch(const pc_trace_desc *traces, int32_t n_traces, const pc_
                         void *d_workspace, int64_t workspace_bytes, void *d_stats, int32_t *d_per_request,
                         void *stream) {
     Plan P;
-    int32_t rc = validate_and_plan(traces, n_traces, inst, n_inst, lds_per_cu(), cu_count(), P);
+    int32_t rc = validate_and_plan(traces, n_traces, inst, n_inst, lds_per_cu(), cu_count(), true, P);
     if (rc != PC_OK) return rc;
     if (n_inst == 0) return ok();
     if (!d_workspace || !d_stats) return fail(PC_EINVAL, "null workspace or stats");
     if (((uintptr_t)d_workspace & 255) != 0) return fail(PC_EINVAL, "workspace must be 256-byte aligned");
+    if (workspace_bytes < P.ws_bytes && P.runs.on) {
+        // enough for the general kernels alone: those replay the batch
+        rc = validate_and_plan(traces, n_traces, inst, n_inst, lds_per_cu(), cu_count(), false, P);
+        if (rc != PC_OK) return rc;
+    }
     if (workspace_bytes < P.ws_bytes)
         return fail(PC_ENOMEM, "workspace %lld bytes < required %lld", (long long)workspace_bytes, (long long)P.ws_bytes);
     hipStream_t s = (hipStream_t)stream;
@@ -582,10 +804,14 @@ int32_t pc_replay_batch(const pc_trace_desc *traces, int32_t n_traces, const pc_
 int32_t pc_replay_batch_static(const pc_trace_desc *traces, int32_t n_traces, const pc_instance_desc *inst,
                                int32_t n_inst, void *d_stats, int32_t *d_per_request, void *stream) {
     Plan P;
-    int32_t rc = validate_and_plan(traces, n_traces, inst, n_inst, lds_per_cu(), cu_count(), P);
+    int32_t rc = validate_and_plan(traces, n_traces, inst, n_inst, lds_per_cu(), cu_count(), true, P);
     if (rc != PC_OK) return rc;
     if (n_inst == 0) return ok();
     if (!d_stats) return fail(PC_EINVAL, "null stats");
+    if (P.ws_bytes > (int64_t)PC_STATIC_WORKSPACE_BYTES && P.runs.on) {
+        rc = validate_and_plan(traces, n_traces, inst, n_inst, lds_per_cu(), cu_count(), false, P);
+        if (rc != PC_OK) return rc;
+    }
     if (P.ws_bytes > (int64_t)PC_STATIC_WORKSPACE_BYTES)
         return fail(PC_ENOMEM, "batch needs %lld workspace bytes, more than the %lld of the static workspace",
                     (long long)P.ws_bytes, (long long)PC_STATIC_WORKSPACE_BYTES);

@@ -199,7 +199,9 @@ struct DevInst {
     int32_t o_key, o_stamp, o_meta, o_table, o_log, o_posslot, o_rset, o_rkeys, o_vlist;
     int32_t o_pfx, o_gtable, o_rcnt, o_res, o_cnt, o_cur, o_fstack;
     int32_t fixc;          // kFixC: the kernel takes the parameters below as constants
-    int32_t pad;
+    // replay on runs (pc_runs.hip): index into the analysed traces, or -1,
+    // and the entries of its rings
+    int32_t run_trace, run_ring, pad;
     // workspace offsets (bytes from workspace base)
     int64_t ws_state;      // state region when layout == kLayWs
     int64_t ws_key;        // uint64 [C] block keys (kLayHybrid; PrefixShield: the 16-byte records)
@@ -221,6 +223,45 @@ struct DevTrace {
     int32_t n_groups, max_req_blocks;
 };
 
+// ---- trace analysis of the replay on runs (pc_runs.hip).  A key buffer is
+// analysed once for all traces that read it.
+struct DevKeyBuf {
+    const uint64_t *keys;
+    int64_t n;
+    int64_t tab0;          // first word of its table (2 n words; later its pieces, 8 bytes each)
+    int64_t id0;           // first word of its ids (n)
+    int64_t bits0;         // first word of its start and weak-link bitmaps
+    uint32_t slots;        // table entries
+    uint32_t blk0;         // first block of runs_insert and runs_link
+};
+struct DevRunTrace {
+    int32_t trace, buf;    // trace descriptor, key buffer
+    int64_t req0;          // first RunReq
+    int64_t first0;        // first word of its prefixes' first requests
+    uint32_t blk0, blk1;   // first block of runs_insert's requests, of runs_list
+};
+struct RunReq;
+struct RunsArgs {
+    const DevInst *inst;
+    const DevTrace *tr;
+    const DevKeyBuf *bufs;
+    const DevRunTrace *traces;
+    uint32_t *table, *id, *start, *weak, *first;
+    RunReq *req;
+    int32_t *tflag;        // per analysed trace: left to the general kernel
+    int32_t *bflag;        // per key buffer: [2 b] no table, [2 b + 1] cuts were added
+    int32_t *done;         // per instance: replayed on runs
+    int32_t n_bufs, n_traces;
+    uint32_t nb_pos;       // blocks of runs_insert and runs_link over positions
+};
+// positions or requests per block of the analysis kernels
+constexpr int kRunsBlock = 256, kRunsListBlock = 4;
+hipError_t launch_runs_analysis(const RunsArgs &A, uint4 *ones, int64_t n_ones, uint4 *zeros, int64_t n_zeros,
+                                uint32_t nb_req, uint32_t nb_list, hipStream_t s);
+hipError_t runs_set_lds_limit(int32_t lds_bytes);
+hipError_t launch_runs_replay(const RunsArgs &A, const int32_t *d_order, int32_t n_launch, int32_t lds_bytes,
+                              uint8_t *ws, int64_t *stats, int32_t *per_req, hipStream_t s);
+
 // Launchers (defined in the .hip files; host-callable).
 hipError_t launch_block_offsets(const int32_t *len, int64_t n_req, int64_t *key_off,
                                 hipStream_t s);
@@ -233,15 +274,15 @@ int32_t replay_static_lds_bytes();
 // per batch, before its launches).
 hipError_t replay_set_lds_limit(int32_t lds_bytes);
 // One launch of n_launch instances d_order[0..n_launch) of one layout,
-// planned for per_cu instances per CU.
+// planned for per_cu instances per CU.  done (or null): instances to skip.
 hipError_t launch_replay(const DevInst *d_inst, const DevTrace *d_traces, const int32_t *d_order,
                          int32_t n_launch, int32_t lds_bytes, int layout, int per_cu, uint8_t *ws,
-                         int64_t *stats, int32_t *per_req, hipStream_t s);
+                         int64_t *stats, int32_t *per_req, const int32_t *done, hipStream_t s);
 // the translation unit of the kernels with state in global memory
 // (pc_replay_global.hip: hybrid and workspace layouts)
 hipError_t replay_hybrid_set_lds_limit(int32_t lds_bytes);
 hipError_t launch_replay_global(const DevInst *d_inst, const DevTrace *d_traces, const int32_t *d_order,
                                 int32_t n_launch, int32_t lds_bytes, int layout, uint8_t *ws, int64_t *stats,
-                                int32_t *per_req, hipStream_t s);
+                                int32_t *per_req, const int32_t *done, hipStream_t s);
 
 }  // namespace pcr

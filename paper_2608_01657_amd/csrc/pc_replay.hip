@@ -2074,10 +2074,12 @@ DEV void run_instance(Coll &coll, const DevInst &I, const DevTrace &T, uint8_t *
 // One workgroup per instance.
 template <int kLay>
 DEV void replay_body(const DevInst *__restrict__ insts, const DevTrace *__restrict__ traces,
-                     const int32_t *__restrict__ order, uint8_t *ws, int64_t *stats, int32_t *per_req) {
+                     const int32_t *__restrict__ order, uint8_t *ws, int64_t *stats, int32_t *per_req,
+                     const int32_t *done) {
     extern __shared__ __align__(16) uint8_t smem[];
     __shared__ Coll coll;
     const int id = order[blockIdx.x];
+    if (done && done[id]) return;    // replayed on runs already
     const DevInst &I = insts[id];
     const DevTrace &T = traces[I.trace];
     uint8_t *sbase;
@@ -2094,8 +2096,9 @@ DEV void replay_body(const DevInst *__restrict__ insts, const DevTrace *__restri
 template <int kLay>
 __global__ __launch_bounds__(kB) __attribute__((amdgpu_waves_per_eu(2)))
 void replay_kernel(const DevInst *__restrict__ insts, const DevTrace *__restrict__ traces,
-                   const int32_t *__restrict__ order, uint8_t *ws, int64_t *stats, int32_t *per_req) {
-    replay_body<kLay>(insts, traces, order, ws, stats, per_req);
+                   const int32_t *__restrict__ order, uint8_t *ws, int64_t *stats, int32_t *per_req,
+                   const int32_t *done) {
+    replay_body<kLay>(insts, traces, order, ws, stats, per_req, done);
 }
 #ifndef PC_REPLAY_GLOBAL_TU
 // An instance whose LDS state takes the whole CU: no occupancy target, so
@@ -2103,8 +2106,9 @@ void replay_kernel(const DevInst *__restrict__ insts, const DevTrace *__restrict
 // request than the same code built for two).
 __global__ __launch_bounds__(kB)
 void replay_kernel_solo(const DevInst *__restrict__ insts, const DevTrace *__restrict__ traces,
-                        const int32_t *__restrict__ order, uint8_t *ws, int64_t *stats, int32_t *per_req) {
-    replay_body<kLayLds>(insts, traces, order, ws, stats, per_req);
+                        const int32_t *__restrict__ order, uint8_t *ws, int64_t *stats, int32_t *per_req,
+                        const int32_t *done) {
+    replay_body<kLayLds>(insts, traces, order, ws, stats, per_req, done);
 }
 #endif
 
@@ -2124,13 +2128,13 @@ hipError_t replay_hybrid_set_lds_limit(int32_t lds_bytes) {
 
 hipError_t launch_replay_global(const DevInst *d_inst, const DevTrace *d_traces, const int32_t *d_order,
                                 int32_t n_launch, int32_t lds_bytes, int layout, uint8_t *ws, int64_t *stats,
-                                int32_t *per_req, hipStream_t s) {
+                                int32_t *per_req, const int32_t *done, hipStream_t s) {
     if (layout == kLayHybrid)
         hipLaunchKernelGGL(replay_kernel<kLayHybrid>, dim3((unsigned)n_launch), dim3(kB), (size_t)lds_bytes, s,
-                           d_inst, d_traces, d_order, ws, stats, per_req);
+                           d_inst, d_traces, d_order, ws, stats, per_req, done);
     else
         hipLaunchKernelGGL(replay_kernel<kLayWs>, dim3((unsigned)n_launch), dim3(kB), 0, s, d_inst, d_traces,
-                           d_order, ws, stats, per_req);
+                           d_order, ws, stats, per_req, done);
     return hipGetLastError();
 }
 
@@ -2150,16 +2154,16 @@ hipError_t replay_set_lds_limit(int32_t lds_bytes) {
 
 hipError_t launch_replay(const DevInst *d_inst, const DevTrace *d_traces, const int32_t *d_order, int32_t n_launch,
                          int32_t lds_bytes, int layout, int per_cu, uint8_t *ws, int64_t *stats, int32_t *per_req,
-                         hipStream_t s) {
+                         const int32_t *done, hipStream_t s) {
     if (n_launch <= 0) return hipSuccess;
     if (layout != kLayLds)
-        return launch_replay_global(d_inst, d_traces, d_order, n_launch, lds_bytes, layout, ws, stats, per_req, s);
+        return launch_replay_global(d_inst, d_traces, d_order, n_launch, lds_bytes, layout, ws, stats, per_req, done, s);
     if (per_cu == 1)
         hipLaunchKernelGGL(replay_kernel_solo, dim3((unsigned)n_launch), dim3(kB), (size_t)lds_bytes, s, d_inst,
-                           d_traces, d_order, ws, stats, per_req);
+                           d_traces, d_order, ws, stats, per_req, done);
     else
         hipLaunchKernelGGL(replay_kernel<kLayLds>, dim3((unsigned)n_launch), dim3(kB), (size_t)lds_bytes, s, d_inst,
-                           d_traces, d_order, ws, stats, per_req);
+                           d_traces, d_order, ws, stats, per_req, done);
     return hipGetLastError();
 }
 

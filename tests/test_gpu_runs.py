@@ -1,0 +1,134 @@
+"""The replay on runs and its trace analysis on the GPU, where they can go
+wrong: key buffers that several traces share or overlap in, duplicates that
+add cuts, instances that must be handed to the general kernel (too many runs,
+too many pieces, a malformed request), a workspace too small for the
+analysis, and the edges of a wavefront (63-65 pieces and requests)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2608_01657_amd as P
+from gpu_util import POLICIES, assert_same, run_key_traces
+from paper_2608_01657_amd import device as dv
+from paper_2608_01657_amd import tracegen as tg
+from test_runs_cpu import chunk_trace
+
+pytestmark = pytest.mark.gpu
+
+
+def _insts(caps, pols=POLICIES, contracts=((tg.Q16 * 2, 30 * tg.Q16),)):
+    return [tg.Instance(0, p, c, contracts=list(contracts)) for p in pols for c in caps]
+
+
+def _trace(reqs, n_groups=3, seed=0):
+    rng = np.random.default_rng(seed)
+    n = len(reqs)
+    g = rng.integers(0, n_groups, n)
+    return tg.KeyTrace(np.concatenate([np.asarray(r, np.uint64) for r in reqs] + [np.zeros(0, np.uint64)]),
+                       np.cumsum([0] + [len(r) for r in reqs]).astype(np.int64), g.astype(np.uint8),
+                       np.zeros(n, np.uint8), (g * 2 + rng.integers(0, 2, n)).astype(np.uint32), n_groups,
+                       2 * n_groups)
+
+
+@pytest.mark.parametrize("seed", range(3))
+def test_unchained_documents_and_duplicates(seed):
+    run_key_traces([chunk_trace(seed, n_req=700)], [_insts((25, 300, 3000))])
+
+
+@pytest.mark.parametrize("n_req", [63, 64, 65])
+def test_shortest_traces_on_runs(n_req):
+    run_key_traces([chunk_trace(50 + n_req, n_req=n_req)], [_insts((1, 7, 64, 4096))])
+
+
+@pytest.mark.parametrize("blocks", [63, 64, 65, 130])
+def test_requests_of_single_block_pieces(blocks):
+    """Every block its own piece (no two requests repeat an order): up to 64
+    pieces on runs, more in the general kernel."""
+    rng = np.random.default_rng(blocks)
+    reqs = [rng.permutation(400)[:blocks] for _ in range(90)]
+    run_key_traces([_trace(reqs)], [_insts((64, 150, 500))])
+
+
+def test_more_runs_than_rings_hold():
+    """Single-block prompts: thousands of runs are live at once."""
+    reqs = [[10 * r] if r % 3 else [10 * r, 7, 8] for r in range(6000)]
+    run_key_traces([_trace(reqs)], [_insts((500, 4096, 9000))])
+
+
+def test_malformed_request_after_many_good_ones():
+    kt = chunk_trace(9, n_req=200)
+    ok, bad = chunk_trace(10, n_req=150), chunk_trace(11, n_req=150)
+    bad.group[120] = 200
+    dts = [dv.upload_keys(k) for k in (kt, ok, bad)]
+    insts = [tg.Instance(t, p, 100) for t in range(3) for p in POLICIES]
+    b = dv.ReplayBatch(dts, insts)
+    b.launch()
+    for (groups, inst, status), x in zip(b.results(), insts):
+        if x.trace == 2:
+            assert status == P.PC_EINVAL and not any(inst.values())
+        else:
+            assert_same((groups, inst, status), oracle.replay_key_trace((kt, ok)[x.trace], x))
+
+
+def _views(kt, dt, ranges):
+    """Traces of request ranges of one uploaded key trace, on its key buffer."""
+    out, kts = [], []
+    for a, b in ranges:
+        out.append(dv.TraceView(keys=dt.keys[:dt.n_keys], key_off=dt.key_off[a:b + 1], group=dt.group[a:b],
+                                contract=dt.contract[a:b], prefix=dt.prefix[a:b], tick=None, n_groups=kt.n_groups,
+                                n_prefix=kt.n_prefix, max_req_blocks=dt.max_req_blocks, n_keys=dt.n_keys))
+        kts.append(tg.KeyTrace(kt.keys, kt.key_off[a:b + 1], kt.group[a:b], kt.contract[a:b], kt.prefix[a:b],
+                               kt.n_groups, kt.n_prefix))
+    return out, kts
+
+
+def test_traces_that_share_and_overlap_in_one_key_buffer():
+    kt = chunk_trace(21, n_req=600)
+    dt = dv.upload_keys(kt)
+    views, kts = _views(kt, dt, [(0, 600), (0, 300), (300, 600), (150, 450), (599, 600)])
+    # the same keys cut into requests elsewhere: starts inside other requests
+    off = np.unique(np.concatenate([[0], np.sort(np.random.default_rng(3).integers(0, kt.keys.size, 400)),
+                                    [kt.keys.size]])).astype(np.int64)
+    n = len(off) - 1
+    other = tg.KeyTrace(kt.keys, off, np.zeros(n, np.uint8), np.zeros(n, np.uint8), np.zeros(n, np.uint32),
+                        kt.n_groups, kt.n_prefix)
+    o = dv.upload_keys(other)
+    o.keys = dt.keys
+    for batch, ks in ((views, kts), (views + [o], kts + [other])):
+        insts = [tg.Instance(t, p, c) for t in range(len(batch)) for p in POLICIES for c in (60, 700)]
+        b = dv.ReplayBatch(batch, insts, per_request=True)
+        b.launch()
+        pr = b.per_request_arrays()
+        for k, (res, x) in enumerate(zip(b.results(), insts)):
+            w = oracle.replay_key_trace(ks[x.trace], x, per_request=True)
+            assert_same(res, w, f"instance {k}")
+            assert np.array_equal(pr[k], w.per_request)
+
+
+def test_general_kernel_where_the_workspace_has_no_room_for_the_analysis():
+    """A workspace of the general kernels' size is accepted, and so is the
+    static entry for a batch whose analysis does not fit its array."""
+    tr = tg.onetouch_4096(2000, 1500)
+    t = dv.upload(tr)
+    dv.cut_and_hash(t)
+    insts = [tg.Instance(0, p, c) for p in POLICIES for c in (256, 4096)]
+    b = dv.ReplayBatch([t], insts)
+    need = P.pc_replay_workspace_bytes(b.tdesc, b.idesc)
+    # the run plan adds at least the table and the ids of every key
+    small = b.workspace[:(need - 12 * t.n_keys) // 8 // 32 * 32]
+    stats = torch.zeros_like(b.stats)
+    P.pc_replay_batch(b.tdesc, b.idesc, small, stats)
+    b.launch()
+    torch.cuda.synchronize()
+    assert torch.equal(stats, b.stats)
+    big = tg.onetouch_4096(2001, 50000)
+    T = dv.upload(big)
+    dv.cut_and_hash(T)
+    B = dv.ReplayBatch([T], insts[:2])
+    assert P.pc_replay_workspace_bytes(B.tdesc, B.idesc) > P.PC_STATIC_WORKSPACE_BYTES
+    B.launch()
+    stats = torch.zeros_like(B.stats)
+    P.pc_replay_batch_static(B.tdesc, B.idesc, stats)
+    torch.cuda.synchronize()
+    assert torch.equal(stats, B.stats)

@@ -1,0 +1,165 @@
+"""The run-based replay (csrc/pc_runs.h) on the CPU, its wavefront run lane
+by lane with every LDS access bounds-checked (runs_host.cpp), against the
+oracle: every counter and every request's outcome, over the trace shapes of
+the package, crafted keys with duplicates, orphans and unchained repeats, and
+rings small enough that an instance must be handed to the general kernel."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import POLICIES, many_groups_batch, random_key_batch, step_boundary_batch
+from paper_2608_01657_amd import GROUP_FIELDS, INST_FIELDS
+from paper_2608_01657_amd import tracegen as tg
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+P, i32, i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("runs") / "librunshost.so")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-Werror", "-Wno-unknown-pragmas", "-shared", "-fPIC",
+                    "-I", os.path.join(ROOT, "paper_2608_01657_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "runs_host.cpp"), "-o", so], check=True)
+    L = ctypes.CDLL(so)
+    L.runs_host_replay.restype = ctypes.c_int
+    L.runs_host_replay.argtypes = [P, P, P, P, P, P, i64, i32, i64, i32, i64, i32, i32, P, P, i64, i32, i32, i32,
+                                   P, P, P]
+    return L
+
+
+def _ptr(a):
+    return None if a is None else a.ctypes.data_as(P)
+
+
+def run_host(L, kt, inst, ring=0):
+    """(groups, inst, per_request), or None when left to the general kernel."""
+    a = [np.ascontiguousarray(x, t) for x, t in ((kt.keys if kt.keys.size else np.zeros(1), np.uint64),
+                                                 (kt.key_off, np.int64), (kt.group, np.uint8),
+                                                 (kt.contract, np.uint8), (kt.prefix, np.uint32))]
+    tick = None if kt.tick is None else np.ascontiguousarray(kt.tick, np.int64)
+    rho = np.array([c[0] for c in inst.contracts], np.int64)
+    beta = np.array([c[1] for c in inst.contracts], np.int64)
+    R = kt.n_req
+    gs = np.zeros((kt.n_groups, len(GROUP_FIELDS)), np.int64)
+    st = np.zeros(len(INST_FIELDS), np.int64)
+    pr = np.zeros((R, 4), np.int32)
+    rc = L.runs_host_replay(*map(_ptr, a), _ptr(tick), R, kt.n_groups, kt.n_prefix, inst.policy, inst.capacity,
+                            inst.flags, len(inst.contracts), _ptr(rho), _ptr(beta), inst.eps_q16,
+                            inst.s3_small_permille, inst.s3_move_threshold, ring, _ptr(gs), _ptr(st), _ptr(pr))
+    if rc:
+        return None
+    return [dict(zip(GROUP_FIELDS, map(int, row))) for row in gs], dict(zip(INST_FIELDS, map(int, st))), pr
+
+
+def compare(L, kt, inst, ring=0, label=""):
+    got = run_host(L, kt, inst, ring)
+    if got is None:
+        return 0
+    o = oracle.replay_key_trace(kt, inst, per_request=True)
+    what = f"{label} {tg.POLICY_NAMES[inst.policy]} C={inst.capacity} flags={inst.flags}"
+    bad = np.flatnonzero((got[2] != o.per_request).any(axis=1))
+    assert bad.size == 0, f"{what}: request {bad[0]}: {got[2][bad[0]]} != {o.per_request[bad[0]]}"
+    for g, (a, b) in enumerate(zip(got[0], o.groups)):
+        assert a == b, f"{what} group {g}: {a} != {b}"
+    assert got[1] == o.inst, what
+    return 1
+
+
+def key_trace(tr):
+    keys, off = oracle.hash_trace(tr)
+    return tg.KeyTrace(keys, off, tr.group, tr.contract, tr.prefix, tr.n_groups, tr.n_prefix, tr.tick)
+
+
+def batch(L, kts, per, ring=0):
+    done = total = 0
+    for i, (kt, insts) in enumerate(zip(kts, per)):
+        for inst in insts:
+            done += compare(L, kt, inst, ring, f"trace {i}")
+            total += 1
+    return done, total
+
+
+@pytest.mark.parametrize("chunk", range(4))
+def test_random_keys(host, chunk):
+    done, total = batch(host, *random_key_batch(chunk))
+    assert done > 0.6 * total      # (a request of more than 64 pieces is left to the general kernel)
+
+
+def test_many_groups(host):
+    done, total = batch(host, *many_groups_batch())
+    assert done == total
+
+
+def test_long_requests_of_random_keys_are_left_or_exact(host):
+    batch(host, *step_boundary_batch())
+
+
+@pytest.mark.parametrize("name,seeds,n,caps", [
+    ("tiny", [0], 1500, (256, 64, 31)), ("onetouch4096", [0, 1], 1200, (4096, 700, 200)),
+    ("twopass", [0], 1000, (4096, 500)), ("delayed", [0], 3000, (4096, 1000)), ("tiers", [0], 1500, (4096, 800)),
+    ("chat", [0], 3000, (1024, 4096, 300)), ("chat_bursty", [0], 2000, (2048, 150)),
+    ("attack_replay", [0], 1500, (511, 97)), ("selector512x8", [0], 1500, (512, 40)),
+    ("selector4096x32", [0], 1500, (4096, 600))])
+def test_workloads(host, name, seeds, n, caps):
+    traces, insts = tg.workload(name, seeds=seeds, n_requests=n)
+    for ti, tr in enumerate(traces):
+        kt = key_trace(tr)
+        for inst in insts:
+            if inst.trace != ti:
+                continue
+            for cap in caps:
+                x = tg.Instance(0, inst.policy, cap, contracts=inst.contracts, flags=inst.flags,
+                                eps_q16=inst.eps_q16)
+                assert compare(host, kt, x, 0, name) == 1
+        for cap in caps:
+            for x in (tg.Instance(0, tg.POLICY_STATICQUOTA, cap, contracts=insts[0].contracts),
+                      tg.Instance(0, tg.POLICY_S3FIFO, cap, contracts=insts[0].contracts, s3_small_permille=400,
+                                  s3_move_threshold=2)):
+                assert compare(host, kt, x, 0, name) == 1
+
+
+def chunk_trace(seed, n_req=500, docs=60, doc_len=(1, 12), n_groups=4):
+    """Unchained keys: a request is a list of documents (with repeats, and
+    now and then only a document's start), then a question of its own."""
+    rng = np.random.default_rng(seed)
+    size = rng.integers(*doc_len, docs)
+    base = 1000 * np.arange(1, docs + 1)
+    keys, off = [], [0]
+    for r in range(n_req):
+        for d in rng.integers(0, docs, rng.integers(0, 7)) ** 2 // docs:
+            k = int(size[d]) if rng.random() < 0.8 else int(rng.integers(1, size[d] + 1))
+            keys.extend(base[d] + np.arange(k))
+        keys.extend(10_000_000 + 100 * r + np.arange(rng.integers(0, 5)))
+        off.append(len(keys))
+    group = rng.integers(0, n_groups, n_req)
+    return tg.KeyTrace(np.array(keys, np.uint64) * np.uint64(0x9E3779B97F4A7C15), np.array(off, np.int64),
+                       group.astype(np.uint8), np.zeros(n_req, np.uint8),
+                       (group * 3 + rng.integers(0, 3, n_req)).astype(np.uint32), n_groups, 3 * n_groups)
+
+
+@pytest.mark.parametrize("seed", range(6))
+def test_unchained_documents(host, seed):
+    kt = chunk_trace(seed)
+    for pol in POLICIES:
+        for cap in (20, 90, 300, 2000):
+            for flags in ([0, 1, 2, 3] if pol == tg.POLICY_PREFIXSHIELD else [0]):
+                assert compare(host, kt, tg.Instance(0, pol, cap, flags=flags, contracts=[(tg.Q16 * 3, 20 * tg.Q16)]),
+                               0, f"chunks {seed}") == 1
+
+
+@pytest.mark.parametrize("ring", [16, 64, 128])
+def test_small_rings_are_exact_or_left(host, ring):
+    """Rings far below the planner's: every window wraps and compacts often,
+    and an instance either overflows (left) or is exact."""
+    left = 0
+    for seed in range(4):
+        kt = chunk_trace(100 + seed, n_req=300)
+        for pol in POLICIES:
+            for cap in (12, 40, 150, 400):
+                left += 1 - compare(host, kt, tg.Instance(0, pol, cap), ring, f"ring {ring}")
+    assert left > 0 if ring == 16 else left < 64
