@@ -104,7 +104,7 @@ struct RunsPlan {
     std::vector<Launch> launches;
     int64_t table_words = 0, id_words = 0, bit_words = 0, first_words = 0, n_req = 0;
     uint32_t nb_pos = 0, nb_req = 0, nb_list = 0;
-    int32_t lds_bytes = 0;
+    int32_t wide_lds = 0;             // of the second launch (widest windows)
     int64_t o_kb = 0, o_rt = 0, o_order = 0;                              // header
     int64_t o_table = 0, o_first = 0, ones = 0;                           // set to ones
     int64_t o_start = 0, o_weak = 0, o_flags = 0, o_done = 0, zeros = 0;  // set to zeros
@@ -198,12 +198,20 @@ void plan_runs(const pc_trace_desc *traces, int32_t n_traces, const pc_instance_
 }
 
 // Launches of the instances that are replayed on runs: one per class of LDS
-// (a wavefront of 16 KiB leaves room for ten on a CU, one of 40 KiB for
-// four, ...), the costliest instances and launches first.
+// (ten, six, five or three wavefronts to a CU), the largest class and the
+// costliest instances first.  Four classes, since four launches run side by
+// side.  A launch asks for the LDS of its largest instance, and a workgroup
+// waits for the shader engine that it was dealt to, even while another has
+// room: with 1,008 PrefixShield and S3-FIFO instances in one class of four to
+// a CU, the 16 LRU instances of the bench batch began when those had ended
+// (194 against 131 ms).
 void plan_run_launches(Plan &P, const std::vector<double> &cost, int32_t n_inst) {
     RunsPlan &R = P.runs;
-    static const int32_t kClass[] = {16 << 10, 40 << 10, 80 << 10, 160 << 10};
-    auto bytes_of = [&](int32_t i) { return pcr::runs_lds_bytes(P.di[i].policy, P.di[i].run_ring); };
+    static const int32_t kClass[] = {16 << 10, 26 << 10, 32 << 10, 54 << 10};
+    auto bytes_of = [&](int32_t i, int wide = 0) {
+        const pcr::DevInst &d = P.di[i];
+        return pcr::runs_lds_bytes(d.policy, pcr::runs_windows(d.policy, d.capacity, wide), P.dt[d.trace].n_prefix);
+    };
     auto class_of = [&](int32_t i) {
         int c = 0;
         while (c < 3 && bytes_of(i) > kClass[c]) ++c;
@@ -225,9 +233,9 @@ void plan_run_launches(Plan &P, const std::vector<double> &cost, int32_t n_inst)
             ++k;
         }
         L.count = (int32_t)k - L.first;
-        R.lds_bytes = std::max(R.lds_bytes, L.lds_bytes);
         R.launches.push_back(L);
     }
+    for (int32_t i : ids) R.wide_lds = std::max(R.wide_lds, bytes_of(i, 1));
     R.order = ids;
 }
 
@@ -337,7 +345,6 @@ int32_t validate_and_plan(const pc_trace_desc *traces, int32_t n_traces, const p
             maxn = pcr::kFixMaxn;
         d.maxn = (int32_t)maxn;
         d.run_trace = R.on ? R.trace_run[s.trace] : -1;
-        d.run_ring = pcr::runs_ring(s.capacity);
         d.log_log2 = ceil_log2(s.capacity + maxn + 128);
         const bool ghost = s.policy == PC_S3FIFO && d.g_cap > 0;
         if (ghost) {
@@ -706,7 +713,7 @@ int32_t launch_planned(const Plan &P, int32_t n_traces, int32_t n_inst, uint8_t 
         e = pcr::launch_runs_analysis(A, (uint4 *)(ws + R.o_table), R.ones / 16, (uint4 *)(ws + R.o_start),
                                       R.zeros / 16, R.nb_req, R.nb_list, s);
         if (e != hipSuccess) return hip_fail(e, "trace analysis launch");
-        e = pcr::runs_set_lds_limit(R.lds_bytes);
+        e = pcr::runs_set_lds_limit(160 * 1024);
         if (e != hipSuccess) return hip_fail(e, "replay LDS limit");
         const int32_t *d_rord = (const int32_t *)(ws + R.o_order);
         std::vector<Task> tasks;
@@ -716,6 +723,9 @@ int32_t launch_planned(const Plan &P, int32_t n_traces, int32_t n_inst, uint8_t 
             }});
         rc = run_tasks(tasks, s, fork);
         if (rc != PC_OK) return rc;
+        A.wide = 1;      // (with every instance done, a few us)
+        e = pcr::launch_runs_replay(A, d_rord, (int32_t)R.order.size(), R.wide_lds, ws, stats, d_per_request, s);
+        if (e != hipSuccess) return hip_fail(e, "replay launch");
         done = A.done;
     }
     if (P.lds_bytes > 0) {

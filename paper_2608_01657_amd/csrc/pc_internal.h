@@ -199,9 +199,7 @@ struct DevInst {
     int32_t o_key, o_stamp, o_meta, o_table, o_log, o_posslot, o_rset, o_rkeys, o_vlist;
     int32_t o_pfx, o_gtable, o_rcnt, o_res, o_cnt, o_cur, o_fstack;
     int32_t fixc;          // kFixC: the kernel takes the parameters below as constants
-    // replay on runs (pc_runs.hip): index into the analysed traces, or -1,
-    // and the entries of its rings
-    int32_t run_trace, run_ring, pad;
+    int32_t run_trace;     // replay on runs (pc_runs.hip): index into the analysed traces, or -1
     // workspace offsets (bytes from workspace base)
     int64_t ws_state;      // state region when layout == kLayWs
     int64_t ws_key;        // uint64 [C] block keys (kLayHybrid; PrefixShield: the 16-byte records)
@@ -253,6 +251,7 @@ struct RunsArgs {
     int32_t *done;         // per instance: replayed on runs
     int32_t n_bufs, n_traces;
     uint32_t nb_pos;       // blocks of runs_insert and runs_link over positions
+    int32_t wide;          // replay: the instances that are not done, with the widest windows
 };
 // positions or requests per block of the analysis kernels
 constexpr int kRunsBlock = 256, kRunsListBlock = 4;

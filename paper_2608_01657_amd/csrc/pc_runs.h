@@ -1,7 +1,7 @@
 // pc_runs.h -- replay of one cache instance by one wavefront, on runs of
 // blocks instead of single blocks.
 //
-// The trace analysis (pc_intern.hip) numbers every distinct block key by the
+// The trace analysis (pc_runs.hip) numbers every distinct block key by the
 // position of its first occurrence in the key buffer (its id) and cuts every
 // request into pieces: maximal stretches of consecutive ids inside which no
 // id has a weak link.  The link into id x is weak when some request holds x
@@ -14,189 +14,252 @@
 //       deepest first, so what an eviction takes is a trailing part [s, hi).
 // A set of blocks that enters the free queue together therefore stays one
 // run of ids for as long as it is cached, and the cache is a short list of
-// runs (30-60 for 4,096 blocks of one-touch prompts) with the attributes
+// runs (30-110 for 4,096 blocks of one-touch prompts) with the attributes
 // that the policies look at.  Lookup, reclamation and release then cost a
 // few wavefront steps for a whole request, with no key compares, no hash
 // table and no barriers.
 //
-// Layout of a run: its first id, and a word of length (bits 0-15) and
-// attributes: owner group (16-21), contract (22-23), retention class
-// (24-25), S3-FIFO frequency (26-27); PrefixShield adds the prefix id,
-// S3-FIFO the request that pins it, the ghost the sequence of its last id.
-// Runs live in LDS rings in free-queue order; a run emptied by hits or
-// evictions stays behind with length 0 until the ring is compacted.
+// A run is its first id and a word of length (bits 0-15) and attributes:
+// owner group (16-21), contract (22-23), retention class (24-25), S3-FIFO
+// frequency (26-27), emptied (31); PrefixShield adds the prefix id, S3-FIFO
+// the request that pins it, the ghost the sequence of its last id.  Runs
+// stand in windows in LDS in free-queue order, 64 to a chunk; a run emptied
+// by hits or evictions stays behind (id kNone) until the window is compacted.
+//
+// What bounds a request is the instruction stream of its one wavefront: about
+// 4 cycles an instruction and 20-25 more a branch, with no other wavefront on
+// the SIMD to fill them.  So steps look at four chunks at once without a
+// branch in between, and what is rare stands behind one common test.
 //
 // The code is written for one wavefront with uniform control flow: `vu`,
 // `vl` and `vb` are a per-lane 32-bit word, 64-bit integer and condition,
 // everything else is uniform.  On the device they are the plain types; a
-// host build (PC_RUNS_HOST) takes 64-lane structures instead and runs the
-// same source on the CPU, lane by lane.
+// host build takes 64-lane structures instead and runs the same source on
+// the CPU, lane by lane.
 //
-// An instance that needs more runs than its rings hold, or more pieces per
-// request than lanes, is left to the general kernel (pc_replay.hip).
+// An instance that needs more runs than its windows hold is replayed again,
+// with windows that take a CU's whole LDS; one that needs more than those, or
+// more pieces per request than lanes, is left to the general kernel
+// (pc_replay.hip).
 #pragma once
 #include <stdint.h>
 
 namespace pcr {
 
-// One request as the trace analysis leaves it (32 bytes, read by every
-// instance of the trace with scalar loads).
+// One request as the trace analysis leaves it: eight words, read by every
+// instance of the trace, eight requests to a wavefront load.
 struct RunReq {
     uint32_t n_full;     // full blocks
-    uint32_t np;         // pieces
-    uint32_t info;       // bits 0-7 group, 8-15 contract, 16: its prefix was referenced before
+    uint32_t info;       // bits 0-7 group, 8-15 contract, 16: its prefix was referenced before, 24-31 pieces
     uint32_t prefix;
-    int64_t tick;
+    uint32_t dt;         // ticks since the request before it
     uint32_t ko;         // its pieces start at pieces[ko] of the trace's key buffer
-    uint32_t pad;
+    uint32_t nn;         // blocks that are no duplicates
+    uint32_t pad[2];
 };
-// One piece: its first id, and its depth in the request (bit 31: an earlier
-// piece of the request holds the same blocks -- duplicates, skipped).
+constexpr uint32_t kRunsMaxPieces = 64;      // more: 255 is stored, and the request is not for this form
+// One piece: its first id; its length (bits 0-14, at most 32,767), whether an
+// earlier piece of the request holds the same blocks (bit 15: duplicates,
+// skipped), and how many blocks that are no duplicates come before it (bits
+// 16-31, at most 65,535).  A request fills 32,767 blocks of a cache at most,
+// so what the limits cut off is cut off anyway.
 struct RunPiece {
-    uint32_t id, depth;
+    uint32_t id, len;
 };
-constexpr uint32_t kPieceDup = 0x80000000u;
+constexpr uint32_t kPieceLen = 0x7FFFu, kPieceDup = 0x8000u;
 
-// Ring entries of an instance.  Runs of fewer than 4 (small caches) or 8
-// blocks on average overflow it.
-constexpr int32_t runs_ring(int32_t capacity) {
-    if (capacity <= 512) return 512;
-    int32_t q = 1024;
-    while (q * 8 < capacity) q *= 2;
-    return q;
+// Entries of an instance's windows (multiples of 256): of the free queue,
+// under S3-FIFO of the small queue, the main queue and the ghost.  At first
+// (wide = 0) instances of up to 4,096 blocks fit five to a CU's LDS under any
+// policy and larger ones three, since a wavefront on every SIMD is what counts
+// for a batch of 1,024; there is room for runs of 3 blocks on average
+// (S3-FIFO: 5), above 4,096 blocks for runs of 6 to 11.
+struct RunWindows {
+    int32_t n[3];
+};
+constexpr RunWindows runs_windows(int policy, int32_t capacity, int wide) {
+    if (wide) {      // one instance to a CU; no window needs more than a run a block, and slack
+        const int32_t most = (capacity + 639) / 256 * 256;
+        if (policy == 1) return {{most < 4096 ? most : 4096, most < 4864 ? most : 4864, most < 3328 ? most : 3328}};
+        const int32_t n = policy == 2 ? 12032 : 18432;
+        return {{most < n ? most : n, 0, 0}};
+    }
+    if (capacity <= 384) return {{512, policy == 1 ? 512 : 0, policy == 1 ? 512 : 0}};
+    if (policy == 1) return capacity <= 4096 ? RunWindows{{1024, 768, 768}} : RunWindows{{1280, 2048, 1024}};
+    return {{capacity <= 2048 ? 1024 : capacity <= 4096 ? 1536 : 3072, 0, 0}};
 }
-constexpr int kRunList = 64;     // runs of the cache that one request may meet
-
-// LDS words of one instance.
-constexpr int32_t runs_lds_bytes(int policy, int32_t q) {
-    const int rings = policy == 1 ? 9 : policy == 2 ? 3 : 2;    // S3-FIFO: small, main, ghost
-    return 4 * (rings * q + 5 * kRunList);
+// PrefixShield keeps its admitted bits in LDS up to this many prefixes.
+constexpr int32_t kRunsLdsPrefix = 1 << 16;
+constexpr int32_t kRunsScratch = 192;     // words that single-lane stores spread over
+// LDS bytes of one instance: scratch, windows, admitted bits.
+constexpr int32_t runs_lds_bytes(int policy, RunWindows w, int64_t n_prefix) {
+    const int64_t words = (policy == 1 || policy == 2 ? 3 : 2) * ((int64_t)w.n[0] + w.n[1] + w.n[2]);
+    const int64_t bits = policy == 2 && n_prefix <= kRunsLdsPrefix ? (n_prefix + 31) / 32 : 0;
+    return (int32_t)(4 * (kRunsScratch + words + bits));
 }
-
-constexpr int kRunOk = 0, kRunGeneral = 1, kRunBroken = 2;
 
 // Replay parameters of one instance (uniform).
 struct RunParams {
     int32_t C, G, K, flags;
     int32_t s_cap, g_cap, move_thr;
-    uint32_t q;                      // ring entries (a power of two)
+    RunWindows win;
     int64_t eps;
     int64_t rho[4], beta[4], invw[4];
     int64_t n_req;
 };
 
-// `W` supplies the lane types and wavefront operations.
-template <class W, int kPol>
+// `W` supplies the lane types and wavefront operations; kK1: one contract.
+template <class W, int kPol, bool kK1>
 struct RunReplay {
     using vu = typename W::vu;
     using vl = typename W::vl;
     using vb = typename W::vb;
     using Lds = typename W::Lds;
     static constexpr int LRU = 0, S3 = 1, PS = 2, SQ = 3;
+    static constexpr bool kX = kPol == PS || kPol == S3;      // runs carry a third word
+    static constexpr bool kQ = kPol == PS || kPol == SQ;      // counts per (group, segment)
     static constexpr uint32_t kLen = 0xFFFFu, kAttr = 0xFFFF0000u;
     static constexpr int kOwnS = 16, kConS = 22, kClsS = 24, kFrqS = 26;
+    static constexpr uint32_t kOwnM = 63u << 16, kClsM = 3u << 24;
+    static constexpr uint32_t kDead = 0x80000000u;            // word of an emptied run
     static constexpr uint32_t kReuseCls = 2, kNormalCls = 1, kProbCls = 0;
     static constexpr uint32_t kNone = 0xFFFFFFFFu;
+    static constexpr int kC = kK1 ? 1 : 4;
+    // Entries that a request may need in the queue's window beyond one per
+    // piece (hits it releases, parts that the ghost remembers, splits).
+    static constexpr uint32_t kSlack = 128;
+    static constexpr uint32_t kFlush = 32768;     // requests between flushes of the 32-bit counters
+    // Words from one chunk of a window to the next, and to a run's second
+    // and third word.
+    static constexpr uint32_t kStep = 64 * (kX ? 3 : 2), kW = 64, kXo = 128;
 
-    struct Ring {
-        Lds lo, w, x;
-        uint32_t head, tail;
+    struct Window {
+        Lds p;
+        vu cap;                  // entries (uniform; rarely looked at)
+        uint32_t tail;           // entries in use
         uint32_t lim;            // compact when the window would grow past this
+    };
+    // Four chunks (a group) of one word of the runs.
+    struct Four {
+        vu v[4];
     };
 
     const RunParams &P;
     W &wv;
     const vu lane;
-    const uint32_t qm;           // ring index mask
-    Ring q0, q1, gh;             // free queue (S3-FIFO: small, main, ghost)
-    Lds xd, xlo, xw, xx, xi;     // the runs the current request meets
-    bool general;                // leave the instance to the general kernel
+    const Lds scratch;
+    Window q0, q1, gh;           // free queue (S3-FIFO: small, main, ghost)
+    uint32_t over;               // not 0: a window was too small, the state is lost
 
-    // uniform state
-    int32_t resident, rmax;
+    // the runs that the request meets (lane k: the k-th)
+    vu md, mlo, mw, mx, mi;
+    uint32_t nm;
+    // words of the queue's first group, as the request goes (not S3-FIFO)
+    Four lo4, w4;
+
+    // uniform state (what only vector instructions use stands in vector
+    // registers: scalar ones are what a request runs out of)
+    int32_t resident;
     int32_t s_size, s_unp, m_unp;
     uint32_t gseq;
-    uint64_t ev_total, s3_moves, s3_reins, s3_ghits, s3_gins;
-    int64_t tprev;
+    vu rmax, n_moves, n_reins, n_ghits, n_gins;          // since the last flush (rmax aside)
+    vl c_moves, c_reins, c_ghits, c_gins;
+    vl rho[kC], beta[kC];
     int32_t last_h, last_m, last_e, last_o;
     // lane x = group x
-    vl E[4];                     // effective balances at tprev (Eq. 1)
+    vl E[kC];                    // effective balances at tprev (Eq. 1)
     vl d_max, d_sum;
-    vu cnt0, cnt1, cnt2;         // queued blocks per segment (PrefixShield, StaticQuota: cnt0)
+    vu cnt0, cnt1, cnt2;         // queued blocks per segment (kQ)
     vu res, res_max;
-    vl evw, c_probe, c_hit, c_dup, c_trunc, c_promo, c_gated, c_orph, c_evc, c_req;
+    vu evw, n_req, n_probe, n_hit, n_evc;         // since the last flush
+    vl c_evw, c_req, c_probe, c_hit, c_evc, c_dup, c_trunc, c_promo, c_gated, c_orph;
 
     static PC_RUNS_FN uint32_t umin(uint32_t a, uint32_t b) { return a < b ? a : b; }
+    static PC_RUNS_FN uint32_t umax(uint32_t a, uint32_t b) { return a > b ? a : b; }
+    PC_RUNS_FN int K() const { return kK1 ? 1 : P.K; }
 
-    PC_RUNS_FN RunReplay(const RunParams &p, W &w, Lds base) : P(p), wv(w), lane(w.lane()), qm(p.q - 1u) {
-        Lds at = base;
-        auto ring = [&](Ring &r, bool x) {
-            r.lo = at; at = at + P.q;
-            r.w = at; at = at + P.q;
-            r.x = at;
-            if (x) at = at + P.q;
-            r.head = r.tail = 0;
-            r.lim = 64;
-        };
-        ring(q0, kPol == S3 || kPol == PS);
-        if (kPol == S3) { ring(q1, true); ring(gh, true); }
-        xd = at; at = at + kRunList;
-        xlo = at; at = at + kRunList;
-        xw = at; at = at + kRunList;
-        xx = at; at = at + kRunList;
-        xi = at;
-        general = false;
-        resident = rmax = 0;
+    PC_RUNS_FN RunReplay(const RunParams &p, W &w, Lds base)
+        : P(p), wv(w), lane(w.lane()), scratch(base) {
+        Lds at = base + (uint32_t)kRunsScratch;
+        at = open(q0, at, (uint32_t)P.win.n[0]);
+        if (kPol == S3) {
+            at = open(q1, at, (uint32_t)P.win.n[1]);
+            open(gh, at, (uint32_t)P.win.n[2]);
+        }
+        over = 0;
+        resident = 0;
         s_size = s_unp = m_unp = 0;
         gseq = 0;
-        ev_total = s3_moves = s3_reins = s3_ghits = s3_gins = 0;
-        tprev = 0;
         last_h = last_m = last_e = last_o = 0;
+        nm = 0;
         const vl z = wv.vl0(0);
         const vu zu = wv.vu0(0);
-        for (int c = 0; c < 4; ++c) E[c] = wv.vl0(c < P.K ? P.beta[c] : 0);
+        md = mlo = mw = mx = mi = zu;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) lo4.v[c] = w4.v[c] = zu;
+#pragma unroll
+        for (int c = 0; c < kC; ++c) {
+            E[c] = wv.vl0(c < P.K ? P.beta[c] : 0);
+            rho[c] = W::hold(wv.vl0(P.rho[c]));
+            beta[c] = W::hold(wv.vl0(P.beta[c]));
+        }
+        rmax = n_moves = n_reins = n_ghits = n_gins = W::hold(zu);
+        c_moves = c_reins = c_ghits = c_gins = z;
         d_max = d_sum = z;
         cnt0 = cnt1 = cnt2 = res = res_max = zu;
-        evw = c_probe = c_hit = c_dup = c_trunc = c_promo = c_gated = c_orph = c_evc = c_req = z;
+        evw = n_req = n_probe = n_hit = n_evc = zu;
+        c_evw = c_req = c_probe = c_hit = c_evc = c_dup = c_trunc = c_promo = c_gated = c_orph = z;
     }
+    // Entries past the tail are emptied runs.
+    PC_RUNS_FN Lds open(Window &r, Lds at, uint32_t n) {
+        r.p = at;
+        r.cap = W::hold(wv.vu0(n));
+        r.tail = 0;
+        r.lim = 64;
+        for (uint32_t b = 0; b < n; b += 64) {
+            W::st_all(r.p, lane + entry(b), wv.vu0(kNone));
+            W::st_all(r.p, lane + (entry(b) + kW), wv.vu0(kDead));
+        }
+        W::sync();
+        return at + (kX ? 3u : 2u) * n;
+    }
+    // first word of the entry at a window position
+    static PC_RUNS_FN uint32_t entry(uint32_t pos) { return pos + (pos >> 6) * (kStep - 64u); }
 
     // ------------------------------------------------------------ debts
-    // Eqs. 1 and 3: balances move to tick t.  The lazy refill of Eq. 1
+    // Eqs. 1 and 3: balances move on by dt ticks.  The lazy refill of Eq. 1
     // composes exactly: min(beta, min(beta, B + rho d1) + rho d2) =
     // min(beta, B + rho (d1 + d2)), so the balances are kept at the last
     // tick and every request adds one uniform amount.  2^62 stands for any
     // amount that certainly reaches beta (balances stay above -2^61).
-    PC_RUNS_FN void refill(int64_t t) {
-        const uint64_t dt = (uint64_t)(t - tprev);
-        tprev = t;
-        if (dt == 0) return;
+    PC_RUNS_FN void refill(uint32_t dt) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
-            if (c < P.K) {
-                uint64_t inc = (uint64_t)P.rho[c] * dt;
-                if (W::mulhi((uint64_t)P.rho[c], dt) != 0 || inc > (1ull << 62)) inc = 1ull << 62;
-                E[c] = W::vmin(E[c] + (int64_t)inc, P.beta[c]);
+        for (int c = 0; c < kC; ++c)
+            if (c < K()) {
+                vl inc = rho[c];
+                // (rho <= 2^40 and dt < 2^32: only a product past 2^64 wraps)
+                if (W::unlikely(dt != 1)) inc = W::mul_sat62(inc, dt);
+                E[c] = W::vmin(E[c] + inc, beta[c]);
             }
     }
     PC_RUNS_FN vl raw_debt() const {
         vl d = W::vmax(-E[0], (int64_t)0);
-        if (P.K > 1)
 #pragma unroll
-            for (int c = 1; c < 4; ++c)
-                if (c < P.K) d = d + W::vmax(-E[c], (int64_t)0);
+        for (int c = 1; c < kC; ++c)
+            if (c < P.K) d = d + W::vmax(-E[c], (int64_t)0);
         return d;
     }
     // Eq. 5 (1/w_c in Q16) and Eq. 8's decrement
     PC_RUNS_FN void norm_debt(vl &d, vl &dec) const {
-        if (P.K == 1) {     // w = 1
+        if (kK1) {     // w = 1: a block is a block
             d = W::vmax(-E[0], (int64_t)0);
-            dec = W::sel(E[0] < (int64_t)0, wv.vl0(65536), wv.vl0(0));
+            dec = wv.vl0(65536);
             return;
         }
         d = wv.vl0(0);
         dec = wv.vl0(0);
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
+        for (int c = 0; c < kC; ++c)
             if (c < P.K) {
                 const vb neg = E[c] < (int64_t)0;
                 d = d + W::sel(neg, W::mul_shr16(-E[c], P.invw[c]), wv.vl0(0));
@@ -205,529 +268,604 @@ struct RunReplay {
             }
     }
 
-    // ------------------------------------------------------------ rings
-    PC_RUNS_FN static vu owner(vu w) { return (w >> kOwnS) & 63u; }
-    PC_RUNS_FN static vu cls(vu w) { return (w >> kClsS) & 3u; }
+    // ------------------------------------------------------------ windows
     PC_RUNS_FN static uint32_t u_owner(uint32_t w) { return (w >> kOwnS) & 63u; }
     PC_RUNS_FN static uint32_t u_cls(uint32_t w) { return (w >> kClsS) & 3u; }
 
-    // Live runs move to the front of the window, in order.
-    template <bool kX>
-    PC_RUNS_FN void compact(Ring &r) {
-        uint32_t nw = r.head;
-        for (uint32_t b = r.head; b < r.tail; b += 64) {
-            W::sync();
-            const vu pos = lane + b;
-            const vu at = pos & qm;
-            const vu lo = W::ld(r.lo, at), w = W::ld(r.w, at);
-            vu x = w;
-            if (kX) x = W::ld(r.x, at);
-            const vb live = (pos < r.tail) & ((w & kLen) > 0u);
-            const uint64_t lm = W::ballot(live);
-            const vu to = (W::mbcnt(lm) + nw) & qm;
-            W::st(live, r.lo, to, lo);
-            W::st(live, r.w, to, w);
-            if (kX) W::st(live, r.x, to, x);
-            nw += (uint32_t)W::popc(lm);
-        }
-        const uint32_t live = nw - r.head;
-        r.head &= qm;            // (positions stay far below 2^32)
-        r.tail = r.head + live;
-        uint32_t lim = (live + live / 2 + 95u) & ~63u;
-        r.lim = umin(lim, P.q);
+    // word `off` of the four chunks from position b (a multiple of 256) on
+    PC_RUNS_FN Four load4(const Window &r, uint32_t b, uint32_t off) const {
+        Four f;
+        W::sync();
+        const vu at = lane + (entry(b) + off);
+#pragma unroll
+        for (uint32_t c = 0; c < 4; ++c) f.v[c] = W::ld(r.p + c * kStep, at);
+        return f;
     }
-    // Room for k more entries (the window never exceeds the ring).
-    template <bool kX>
-    PC_RUNS_FN bool room_for(Ring &r, uint32_t k) {
-        if (r.tail + k - r.head <= r.lim) return true;
-        compact<kX>(r);
-        const uint32_t need = r.tail + k - r.head;
-        if (need > P.q) { general = true; return false; }
-        if (need > r.lim) r.lim = umin((need + 63u) & ~63u, P.q);
-        return true;
+    PC_RUNS_FN void store(Window &r, uint32_t b, uint32_t c, uint32_t off, vu x) {
+        W::st_all(r.p + c * kStep, lane + (entry(b) + off), x);
     }
-    PC_RUNS_FN void push(Ring &r, uint32_t lo, uint32_t w, uint32_t x, bool has_x) {
-        const uint32_t at = r.tail & qm;
-        wv.st1(r.lo, at, lo);
-        wv.st1(r.w, at, w);
-        if (has_x) wv.st1(r.x, at, x);
-        r.tail += 1;
+    // Words of one entry, by lane 0 (the others write words of their own in
+    // scratch, so that no execution mask changes).
+    PC_RUNS_FN void put2(const Window &r, uint32_t at, uint32_t lo, uint32_t w) {
+        wv.template st1<2>(r.p, at, scratch, lo, w, 0u);
     }
-    // The run at window position `pos` becomes two: everything from pos + 1
-    // on moves up by one entry.
-    PC_RUNS_FN void open_gap(Ring &r, uint32_t pos) {
-        const uint32_t first = pos + 1;
-        uint32_t e = r.tail;
-        while (e > first) {
-            const uint32_t b = e - first > 64u ? e - 64u : first;
-            W::sync();
-            const vu p = lane + b;
-            const vb in = p < e;
-            const vu from = p & qm, to = (p + 1u) & qm;
-            const vu lo = W::ld(r.lo, from), w = W::ld(r.w, from), x = W::ld(r.x, from);
-            W::st(in, r.lo, to, lo);
-            W::st(in, r.w, to, w);
-            W::st(in, r.x, to, x);
-            e = b;
-        }
+    PC_RUNS_FN void put3(const Window &r, uint32_t at, uint32_t lo, uint32_t w, uint32_t x) {
+        wv.template st1<kX ? 3 : 2>(r.p, at, scratch, lo, w, x);
+    }
+    PC_RUNS_FN void push(Window &r, uint32_t lo, uint32_t w, uint32_t x) {
+        put3(r, entry(r.tail), lo, w, x);
         r.tail += 1;
     }
 
-    // Evicted blocks, `take` of them from each lane's run of word w.
-    PC_RUNS_FN void count_evicted(vu w, vu take) {
-        uint64_t vm = W::ballot(take > 0u);
-        while (vm) {
-            const int l = W::ffs(vm);
-            vm &= vm - 1;
-            const uint32_t o = u_owner(W::rdl(w, l)), n = W::rdl(take, l);
-            const vb me = lane == o;
-            evw = evw + W::widen(W::sel(me, wv.vu0(n), wv.vu0(0)));
-            res = res - W::sel(me, wv.vu0(n), wv.vu0(0));
+    // Live runs move to the front of the window, in order; the rest of it is
+    // emptied.
+    PC_RUNS_FN void compact(Window &r) {
+        uint32_t nw = 0;
+        const uint32_t nc = (r.tail + 63u) >> 6;
+        for (uint32_t c = 0; c < nc; ++c) {
+            W::sync();
+            const vu at = lane + c * kStep;
+            const vu lo = W::ld(r.p, at), w = W::ld(r.p + kW, at);
+            vu x = w;
+            if (kX) x = W::ld(r.p + kXo, at);
+            const vb live = lo != kNone;
+            const uint64_t m = W::ballot(live);
+            const vu pos = W::mbcnt(m) + nw;
+            const vu to = pos + (pos >> 6) * (kStep - 64u);
+            W::st(live, r.p, to, lo);
+            W::st(live, r.p + kW, to, w);
+            if (kX) W::st(live, r.p + kXo, to, x);
+            nw += (uint32_t)W::popc(m);
+        }
+        W::sync();
+        for (uint32_t c = nw >> 6; c < nc; ++c) {
+            const vb past = lane + 64u * c >= nw;
+            const vu at = lane + c * kStep;
+            W::st(past, r.p, at, wv.vu0(kNone));
+            W::st(past, r.p + kW, at, wv.vu0(kDead));
+        }
+        W::sync();
+        r.tail = nw;
+        // a scan pays per 256 entries and a compaction per 64: room for 32
+        // entries at least, and not past a group that the live runs leave
+        r.lim = umin(umax((nw + 32u + 63u) & ~63u, umin((nw + 255u) & ~255u, nw + 128u)), W::uni(r.cap) - kSlack);
+    }
+    // Room for k more entries, and kSlack behind them, compacting if need be.
+    PC_RUNS_FN bool room_for(Window &r, uint32_t k) {
+        if (W::likely(r.tail + k <= r.lim)) return true;
+        compact(r);
+        const uint32_t most = W::uni(r.cap) - kSlack;
+        if (r.tail + k > most) return false;
+        r.lim = umax(r.lim, umin(r.tail + k + 32u, most));
+        return true;
+    }
+    // The entry at `pos` is needed twice: everything behind it moves up by one.
+    PC_RUNS_FN void open_gap(Window &r, uint32_t pos) {
+        uint32_t e = r.tail;                 // entries [pos, e) still to move
+        while (e > pos) {
+            const uint32_t b = e - pos > 64u ? e - 64u : pos;
+            W::sync();
+            const vu from = lane + b, to = from + 1u;
+            const vb in = from < e;
+            const vu fa = from + (from >> 6) * (kStep - 64u), ta = to + (to >> 6) * (kStep - 64u);
+            const vu lo = W::ld_if(in, r.p, fa), w = W::ld_if(in, r.p + kW, fa), x = W::ld_if(in, r.p + kXo, fa);
+            W::st(in, r.p, ta, lo);
+            W::st(in, r.p + kW, ta, w);
+            W::st(in, r.p + kXo, ta, x);
+            e = b;
+        }
+        W::sync();
+        r.tail += 1;
+    }
+
+    // d more (or, as a two's complement, fewer) blocks in a queue
+    PC_RUNS_FN void count_queue(vu is_owner, uint32_t seg, uint32_t d) {
+        cnt0 = W::mad24(is_owner, kPol == SQ || seg == 0 ? d : 0u, cnt0);
+        if (kPol == PS) {
+            cnt1 = W::mad24(is_owner, seg == 1 ? d : 0u, cnt1);
+            cnt2 = W::mad24(is_owner, seg == 2 ? d : 0u, cnt2);
         }
     }
-    // One queue count per (owner, segment): d blocks more or fewer.
-    PC_RUNS_FN void count_queue(uint32_t o, uint32_t seg, uint32_t d) {
-        const vu dv = W::sel(lane == o, wv.vu0(d), wv.vu0(0));
-        if (seg == 0) cnt0 = cnt0 + dv;
-        else if (seg == 1) cnt1 = cnt1 + dv;
-        else cnt2 = cnt2 + dv;
-    }
+    PC_RUNS_FN vu is_lane(uint32_t l) const { return W::sel(lane == l, wv.vu0(1), wv.vu0(0)); }
     PC_RUNS_FN uint32_t seg_of(uint32_t w) const {
         return (kPol == PS && !(P.flags & 1)) ? u_cls(w) : 0u;
     }
-
-    // k victims from the queue, oldest first: only blocks owned by x (x >= 0)
-    // of segment s (s >= 0).
-    PC_RUNS_FN void take(int32_t x, int32_t s, uint32_t k) {
-        uint32_t rem = k;
-        W::sync();
-        for (uint32_t b = q0.head; b < q0.tail && rem > 0; b += 64) {
-            const vu pos = lane + b;
-            const vu at = pos & qm;
-            const vu w = W::ld(q0.w, at);
-            vb ok = pos < q0.tail;
-            if (kPol != LRU && x >= 0) ok = ok & (owner(w) == (uint32_t)x);
-            if (kPol == PS && s >= 0) ok = ok & (cls(w) == (uint32_t)s);
-            const vu len = W::sel(ok, w & kLen, wv.vu0(0));
-            if (W::ballot(len > 0u) == 0) continue;
-            const vu upto = W::scan(len);
-            const vu before = upto - len;
-            const vu tk = W::sel(before < rem, W::vmin(len, wv.vu0(rem) - before), wv.vu0(0));
-            const uint32_t tot = W::rdl(upto, 63);
-            const uint32_t nv = umin(tot, rem);
-            W::st(tk > 0u, q0.w, at, w - tk);
-            count_evicted(w, tk);
-            if (kPol == PS || kPol == SQ) {
-                uint64_t vm = W::ballot(tk > 0u);
-                while (vm) {
-                    const int l = W::ffs(vm);
-                    vm &= vm - 1;
-                    const uint32_t wl = W::rdl(w, l);
-                    count_queue(u_owner(wl), seg_of(wl), 0u - W::rdl(tk, l));
-                }
-            }
-            rem -= nv;
-            resident -= (int32_t)nv;
-            ev_total += nv;
-        }
-        if (rem) general = true;    // cannot happen: the counts say that the queue holds k
+    PC_RUNS_FN void victims(vu is_owner, uint32_t n) {
+        evw = W::mad24(is_owner, n, evw);
+        res = W::mad24(is_owner, 0u - n, res);
     }
-    // Window position of the oldest live run of (x, s).
-    PC_RUNS_FN uint32_t head_pos(uint32_t x, int32_t s) const {
+
+    // k victims from the queue, oldest first: those whose word, under `mask`,
+    // is `pat` (owner x >= 0, or any owner).
+    PC_RUNS_FN void take(uint32_t mask, uint32_t pat, int32_t x, uint32_t seg, uint32_t k) {
+        uint32_t rem = k;
+        uint32_t b = 0;
+        for (;;) {
+            uint64_t m4[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) m4[c] = W::ballot((w4.v[c] & (mask | kDead)) == pat);
+#pragma unroll
+            for (uint32_t c = 0; c < 4; ++c) {
+                uint64_t m = m4[c];
+                if (m == 0) continue;
+                // the first runs one by one (mostly a take ends inside the
+                // second), many small ones by a prefix sum
+                int it = 0;
+                do {
+                    const int l = W::ffs(m);
+                    m &= m - 1;
+                    const uint32_t wl = W::rdl(w4.v[c], l), len = wl & kLen;
+                    const bool all = len <= rem;
+                    const uint32_t n = all ? len : rem;
+                    w4.v[c] = W::setlane(w4.v[c], l, all ? kDead : wl - n);
+                    lo4.v[c] = W::setlane(lo4.v[c], l, all ? kNone : W::rdl(lo4.v[c], l));
+                    rem -= n;
+                    if (!(kQ && x >= 0)) {
+                        const vu o = is_lane(u_owner(wl));
+                        victims(o, n);
+                        if (kQ) count_queue(o, seg_of(wl), 0u - n);
+                    }
+                } while (rem > 0 && m && ++it < 6);
+                if (W::unlikely(rem > 0 && m)) {
+                    const vu len = W::sel(W::of_mask(m), w4.v[c] & kLen, wv.vu0(0));
+                    const vu upto = W::scan(len), before = upto - len;
+                    const vu tk = W::sel(before < rem, W::vmin(len, wv.vu0(rem) - before), wv.vu0(0));
+                    rem -= umin(W::rdl(upto, 63), rem);
+                    if (!(kQ && x >= 0))
+                        for (uint64_t vm = W::ballot(tk > 0u); vm; vm &= vm - 1) {
+                            const int l = W::ffs(vm);
+                            const uint32_t wl = W::rdl(w4.v[c], l), n = W::rdl(tk, l);
+                            const vu o = is_lane(u_owner(wl));
+                            victims(o, n);
+                            if (kQ) count_queue(o, seg_of(wl), 0u - n);
+                        }
+                    const vb all = (tk > 0u) & (tk == len);
+                    lo4.v[c] = W::sel(all, wv.vu0(kNone), lo4.v[c]);
+                    w4.v[c] = W::sel(all, wv.vu0(kDead), w4.v[c] - tk);
+                }
+                store(q0, b, c, 0, lo4.v[c]);
+                store(q0, b, c, kW, w4.v[c]);
+                if (W::likely(rem == 0)) break;
+            }
+            if (W::likely(rem == 0)) break;
+            b += 256;
+            if (b >= q0.tail) { over = 1; break; }   // cannot happen: the counts say that the queue holds k
+            lo4 = load4(q0, b, 0);
+            w4 = load4(q0, b, kW);
+        }
+        if (W::unlikely(b)) reload();
+        if (kQ && x >= 0) {
+            const vu o = is_lane((uint32_t)x);
+            victims(o, k);
+            count_queue(o, seg, 0u - k);
+        }
+        resident -= (int32_t)k;
+    }
+    // the queue's first group again
+    PC_RUNS_FN void reload() {
         W::sync();
-        for (uint32_t b = q0.head; b < q0.tail; b += 64) {
-            const vu pos = lane + b;
-            const vu w = W::ld(q0.w, pos & qm);
-            vb ok = (pos < q0.tail) & ((w & kLen) > 0u) & (owner(w) == x);
-            if (s >= 0) ok = ok & (cls(w) == (uint32_t)s);
-            const uint64_t m = W::ballot(ok);
-            if (m) return b + (uint32_t)W::ffs(m);
+        lo4 = load4(q0, 0, 0);
+        w4 = load4(q0, 0, kW);
+    }
+    // Window position of the oldest live run that matches.
+    PC_RUNS_FN uint32_t head_pos(uint32_t mask, uint32_t pat) {
+        W::sync();
+        const uint32_t nc = (q0.tail + 63u) >> 6;
+        for (uint32_t c = 0; c < nc; ++c) {
+            const vu w = W::ld(q0.p + kW, lane + c * kStep);
+            const uint64_t m = W::ballot((w & (mask | kDead)) == pat);
+            if (m) return 64u * c + (uint32_t)W::ffs(m);
         }
         return kNone;
     }
     // Alg. 2 (Eqs. 5-9): runs of victims from the group with the largest
-    // projected debt.
+    // projected debt, one (group, segment) queue at a time.  A take that ends
+    // with its queue leaves the group in the lead with the rest of its run of
+    // wins, so the next turn goes on with the group's next segment.
     PC_RUNS_FN void evict_ps(uint32_t e) {
-        const int nseg = (P.flags & 1) ? 1 : 3;
-        const vb grp = lane < (uint32_t)P.G;
+        const bool seg3 = !(P.flags & 1);
         vl Pd, D;
         norm_debt(Pd, D);
-        vu avail = cnt0 + cnt1 + cnt2;
         uint32_t rem = e;
-        while (rem > 0 && !general) {
-            const vb inE = grp & (avail > 0u) & (Pd > P.eps);          // Eq. 6
-            const uint64_t Em = W::ballot(inE);
-            if (!Em) break;
-            int gs;
-            int64_t pg, thr = P.eps;
-            if ((Em & (Em - 1)) == 0) {      // one indebted candidate owner
-                gs = W::ffs(Em);
-                pg = W::rdl64(Pd, gs);
-            } else {
-                pg = W::wmax64(W::sel(inE, Pd, wv.vl0(-1)));           // Eq. 7
-                uint64_t tied = W::ballot(inE & (Pd == pg));
-                gs = W::ffs(tied);
-                if (tied & (tied - 1)) {     // ties: lowest non-empty segment, then the oldest head
-                    const vu seg = W::sel(cnt0 > 0u, wv.vu0(0), W::sel(cnt1 > 0u, wv.vu0(1), wv.vu0(2)));
-                    int mseg = nseg == 1 ? 0 : 2;
-                    if (nseg == 3) {
-                        for (int s = 1; s >= 0; --s)
-                            if (W::ballot(seg == (uint32_t)s) & tied) mseg = s;
-                        tied &= W::ballot(seg == (uint32_t)mseg);
-                        gs = W::ffs(tied);
-                    }
-                    if (tied & (tied - 1)) {
-                        uint32_t best = kNone;
-                        for (uint64_t tm = tied; tm; tm &= tm - 1) {
-                            const int x = W::ffs(tm);
-                            const uint32_t hp = head_pos((uint32_t)x, nseg == 1 ? -1 : mseg);
-                            if (hp < best) { best = hp; gs = x; }
-                        }
-                    }
-                }
-                const int64_t p2 = W::wmax64(W::sel(inE & (lane != (uint32_t)gs), Pd, wv.vl0(-1)));
-                if (p2 > thr) thr = p2;
+        for (;;) {
+            const vb own = (cnt0 | cnt1 | cnt2) > 0u;
+            const uint64_t Em = W::ballot(own & (Pd > P.eps));         // Eq. 6
+            if (W::unlikely(Em == 0)) break;
+            // Eq. 7 among the first and the last of them, or all
+            int gs = W::ffs(Em);
+            const int l2 = 63 - W::clz(Em);
+            int64_t pg = W::rdl64(Pd, gs), p2 = W::rdl64(Pd, l2);
+            if (p2 > pg) {
+                const int64_t t = pg;
+                pg = p2;
+                p2 = t;
+                gs = l2;
             }
-            const int64_t dg = W::rdl64(D, gs);
-            if (dg <= 0) { general = true; break; }    // cannot happen: an indebted group has a decrement
-            const uint32_t ag = W::rdl(avail, gs);
+            if (W::popc(Em) != 2) {
+                if (W::likely(W::popc(Em) == 1)) {
+                    p2 = -1;
+                } else {
+                    const vl in = W::sel(W::of_mask(Em), Pd, wv.vl0(-1));
+                    pg = W::wmax64(in);
+                    gs = W::ffs(W::ballot(in == pg));
+                    p2 = W::wmax64(W::sel(lane != (uint32_t)gs, in, wv.vl0(-1)));
+                }
+            }
+            if (W::unlikely(p2 == pg)) gs = tie_break(W::ballot(Pd == pg) & Em, seg3);
+            const int64_t thr = p2 > P.eps ? p2 : P.eps;
+            const int64_t dg = kK1 ? 65536 : W::rdl64(D, gs);
+            if (!kK1 && dg <= 0) { over = 1; return; }    // cannot happen: an indebted group has a decrement
             // the group keeps winning strictly while P - i D > max(second, eps)
-            uint64_t k = 1;
-            if (pg > thr) {
-                const uint64_t num = (uint64_t)(pg - thr) + (uint64_t)dg - 1;
-                k = P.K == 1 ? num >> 16 : W::udiv(num, (uint64_t)dg);
-                if (k < 1) k = 1;
-            }
-            if (k > rem) k = rem;
-            if (k > ag) k = ag;
-            uint32_t kk = (uint32_t)k;
-            if (nseg == 1) {
-                take(gs, -1, kk);
-            } else {
-                for (int s = 0; s < 3 && kk > 0; ++s) {
-                    const uint32_t cs = W::rdl(s == 0 ? cnt0 : s == 1 ? cnt1 : cnt2, gs);
-                    const uint32_t tk = umin(cs, kk);
-                    if (tk > 0) take(gs, s, tk);
-                    kk -= tk;
-                }
-            }
-            const vb me = lane == (uint32_t)gs;
+            const uint32_t c0 = W::rdl(cnt0, gs), c1 = W::rdl(cnt1, gs), c2 = W::rdl(cnt2, gs);
+            const uint32_t seg = c0 ? 0u : c1 ? 1u : 2u, cs = c0 ? c0 : c1 ? c1 : c2;
+            uint32_t k = umin(cs, rem);
+            const uint64_t num = (uint64_t)(pg - thr) + (uint64_t)dg - 1;    // pg >= thr
+            const uint64_t wins = kK1 ? num >> 16 : W::udiv(num, (uint64_t)dg);
+            if (wins < k) k = wins ? (uint32_t)wins : 1u;
+            const uint32_t mask = seg3 ? kOwnM | kClsM : kOwnM;
+            take(mask, ((uint32_t)gs << kOwnS) | (seg << kClsS), gs, seg, k);
+            rem -= k;
+            if (W::likely(rem == 0) || over) return;
             const vl np = Pd - (int64_t)k * dg;
-            Pd = W::sel(me, W::vmax(np, (int64_t)0), Pd);
-            avail = W::sel(me, avail - (uint32_t)k, avail);
-            rem -= (uint32_t)k;
+            Pd = W::sel(lane == (uint32_t)gs, W::vmax(np, (int64_t)0), Pd);
         }
         // no indebted candidate owner: global segment order (Eq. 9 fallback)
-        for (int s = 0; s < nseg && rem > 0 && !general; ++s) {
+        for (uint32_t s = 0; s < 3 && rem > 0 && !over; ++s) {
             const uint32_t tot = W::wsum(s == 0 ? cnt0 : s == 1 ? cnt1 : cnt2);
             const uint32_t tk = umin(tot, rem);
-            if (tk > 0) take(-1, nseg == 1 ? -1 : s, tk);
+            if (tk > 0) take(seg3 ? kClsM : 0u, s << kClsS, -1, s, tk);
             rem -= tk;
         }
-        if (rem > 0) general = true;
+        if (rem > 0) over = 1;
+    }
+    // Ties in projected debt: lowest non-empty segment, then the oldest head.
+    PC_RUNS_FN int tie_break(uint64_t tied, bool seg3) {
+        uint32_t seg = 0;
+        if (seg3) {
+            const uint64_t s0 = W::ballot(cnt0 > 0u) & tied, s1 = W::ballot(cnt1 > 0u) & tied;
+            if (s0) tied = s0;
+            else if (s1) { tied = s1; seg = 1; }
+            else seg = 2;
+        }
+        int gs = W::ffs(tied);
+        if (tied & (tied - 1)) {
+            uint32_t best = kNone;
+            for (uint64_t tm = tied; tm; tm &= tm - 1) {
+                const int x = W::ffs(tm);
+                const uint32_t hp = head_pos(seg3 ? kOwnM | kClsM : kOwnM, ((uint32_t)x << kOwnS) | (seg << kClsS));
+                if (hp < best) { best = hp; gs = x; }
+            }
+        }
+        return gs;
     }
 
     // ------------------------------------------------------------ S3-FIFO
-    // Position of the oldest live run that the request does not pin.
-    PC_RUNS_FN uint32_t first_unpinned(Ring &r, uint32_t pin, uint32_t &lo, uint32_t &w) {
+    // A queue's runs that the request does not pin, oldest first, one chunk
+    // at a time in registers; at the end of a chunk it is read again, for
+    // what was appended to it meanwhile, before the next one.
+    struct Cursor {
+        vu lo, w;
+        uint64_t m;
+        uint32_t c;
+    };
+    PC_RUNS_FN void fill(const Window &r, uint32_t pin, Cursor &q) {
         W::sync();
-        for (uint32_t b = r.head; b < r.tail; b += 64) {
-            const vu pos = lane + b;
-            const vu at = pos & qm;
-            const vu wl = W::ld(r.w, at), ll = W::ld(r.lo, at), xl = W::ld(r.x, at);
-            const vb live = (pos < r.tail) & ((wl & kLen) > 0u);
-            if (b == r.head) {     // runs emptied at the front leave the window
-                const uint64_t lm = W::ballot(live);
-                if (!lm) { r.head = umin(b + 64, r.tail); continue; }
-                r.head += (uint32_t)W::ffs(lm);
-            }
-            const uint64_t m = W::ballot(live & (xl != pin));
-            if (m) {
-                const int l = W::ffs(m);
-                lo = W::rdl(ll, l);
-                w = W::rdl(wl, l);
-                return b + (uint32_t)l;
-            }
+        const vu at = lane + q.c * kStep;
+        q.lo = W::ld(r.p, at);
+        q.w = W::ld(r.p + kW, at);
+        q.m = W::ballot(W::ld(r.p + kXo, at) != pin) & W::ballot(q.lo != kNone);
+    }
+    PC_RUNS_FN bool next(const Window &r, uint32_t pin, Cursor &q) {
+        if (W::likely(q.m != 0)) return true;
+        fill(r, pin, q);
+        while (q.m == 0) {
+            q.c += 1;
+            if (64u * q.c >= r.tail) return false;
+            fill(r, pin, q);
         }
-        return kNone;
+        return true;
+    }
+    // The deepest k blocks of the run in lane l (word w, first id lo) leave it.
+    PC_RUNS_FN void shorten(Window &r, Cursor &q, int l, uint32_t lo, uint32_t w, uint32_t k) {
+        const bool all = k == (w & kLen);
+        const uint32_t nw = all ? kDead : w - k;
+        q.w = W::setlane(q.w, l, nw);
+        if (all) q.m &= q.m - 1;
+        put2(r, entry(64u * q.c + (uint32_t)l), all ? kNone : lo, nw);
     }
     PC_RUNS_FN void evict_s3(uint32_t e, uint32_t pin) {
         uint32_t rem = e;
-        while (rem > 0 && !general) {
-            const bool useS = (s_size >= P.s_cap && s_unp > 0) || m_unp == 0;
-            uint32_t lo = 0, w = 0;
-            if (useS) {
-                const uint32_t pos = first_unpinned(q0, pin, lo, w);
-                if (pos == kNone) { general = true; break; }
+        if (!room_for(q1, 32) || !ghost_room(32)) { over = 1; return; }
+        Cursor S, M;
+        S.c = M.c = 0;
+        M.m = 0;
+        M.lo = M.w = wv.vu0(0);
+        fill(q0, pin, S);
+        while (rem > 0) {
+            if (W::unlikely(q1.tail > q1.lim + kSlack / 2 || gh.tail > gh.lim + kSlack / 2)) {
+                if (!room_for(q1, 1) || !ghost_room(1)) { over = 1; return; }
+                M.c = 0;         // (positions changed)
+                M.m = 0;
+            }
+            uint32_t lo, w, k, again = 0;       // again: enter the main queue's tail
+            if (W::likely((s_size >= P.s_cap && s_unp > 0) || m_unp == 0)) {
+                if (!next(q0, pin, S)) { over = 1; return; }
+                const int l = W::ffs(S.m);
+                lo = W::rdl(S.lo, l);
+                w = W::rdl(S.w, l);
                 // how many of the run's blocks (deepest first) go before the
                 // one-at-a-time rule would look at the main queue
                 const uint32_t len = w & kLen;
                 const int32_t la = s_size - P.s_cap + 1 < s_unp ? s_size - P.s_cap + 1 : s_unp;
-                uint32_t k;
                 if ((int32_t)((w >> kFrqS) & 3u) >= P.move_thr) {
                     // (the first move gives the main queue an unpinned block)
                     k = umin(len, m_unp == 0 ? (la > 1 ? (uint32_t)la : 1u) : (uint32_t)la);
-                    wv.st1(q0.w, pos & qm, w - k);
-                    if (!room_for<true>(q1, 1)) break;
-                    push(q1, lo + len - k, k | (w & kAttr & ~(3u << kFrqS)), pin - 1u, true);
-                    s3_moves += k;
+                    again = k | (w & kAttr & ~(3u << kFrqS));
+                    n_moves = n_moves + k;
                     m_unp += (int32_t)k;
                 } else {
                     k = umin(len, rem);
                     if (m_unp > 0) k = umin(k, (uint32_t)la);
-                    wv.st1(q0.w, pos & qm, w - k);
-                    victims(w, k);
-                    if (P.g_cap > 0) {
-                        if (!ghost_room()) break;
-                        push(gh, lo + len - k, k, gseq, true);
-                    }
+                    if (P.g_cap > 0) push(gh, lo + len - k, k, gseq);
                     gseq += k;
-                    s3_gins += k;
-                    rem -= k;
+                    n_gins = n_gins + k;
                 }
                 s_size -= (int32_t)k;
                 s_unp -= (int32_t)k;
+                shorten(q0, S, l, lo, w, k);
             } else {
-                const uint32_t pos = first_unpinned(q1, pin, lo, w);
-                if (pos == kNone) { general = true; break; }
+                if (!next(q1, pin, M)) { over = 1; return; }
+                const int l = W::ffs(M.m);
+                lo = W::rdl(M.lo, l);
+                w = W::rdl(M.w, l);
                 const uint32_t len = w & kLen;
                 if ((w >> kFrqS) & 3u) {
-                    wv.st1(q1.w, pos & qm, w - len);
-                    if (!room_for<true>(q1, 1)) break;
-                    push(q1, lo, w - (1u << kFrqS), pin - 1u, true);
-                    s3_reins += len;
+                    k = len;
+                    again = w - (1u << kFrqS);
+                    n_reins = n_reins + len;
                 } else {
-                    const uint32_t k = umin(umin(len, rem), (uint32_t)m_unp);
-                    wv.st1(q1.w, pos & qm, w - k);
-                    victims(w, k);
+                    k = umin(umin(len, rem), (uint32_t)m_unp);
                     m_unp -= (int32_t)k;
-                    rem -= k;
                 }
+                shorten(q1, M, l, lo, w, k);
+            }
+            if (again) {
+                push(q1, lo + (w & kLen) - k, again, pin - 1u);
+            } else {
+                victims(is_lane(u_owner(w)), k);
+                rem -= k;
             }
         }
+        resident -= (int32_t)e;
     }
-    PC_RUNS_FN void victims(uint32_t w, uint32_t k) {
-        const vu d = W::sel(lane == u_owner(w), wv.vu0(k), wv.vu0(0));
-        evw = evw + W::widen(d);
-        res = res - d;
-        resident -= (int32_t)k;
-        ev_total += k;
-    }
-    // Ids of a ghost run that have left the window of the last g_cap
-    // insertions (its deepest ids went in first).
-    PC_RUNS_FN vu expired(vu w, vu base) const {
-        const vu age = wv.vu0(gseq - (uint32_t)P.g_cap) - base;     // signed
-        const vu len = w & kLen;
-        return W::sel((age >> 31) > 0u, wv.vu0(0), W::vmin(age, len));
-    }
-    // Room for one more ghost run: runs that left the window are dropped
-    // where they are first in the ring, and all of them by a compaction.
-    PC_RUNS_FN bool ghost_room() {
-        if (gh.tail + 1 - gh.head <= gh.lim) return true;
+    // Room for k more ghost runs: ids that have left the ghost (older than
+    // the last g_cap insertions; a run's deepest ids went in first) go first.
+    PC_RUNS_FN bool ghost_room(uint32_t k) {
+        if (W::likely(gh.tail + k <= gh.lim)) return true;
         W::sync();
-        for (uint32_t b = gh.head; b < gh.tail; b += 64) {
-            const vu pos = lane + b;
-            const vu at = pos & qm;
-            const vu w = W::ld(gh.w, at), base = W::ld(gh.x, at);
-            const vu ex = expired(w, base);
-            const vb in = (pos < gh.tail) & (ex > 0u);
-            W::st(in, gh.w, at, w - ex);
-            W::st(in, gh.x, at, base + ex);
+        const uint32_t nc = (gh.tail + 63u) >> 6;
+        for (uint32_t c = 0; c < nc; ++c) {
+            const vu at = lane + c * kStep;
+            const vu lo = W::ld(gh.p, at), w = W::ld(gh.p + kW, at), base = W::ld(gh.p + kXo, at);
+            const vu age = wv.vu0(gseq - (uint32_t)P.g_cap) - base;     // signed
+            const vu ex = W::sel((age >> 31) > 0u, wv.vu0(0), W::vmin(age, w & kLen));
+            const vb gone = ex == (w & kLen);
+            W::st_all(gh.p, at, W::sel(gone, wv.vu0(kNone), lo));
+            W::st_all(gh.p + kW, at, W::sel(gone, wv.vu0(kDead), w - ex));
+            W::st_all(gh.p + kXo, at, base + ex);
         }
-        return room_for<true>(gh, 1);
+        return room_for(gh, k);
     }
 
     // ------------------------------------------------------------ lookup
-    // Runs of ring r that the request's pieces [pa, pa + pl) meet: their
-    // leading part is filed in the list with its depth in the request, and
-    // taken off the run (kKeep: left there, its window position filed).  By
-    // (a) at the top a run meets one piece at most.
-    template <bool kX, bool kKeep, bool kGhost>
-    PC_RUNS_FN uint32_t match(Ring &r, uint32_t nm, uint32_t ringbit, uint32_t np, vu pa, vu pl, vu pc) {
-        W::sync();
-        for (uint32_t b = r.head; b < r.tail; b += 64) {
-            const vu pos = lane + b;
-            const vu at = pos & qm;
-            vu lo = W::ld(r.lo, at), w = W::ld(r.w, at);
-            vu x = w;
-            if (kX) x = W::ld(r.x, at);
-            const vb in = pos < r.tail;
-            vu len = W::sel(in, w & kLen, wv.vu0(0));
-            if (kGhost) {
-                const vu ex = expired(w, x);
-                len = len - W::sel(in, ex, wv.vu0(0));
-            } else if (!kKeep && b == r.head) {
-                const uint64_t lm = W::ballot(len > 0u);
-                r.head = lm ? r.head + (uint32_t)W::ffs(lm) : umin(b + 64, r.tail);
-            }
-            bool any = false;
-            for (uint32_t i = 0; i < np; ++i) {
-                const uint32_t a = W::rdl(pa, (int)i), L = W::rdl(pl, (int)i);
-                const vb m = ((lo - a) < L) & (len > 0u);
-                const uint64_t mm = W::ballot(m);
-                if (mm == 0) continue;
-                any = true;
-                const vu ov = W::vmin(len, wv.vu0(a + L) - lo);
-                const vu k = W::mbcnt(mm) + nm;
-                const vb ok = m & (k < (uint32_t)kRunList);
-                W::st(ok, xd, k, lo - a + W::rdl(pc, (int)i));
-                W::st(ok, xlo, k, lo);
-                W::st(ok, xw, k, (w & kAttr) | ov);
-                if (kX && !kKeep && !kGhost) W::st(ok, xx, k, x);
-                if (kKeep) W::st(ok, xx, k, (pos << 1) | ringbit);
-                W::st(ok, xi, k, wv.vu0(i));
-                nm += (uint32_t)W::popc(mm);
+    PC_RUNS_FN void file(uint32_t d, uint32_t lo, uint32_t w, uint32_t x, uint32_t i) {
+        if (W::unlikely(nm >= 64u)) { over = 1; return; }
+        md = W::setlane(md, (int)nm, d);
+        mlo = W::setlane(mlo, (int)nm, lo);
+        mw = W::setlane(mw, (int)nm, w);
+        if (kX) mx = W::setlane(mx, (int)nm, x);
+        mi = W::setlane(mi, (int)nm, i);
+        nm += 1;
+    }
+    // Pieces [pa, pa + pl) that meet a run of the group, as a mask.
+    PC_RUNS_FN uint64_t meets(const Four &lo, uint32_t np, vu pa, vu pl) const {
+        uint64_t pm = 0;
+        uint32_t i = 0;
+        do {
+            const uint32_t a = W::rdl(pa, (int)i), L = W::rdl(pl, (int)i);
+            const uint64_t any = (W::ballot(lo.v[0] - a < L) | W::ballot(lo.v[1] - a < L)) |
+                                 (W::ballot(lo.v[2] - a < L) | W::ballot(lo.v[3] - a < L));
+            pm |= any ? 1ull << i : 0ull;
+        } while (++i < np);
+        return pm;
+    }
+    // Runs of window r, group b (ids lo), that the pieces of mask pm meet:
+    // their leading part is filed with its depth in the request and taken off
+    // the run (kKeep: left there, its position and window filed).  By (a) at
+    // the top a run meets one piece at most.
+    template <bool kKeep, bool kGhost>
+    PC_RUNS_FN void meet(Window &r, uint32_t b, Four &lo, uint64_t pm, uint32_t ringbit, vu pa, vu pl, vu pc,
+                         uint32_t &found, uint32_t &far) {
+        for (; pm; pm &= pm - 1) {
+            const int i = W::ffs(pm);
+            const uint32_t a = W::rdl(pa, i), L = W::rdl(pl, i), depth = W::rdl(pc, i);
+#pragma unroll
+            for (uint32_t c = 0; c < 4; ++c) {
+                uint64_t m = W::ballot(lo.v[c] - a < L);
+                if (m == 0) continue;
+                const vu at = lane + (entry(b) + c * kStep);
+                vu w = W::ld(r.p + kW, at), x = w;
+                if (kX && !kKeep) x = W::ld(r.p + kXo, at);
+                do {
+                    const int l = W::ffs(m);
+                    m &= m - 1;
+                    const uint32_t el = W::rdl(lo.v[c], l), ew = W::rdl(w, l);
+                    uint32_t len = ew & kLen;
+                    if (kGhost) {       // (its last ids may have left the ghost)
+                        const int32_t age = (int32_t)(gseq - (uint32_t)P.g_cap - W::rdl(x, l));
+                        if (age > 0) len -= umin((uint32_t)age, len);
+                        if (len == 0) continue;
+                    }
+                    const uint32_t ov = umin(len, a + L - el), d = depth + (el - a);
+                    const uint32_t pos = b + 64u * c + (uint32_t)l;
+                    file(d, el, (ew & kAttr) | ov, kKeep ? pos << 1 | ringbit : kX ? W::rdl(x, l) : 0u, (uint32_t)i);
+                    found += ov;
+                    far = umax(far, d + ov);
+                    if (!kKeep) {
+                        const bool rest = (ew & kLen) != ov;
+                        lo.v[c] = W::setlane(lo.v[c], l, rest ? el + ov : kNone);
+                        w = W::setlane(w, l, rest ? ew - ov : kDead);
+                        if (kQ) count_queue(is_lane(u_owner(ew)), seg_of(ew), 0u - ov);
+                    }
+                } while (m);
                 if (!kKeep) {
-                    lo = W::sel(m, lo + ov, lo);
-                    w = W::sel(m, w - ov, w);
+                    store(r, b, c, 0, lo.v[c]);
+                    store(r, b, c, kW, w);
+                    if (!kGhost && b == 0) w4.v[c] = w;
                 }
-                len = W::sel(m, kKeep ? wv.vu0(0) : len - ov, len);
-            }
-            if (!kKeep && any) {
-                W::st(in, r.lo, at, lo);
-                W::st(in, r.w, at, w);
             }
         }
-        if (nm > (uint32_t)kRunList) general = true;
-        return nm;
+    }
+    // All groups of a window from position b on.
+    template <bool kKeep, bool kGhost>
+    PC_RUNS_FN void meet_from(Window &r, uint32_t b, uint32_t ringbit, uint32_t np, vu pa, vu pl, vu pc,
+                              uint32_t &found, uint32_t &far) {
+        for (; b < r.tail; b += 256) {
+            Four lo = load4(r, b, 0);
+            const uint64_t pm = meets(lo, np, pa, pl);
+            if (W::unlikely(pm != 0)) meet<kKeep, kGhost>(r, b, lo, pm, ringbit, pa, pl, pc, found, far);
+        }
     }
 
     // ------------------------------------------------------------ request
-    // `pid`, `pdepth`: the request's pieces, lane i piece i (i < np <= 64).
+    // `pid`, `plen`: the request's pieces as stored, lane i piece i (i < np).
     // `adm`: its prefix was admitted before; returns whether it is now.
-    PC_RUNS_FN bool request(uint32_t r, const RunReq &q, vu pid, vu pdepth, bool adm) {
+    // With `over` set, the instance is lost to this form.
+    PC_RUNS_FN bool request(uint32_t r, const RunReq &q, vu pid, vu plen, bool adm) {
         const uint32_t g = q.info & 0xFFu, c = (q.info >> 8) & 0xFFu;
-        const bool q1bit = ((q.info >> 16) & 1u) != 0;
-        const uint32_t np = q.np;
-        if (np > 64u || c >= (uint32_t)P.K) { general = true; return adm; }
-        refill(q.tick);
+        const uint32_t np = q.info >> 24;
+        // (the only place that compacts the free queue; S3-FIFO's main queue
+        // and ghost are looked at where they grow)
+        if (W::unlikely(np > kRunsMaxPieces || c >= (uint32_t)K())) { over = 1; return adm; }
+        if (W::unlikely(q0.tail + np > q0.lim) && !room_for(q0, np)) { over = 1; return adm; }
+        Four m4;                     // S3-FIFO: ids of the main queue's first group
+        if (kPol != S3) {
+            reload();
+        } else {
+            lo4 = load4(q0, 0, 0);
+            m4 = load4(q1, 0, 0);
+        }
+        refill(q.dt);
         const uint32_t room = (uint32_t)(kPol == SQ ? P.C / P.G : P.C);
         const uint32_t n = umin(q.n_full, room);
-        const vb me = lane == g;
+        const vu me = is_lane(g);
         const vu zu = wv.vu0(0);
 
-        // pieces cut to n blocks; their depths without the duplicates
-        vu pl, pc;
-        uint32_t nn = n;             // blocks that are no duplicates
-        if (np <= 1u) {
-            pl = W::sel(lane < np, wv.vu0(n), zu);
-            pc = zu;
-        } else {
-            const vu d = pdepth & ~kPieceDup;
-            const vu nx = W::sel(lane == np - 1u, wv.vu0(n), W::vmin(W::next_lane(d), wv.vu0(n)));
-            pl = W::sel((lane < np) & (d < nx) & (pdepth < kPieceDup), nx - d, zu);
-            const vu upto = W::scan(pl);
-            pc = upto - pl;
-            nn = W::rdl(upto, 63);
+        // pieces, their lengths without the duplicates, cut to n blocks
+        const vb real = lane < np;
+        vu pl = W::sel(real & ((plen & kPieceDup) == 0u), plen & kPieceLen, zu);
+        const vu pc = plen >> 16;
+        uint32_t nn = q.nn;          // blocks that are no duplicates
+        if (W::unlikely(n != q.n_full)) {
+            const vu raw = W::sel(real, plen & kPieceLen, zu);
+            const vu start = W::scan(raw) - raw;
+            pl = W::sel(start < n, W::vmin(pl, wv.vu0(n) - start), zu);
+            nn = W::wsum(pl);
         }
 
         // ---- lookup
-        uint32_t nm;
-        if (kPol == S3) {
-            nm = match<false, true, false>(q0, 0, 0, np, pid, pl, pc);
-            nm = match<false, true, false>(q1, nm, 1, np, pid, pl, pc);
-        } else {
-            nm = match<kPol == PS, false, false>(q0, 0, 0, np, pid, pl, pc);
-        }
-        if (general) return adm;
-        uint32_t hend = 0, norph = 0, npromo = 0, ngated = 0;
-        vu md = zu, mlo = zu, mw = zu, mx = zu, mi = zu;
-        uint64_t left = 0;           // met runs that are hits
-        if (nm > 0) {
-            W::sync();
-            md = W::ld(xd, lane & 63u);
-            mlo = W::ld(xlo, lane & 63u);
-            mw = W::ld(xw, lane & 63u);
-            if (kPol == PS || kPol == S3) mx = W::ld(xx, lane & 63u);
-            mi = W::ld(xi, lane & 63u);
-            const vb inl = lane < nm;
-            md = W::sel(inl, md, zu);
-            mw = W::sel(inl, mw, zu);
-            const vu ml = mw & kLen;
-            uint32_t found, far;
-            if (nm == 1) {
-                found = W::rdl(ml, 0);
-                far = W::rdl(md, 0) + found;
+        nm = 0;
+        uint32_t found = 0, far = 0;
+        {
+            const uint64_t pm = meets(lo4, np, pid, pl);
+            if (kPol == S3) {
+                const uint64_t pm1 = meets(m4, np, pid, pl);
+                if (W::unlikely((pm | pm1) != 0)) {
+                    meet<true, false>(q0, 0, lo4, pm, 0, pid, pl, pc, found, far);
+                    meet<true, false>(q1, 0, m4, pm1, 1, pid, pl, pc, found, far);
+                }
+                if (W::unlikely(umax(q0.tail, q1.tail) > 256)) {
+                    meet_from<true, false>(q0, 256, 0, np, pid, pl, pc, found, far);
+                    meet_from<true, false>(q1, 256, 1, np, pid, pl, pc, found, far);
+                }
             } else {
-                found = W::wsum(ml);
-                far = W::wmax(md + ml);
+                if (W::unlikely(pm != 0)) meet<false, false>(q0, 0, lo4, pm, 0, pid, pl, pc, found, far);
+                if (W::unlikely(q0.tail > 256)) meet_from<false, false>(q0, 256, 0, np, pid, pl, pc, found, far);
             }
-            if (found == far) hend = found;      // disjoint parts that end at their sum: no gap
-            else
+        }
+        uint32_t hend = found;       // disjoint parts that end at their sum: no gap
+        uint32_t norph = 0, npromo = 0, ngated = 0;
+        uint64_t hits = 0;           // met runs that are hits
+        uint32_t hitS = 0, hitM = 0;
+        if (W::unlikely(nm > 0)) {
+            const uint64_t inl = ~0ull >> (64u - nm);
+            hits = inl;
+            if (found != far) {
+                hend = 0;
                 for (uint32_t it = 0; it < nm; ++it) {
-                    const uint64_t m = W::ballot(inl & (md == hend));
+                    const uint64_t m = W::ballot(md == hend) & inl;
                     if (!m) break;
-                    hend += W::rdl(ml, W::ffs(m));
+                    hend += W::rdl(mw, W::ffs(m)) & kLen;
                 }
-            norph = found - hend;
-            left = W::ballot(inl & (md < hend));
-            const uint64_t orph = W::ballot(inl) & ~left;
-            if (kPol == PS || kPol == SQ)        // hits and orphans leave their queue
-                for (uint32_t k = 0; k < nm; ++k) {
-                    const uint32_t w = W::rdl(mw, (int)k);
-                    count_queue(u_owner(w), seg_of(w), 0u - (w & kLen));
+                norph = found - hend;
+                hits = W::ballot(md < hend) & inl;
+                for (uint64_t om = inl & ~hits; om; om &= om - 1) {
+                    const uint32_t w = W::rdl(mw, W::ffs(om));
+                    res = W::mad24(is_lane(u_owner(w)), 0u - (w & kLen), res);
                 }
-            for (uint64_t om = orph; om; om &= om - 1) {
-                const uint32_t w = W::rdl(mw, W::ffs(om));
-                res = res - W::sel(lane == u_owner(w), wv.vu0(w & kLen), zu);
+                resident -= (int32_t)norph;
             }
-            resident -= (int32_t)norph;
-            if (kPol == PS && q1bit && adm) {
+            if (kPol == PS && ((q.info >> 16) & 1u) && adm) {
                 // Eq. 4: proven reuse of a block of (g, c, p), not yet REUSE
-                const vb el = inl & (md < hend) & (owner(mw) == g) & (((mw >> kConS) & 3u) == c) &
-                              (cls(mw) != kReuseCls) & (mx == q.prefix);
-                const uint64_t em = W::ballot(el);
+                const vu mine = (mw >> kOwnS) & 255u;      // owner and contract
+                const vb el = (mine == (g | (c << 6))) & (mx == q.prefix);
+                const vb once = (mw & kClsM) != (kReuseCls << kClsS);
+                const uint64_t em = W::ballot(el) & W::ballot(once) & hits;
                 if (em) {
-                    const uint32_t ne = W::wsum(W::sel(el, ml, zu));
+                    uint32_t ne = 0;
+                    for (uint64_t t = em; t; t &= t - 1) ne += W::rdl(mw, W::ffs(t)) & kLen;
                     const bool open = W::rdl64(raw_debt(), (int)g) <= P.eps || (P.flags & 2);
                     if (open) {
                         npromo = ne;
-                        mw = W::sel(el, (mw & ~(3u << kClsS)) | (kReuseCls << kClsS), mw);
+                        mw = W::sel(W::of_mask(em), (mw & ~kClsM) | (kReuseCls << kClsS), mw);
                     } else {
                         ngated = ne;
                     }
                 }
             }
+            if (kPol == S3) touch_s3(r, hits, hitS, hitM);
         }
         const uint32_t m = nn - hend;
-        uint32_t hitS = 0, hitM = 0;
-        if (kPol == S3) touch_s3(r, nm, left, mlo, mw, mx, hitS, hitM);
-        if (general) return adm;
 
         // ---- reclamation
         int32_t e;
         if (kPol == SQ) e = (int32_t)m - ((int32_t)room - (int32_t)W::rdl(res, (int)g));
         else e = (int32_t)m - (P.C - resident);
-        if (e < 0) e = 0;
-        if (e > 0) {
-            if (kPol == LRU) take(-1, -1, (uint32_t)e);
+        if (W::likely(e > 0)) {
+            if (kPol == LRU) take(0u, 0u, -1, 0u, (uint32_t)e);
             else if (kPol == PS) evict_ps((uint32_t)e);
-            else if (kPol == SQ) take((int32_t)g, -1, (uint32_t)e);
+            else if (kPol == SQ) take(kOwnM, g << kOwnS, (int32_t)g, 0u, (uint32_t)e);
             else evict_s3((uint32_t)e, r + 1u);
-            if (general) return adm;
-            c_evc = c_evc + W::widen(W::sel(me, wv.vu0((uint32_t)e), zu));
+            n_evc = W::mad24(me, (uint32_t)e, n_evc);
+        } else {
+            e = 0;
         }
 
         // ---- charge (Eq. 2), class of the new blocks, admission
         uint32_t nw = g << kOwnS;            // attributes of the new blocks
-        bool adm_now = adm;
-        if (m > 0) {
-            const int64_t cost = (int64_t)m * 65536;
-            int64_t B = 0;
+        const int32_t cost = -(int32_t)(m << 16);     // m <= 32,767
 #pragma unroll
-            for (int cc = 0; cc < 4; ++cc)
-                if (cc < P.K && (uint32_t)cc == c) {
-                    E[cc] = W::sel(me, E[cc] - cost, E[cc]);
-                    if (kPol == PS) B = W::rdl64(E[cc], (int)g);
+        for (int cc = 0; cc < kC; ++cc)
+            if (kK1 || (uint32_t)cc == c) {
+                E[cc] = W::mad64(me, cost, E[cc]);
+                if (kPol == PS) {
+                    const int64_t bal = W::rdl64(E[cc], (int)g);
+                    const uint32_t cl = (bal < -P.eps || !adm) ? kProbCls : kNormalCls;
+                    nw |= (c << kConS) | (cl << kClsS);
                 }
-            if (kPol == PS) {
-                const uint32_t cl = (B < -P.eps || !adm) ? kProbCls : kNormalCls;
-                nw |= (c << kConS) | (cl << kClsS);
             }
-            adm_now = true;
-            res = res + W::sel(me, wv.vu0(m), zu);
-            resident += (int32_t)m;
-        }
+        res = W::mad24(me, m, res);
+        resident += (int32_t)m;
 
         // ---- new blocks and released blocks enter the queue, deepest first
         if (kPol == S3) {
@@ -735,29 +873,47 @@ struct RunReplay {
             s_unp += (int32_t)hitS;
             m_unp += (int32_t)hitM;
         } else {
-            release(np, pid, pl, pc, hend, nw, m, q.prefix, left, md, mlo, mw, mx, mi);
+            if (kQ) count_queue(me, seg_of(nw), m);
+            release(np, pid, pl, pc, hend, nw, m, q.prefix, hits);
         }
-        if (general) return adm;
 
         // ---- counters and the accounting of every group
-        c_req = c_req + W::widen(W::sel(me, wv.vu0(1), zu));
-        c_probe = c_probe + W::widen(W::sel(me, wv.vu0(n), zu));
-        c_hit = c_hit + W::widen(W::sel(me, wv.vu0(hend), zu));
-        if (nn != n) c_dup = c_dup + W::widen(W::sel(me, wv.vu0(n - nn), zu));
-        if (n != q.n_full) c_trunc = c_trunc + W::widen(W::sel(me, wv.vu0(q.n_full - n), zu));
-        if (norph) c_orph = c_orph + W::widen(W::sel(me, wv.vu0(norph), zu));
-        if (npromo) c_promo = c_promo + W::widen(W::sel(me, wv.vu0(npromo), zu));
-        if (ngated) c_gated = c_gated + W::widen(W::sel(me, wv.vu0(ngated), zu));
+        n_req = n_req + me;
+        n_probe = W::mad24(me, n, n_probe);
+        n_hit = W::mad24(me, hend, n_hit);
+        if (W::unlikely(((nn ^ n) | (n ^ q.n_full) | norph | npromo | ngated) != 0)) {
+            c_dup = c_dup + W::widen(W::mad24(me, n - nn, zu));
+            c_trunc = c_trunc + W::widen(me) * (int64_t)(q.n_full - n);
+            c_orph = c_orph + W::widen(W::mad24(me, norph, zu));
+            c_promo = c_promo + W::widen(W::mad24(me, npromo, zu));
+            c_gated = c_gated + W::widen(W::mad24(me, ngated, zu));
+        }
         const vl d = raw_debt();
         d_sum = d_sum + d;
         d_max = W::vmax(d_max, d);
         res_max = W::vmax(res_max, res);
-        if (resident > rmax) rmax = resident;
+        rmax = W::vmax(rmax, wv.vu0((uint32_t)resident));
         last_h = (int32_t)hend;
         last_m = (int32_t)m;
         last_e = e;
         last_o = (int32_t)norph;
-        return adm_now;
+        return adm || m > 0;
+    }
+    // 32-bit counters into the 64-bit ones, once in kFlush requests at least
+    // (a request adds at most 32,767 to each, and reinserts every block three
+    // times at most).
+    PC_RUNS_FN void flush() {
+        c_evw = c_evw + W::widen(evw);
+        c_req = c_req + W::widen(n_req);
+        c_probe = c_probe + W::widen(n_probe);
+        c_hit = c_hit + W::widen(n_hit);
+        c_evc = c_evc + W::widen(n_evc);
+        evw = n_req = n_probe = n_hit = n_evc = wv.vu0(0);
+        c_moves = c_moves + W::widen(n_moves);
+        c_reins = c_reins + W::widen(n_reins);
+        c_ghits = c_ghits + W::widen(n_ghits);
+        c_gins = c_gins + W::widen(n_gins);
+        n_moves = n_reins = n_ghits = n_gins = W::hold(wv.vu0(0));
     }
 
     // The request's blocks enter the free queue deepest first: new blocks
@@ -765,48 +921,34 @@ struct RunReplay {
     // that continue each other inside a piece, with equal attributes, become
     // one run again, and so do the last hit and the new blocks behind it.
     PC_RUNS_FN void release(uint32_t np, vu pid, vu pl, vu pc, uint32_t hend, uint32_t nw, uint32_t m, uint32_t p,
-                            uint64_t hits, vu md, vu mlo, vu mw, vu mx, vu mi) {
+                            uint64_t hits) {
         const uint32_t nh = (uint32_t)W::popc(hits);
-        constexpr bool kX = kPol == PS;
-        if (!room_for<kX>(q0, np + nh)) return;
         uint32_t cd = hend;                                   // depth reached, going up
-        uint32_t clo = 0, clen = 0, cat = 0, cx = 0, cp = kNone;    // run being built
-        if (m > 0) {
-            const vb isn = (pl > 0u) & (pc + pl > hend);
-            const uint64_t nmask = W::ballot(isn);
-            // the shallowest new piece may continue a hit; the others are whole
-            const int sh = W::ffs(nmask);
-            const uint64_t deep = nmask & (nmask - 1);
-            if (deep) {
-                const uint32_t nd = (uint32_t)W::popc(deep);
-                const vu at = (wv.vu0(q0.tail + nd - 1u) - W::mbcnt(deep)) & qm;
-                const vb isd = isn & (lane > (uint32_t)sh);
-                W::st(isd, q0.lo, at, pid);
-                W::st(isd, q0.w, at, pl | nw);
-                if (kX) W::st(isd, q0.x, at, wv.vu0(p));
-                q0.tail += nd;
-            }
-            const uint32_t spc = W::rdl(pc, sh), spl = W::rdl(pl, sh);
-            const uint32_t off = hend > spc ? hend - spc : 0u;
-            clo = W::rdl(pid, sh) + off;
-            clen = spl - off;
-            cat = nw;
-            cx = p;
-            cp = (uint32_t)sh;
-            if (kPol == PS || kPol == SQ) count_queue(u_owner(nw), seg_of(nw), m);
+        uint32_t clo = 0, clen = 0, cat = nw, cx = p, cp = kNone;    // run being built
+        // deepest piece first; the shallowest new one may continue a hit
+        const vb isn = pl > 0u;
+        for (uint64_t nmask = W::ballot(isn & (pc + pl > hend)); nmask;) {
+            const int i = 63 - W::clz(nmask);
+            nmask &= ~(1ull << i);
+            const uint32_t at = W::rdl(pc, i);
+            const uint32_t off = hend > at ? hend - at : 0u;
+            clo = W::rdl(pid, i) + off;
+            clen = W::rdl(pl, i) - off;
+            cp = (uint32_t)i;
+            if (nmask) push(q0, clo, clen | cat, cx);
         }
         for (uint32_t it = 0; it < nh; ++it) {
             const uint64_t mk = W::ballot(md + (mw & kLen) == cd) & hits;
-            if (!mk) { general = true; return; }    // cannot happen: the hits tile [0, hend)
+            if (W::unlikely(!mk)) { over = 1; return; }        // cannot happen: the hits tile [0, hend)
             const int l = W::ffs(mk);
             const uint32_t w = W::rdl(mw, l), lo = W::rdl(mlo, l), len = w & kLen;
             const uint32_t x = kX ? W::rdl(mx, l) : 0u, i = W::rdl(mi, l);
-            if (kPol == PS || kPol == SQ) count_queue(u_owner(w), seg_of(w), len);
-            if (i == cp && lo + len == clo && (w & kAttr) == cat && x == cx) {
+            if (kQ) count_queue(is_lane(u_owner(w)), seg_of(w), len);
+            if (i == cp && lo + len == clo && (w & kAttr) == cat && (!kX || x == cx)) {
                 clo = lo;
                 clen += len;
             } else {
-                if (clen) push(q0, clo, clen | cat, cx, kX);
+                if (clen) push(q0, clo, clen | cat, cx);
                 clo = lo;
                 clen = len;
                 cat = w & kAttr;
@@ -815,114 +957,94 @@ struct RunReplay {
             }
             cd -= len;
         }
-        if (clen) push(q0, clo, clen | cat, cx, kX);
+        if (clen) push(q0, clo, clen | cat, cx);
     }
 
     // S3-FIFO: hits stay in their queue, one access more, pinned for the
     // request; a run that is met in part becomes two, its deeper part first.
-    // Orphans leave.
-    PC_RUNS_FN void touch_s3(uint32_t r, uint32_t nm, uint64_t hits, vu mlo, vu mw, vu mx, uint32_t &hitS,
-                             uint32_t &hitM) {
-        if (nm == 0) return;
-        const vu zu = wv.vu0(0);
-        const vb inl = lane < nm, isM = (mx & 1u) > 0u, isH = W::of_mask(hits);
-        const vu at = (mx >> 1) & qm, ov = mw & kLen;
-        const vu full = W::sel(isM, W::ld(q1.w, at), W::ld(q0.w, at));
-        const vu rest = (full & kLen) - ov;
-        const vu f = (full >> kFrqS) & 3u;
-        const vu hw = (full & (kAttr & ~(3u << kFrqS))) | (W::vmin(f + 1u, wv.vu0(3)) << kFrqS) | ov;
-        const vb whole = inl & isH & (rest == 0u), orph = inl & (!isH);
-        touch_ring(q0, (!isM) & whole, (!isM) & orph, at, hw, mlo + ov, (full & kAttr) | rest, r + 1u);
-        touch_ring(q1, isM & whole, isM & orph, at, hw, mlo + ov, (full & kAttr) | rest, r + 1u);
-        const uint32_t all = W::wsum(W::sel(inl & isH, ov, zu));
-        hitM = W::wsum(W::sel(inl & isH & isM, ov, zu));
-        hitS = all - hitM;
-        s_unp -= (int32_t)hitS;
-        m_unp -= (int32_t)hitM;
-        if (W::ballot(orph)) {
-            const uint32_t oM = W::wsum(W::sel(orph & isM, ov, zu)), oS = W::wsum(W::sel(orph & (!isM), ov, zu));
-            s_size -= (int32_t)oS;
-            s_unp -= (int32_t)oS;
-            m_unp -= (int32_t)oM;
-        }
-        // runs met in part, last window position first: a split moves only
-        // the runs behind it
-        uint64_t part = W::ballot(inl & isH & (rest > 0u));
-        while (part) {
-            const vu key = W::sel(W::of_mask(part), (mx >> 1) + 1u, zu);
-            const uint64_t tm = W::ballot(key == W::wmax(key)) & part;
-            const int k = W::ffs(tm);
-            part &= ~(1ull << k);
-            const uint32_t pos = W::rdl(mx, k) >> 1, lo = W::rdl(mlo, k), o = W::rdl(ov, k);
-            const uint32_t dw = W::rdl(full, k) - o, tw = W::rdl(hw, k);
-            if (W::rdl(mx, k) & 1u) split(q1, pos, lo, o, dw, tw, r + 1u);
-            else split(q0, pos, lo, o, dw, tw, r + 1u);
+    // Orphans leave.  Runs of a window go in the order of their positions,
+    // last first: a split moves only the runs behind it.
+    PC_RUNS_FN void touch_s3(uint32_t r, uint64_t hits, uint32_t &hitS, uint32_t &hitM) {
+        uint64_t left = ~0ull >> (64u - nm);
+        while (left) {
+            int k = W::ffs(left);
+            if (left & (left - 1)) {
+                const vu key = W::sel(W::of_mask(left), mx + 1u, wv.vu0(0));
+                k = W::ffs(W::ballot(key == W::wmax(key)) & left);
+            }
+            left &= ~(1ull << k);
+            const uint32_t at = W::rdl(mx, k), lo = W::rdl(mlo, k), ov = W::rdl(mw, k) & kLen;
+            const bool hit = (hits >> k) & 1u;
+            if (at & 1u) {
+                m_unp -= (int32_t)ov;
+                if (hit) hitM += ov;
+                touch_run(q1, at >> 1, lo, ov, hit, r + 1u);
+            } else {
+                s_unp -= (int32_t)ov;
+                if (hit) hitS += ov; else s_size -= (int32_t)ov;
+                touch_run(q0, at >> 1, lo, ov, hit, r + 1u);
+            }
         }
     }
-    PC_RUNS_FN void touch_ring(Ring &rg, vb whole, vb orph, vu at, vu hw, vu olo, vu ow, uint32_t pin) {
-        W::st(whole, rg.w, at, hw);
-        W::st(whole, rg.x, at, wv.vu0(pin));
-        W::st(orph, rg.lo, at, olo);
-        W::st(orph, rg.w, at, ow);
-    }
-    PC_RUNS_FN void split(Ring &rg, uint32_t pos, uint32_t lo, uint32_t o, uint32_t dw, uint32_t tw, uint32_t pin) {
-        if (rg.tail + 1u - rg.head > P.q) { general = true; return; }
-        open_gap(rg, pos);
-        wv.st1(rg.lo, pos & qm, lo + o);
-        wv.st1(rg.w, pos & qm, dw);
-        wv.st1(rg.lo, (pos + 1u) & qm, lo);
-        wv.st1(rg.w, (pos + 1u) & qm, tw);
-        wv.st1(rg.x, (pos + 1u) & qm, pin);
+    PC_RUNS_FN void touch_run(Window &rg, uint32_t pos, uint32_t lo, uint32_t ov, bool hit, uint32_t pin) {
+        W::sync();
+        uint32_t at = entry(pos);
+        const uint32_t full = wv.ld1(rg.p + kW, at);
+        const uint32_t rest = (full & kLen) - ov;
+        if (W::unlikely(!hit)) {
+            put2(rg, at, rest ? lo + ov : kNone, rest ? full - ov : kDead);
+            return;
+        }
+        const uint32_t f = (full >> kFrqS) & 3u;
+        const uint32_t hw = (full & kAttr & ~(3u << kFrqS)) | ((f < 3u ? f + 1u : 3u) << kFrqS) | ov;
+        if (W::unlikely(rest)) {
+            if (rg.tail >= W::uni(rg.cap)) { over = 1; return; }
+            open_gap(rg, pos);
+            put2(rg, at, lo + ov, full - ov);
+            at = entry(pos + 1u);
+        }
+        put3(rg, at, lo, hw, pin);
     }
     // New blocks enter the small queue, or the main queue where the ghost
     // remembers them, deepest first.
     PC_RUNS_FN void insert_s3(uint32_t r, uint32_t np, vu pid, vu pl, vu pc, uint32_t hend, uint32_t nw, uint32_t m) {
         const vu zu = wv.vu0(0);
         const vb isn = (pl > 0u) & (pc + pl > hend);
-        const vu off = W::sel(isn & (wv.vu0(hend) > pc), wv.vu0(hend) - pc, zu);
+        const vu off = W::sel(pc < hend, wv.vu0(hend) - pc, zu);
         const vu a = pid + off, L = W::sel(isn, pl - off, zu);
-        uint32_t ng = 0;
-        if (P.g_cap > 0) ng = match<true, false, true>(gh, 0, 0, np, a, L, zu);
-        if (general) return;
-        const uint64_t nmask = W::ballot(isn);
-        const uint32_t nnew = (uint32_t)W::popc(nmask);
-        if (!room_for<true>(q0, nnew + ng)) return;
-        uint32_t nghost = 0;
-        if (ng == 0) {
-            const vu at = (wv.vu0(q0.tail + nnew - 1u) - W::mbcnt(nmask)) & qm;
-            W::st(isn, q0.lo, at, a);
-            W::st(isn, q0.w, at, L | nw);
-            W::st(isn, q0.x, at, wv.vu0(r));
-            q0.tail += nnew;
-        } else {
-            if (!room_for<true>(q1, ng)) return;
-            W::sync();
-            const vb inl = lane < ng;
-            const vu glo = W::ld(xlo, lane & 63u), gl = W::ld(xw, lane & 63u) & kLen, gi = W::ld(xi, lane & 63u);
-            for (uint64_t pm = nmask; pm; ) {
-                const int i = 63 - W::clz(pm);
-                pm &= ~(1ull << i);
-                const uint32_t lo = W::rdl(a, i);
-                uint32_t end = lo + W::rdl(L, i);
-                uint64_t gm = W::ballot(inl & (gi == (uint32_t)i));
-                while (gm) {       // the ghost's parts of this piece, deepest first
-                    const vu key = W::sel(W::of_mask(gm), glo - lo + 1u, zu);
-                    const uint32_t top = W::wmax(key);
-                    const int l = W::ffs(W::ballot(key == top) & gm);
-                    gm &= ~(1ull << l);
-                    const uint32_t x0 = W::rdl(glo, l), xl = W::rdl(gl, l);
-                    if (x0 + xl < end) push(q0, x0 + xl, (end - x0 - xl) | nw, r, true);
-                    push(q1, x0, xl | nw, r, true);
-                    nghost += xl;
-                    end = x0;
+        nm = 0;
+        uint32_t nghost = 0, far = 0;
+        if (P.g_cap > 0) meet_from<false, true>(gh, 0, 0, np, a, L, zu, nghost, far);
+        uint64_t nmask = W::ballot(isn);
+        uint64_t inl = 0;
+        if (W::unlikely(nm > 0)) {
+            if (over || q0.tail + (uint32_t)W::popc(nmask) + nm > W::uni(q0.cap) || q1.tail + nm > W::uni(q1.cap)) { over = 1; return; }
+            inl = ~0ull >> (64u - nm);
+        }
+        while (nmask) {
+            const int i = 63 - W::clz(nmask);
+            nmask &= ~(1ull << i);
+            const uint32_t lo = W::rdl(a, i);
+            uint32_t end = lo + W::rdl(L, i);
+            uint64_t gm = inl ? W::ballot(mi == (uint32_t)i) & inl : 0ull;
+            while (gm) {       // the ghost's parts of this piece, deepest first
+                int l = W::ffs(gm);
+                if (gm & (gm - 1)) {
+                    const vu key = W::sel(W::of_mask(gm), mlo - lo + 1u, zu);
+                    l = W::ffs(W::ballot(key == W::wmax(key)) & gm);
                 }
-                if (end > lo) push(q0, lo, (end - lo) | nw, r, true);
+                gm &= ~(1ull << l);
+                const uint32_t x0 = W::rdl(mlo, l), xl = W::rdl(mw, l) & kLen;
+                if (x0 + xl < end) push(q0, x0 + xl, (end - x0 - xl) | nw, r);
+                push(q1, x0, xl | nw, r);
+                end = x0;
             }
+            if (end > lo) push(q0, lo, (end - lo) | nw, r);
         }
         s_size += (int32_t)(m - nghost);
         s_unp += (int32_t)(m - nghost);
         m_unp += (int32_t)nghost;
-        s3_ghits += nghost;
+        n_ghits = n_ghits + nghost;
     }
 };
 

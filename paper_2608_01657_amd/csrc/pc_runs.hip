@@ -24,10 +24,11 @@ namespace {
 
 #define DEV __device__ __forceinline__
 #define GLOBAL __attribute__((address_space(1)))
-#define CONST_AS __attribute__((address_space(4)))
 #define LDS_AS __attribute__((address_space(3)))
 
 // ------------------------------------------------------------ wavefront
+// (LLVM's intrinsic; clang has no builtin for it)
+extern "C" __device__ uint32_t pc_writelane(uint32_t x, uint32_t l, uint32_t v) __asm("llvm.amdgcn.writelane.i32");
 struct DevWave {
     using vu = uint32_t;
     using vl = int64_t;
@@ -40,7 +41,6 @@ struct DevWave {
     // compiler from moving a lane's load above another lane's store
     DEV static void sync() {
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
-        __builtin_amdgcn_wave_barrier();
     }
     DEV static uint64_t ballot(bool b) { return __ballot(b); }
     DEV static bool of_mask(uint64_t m) { return (m >> __lane_id()) & 1ull; }
@@ -102,6 +102,13 @@ struct DevWave {
     DEV static uint32_t mbcnt(uint64_t m) {
         return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
     }
+    DEV static uint32_t prev_lane(uint32_t v) {    // lane i: the value of lane i - 1
+        return (uint32_t)__builtin_amdgcn_ds_bpermute((int)(((uint32_t)__lane_id() - 1u) << 2), (int)v);
+    }
+    DEV static uint32_t setlane(uint32_t v, int l, uint32_t x) {
+        return pc_writelane(x, (uint32_t)l, v);
+    }
+    DEV static void st_all(Lds p, uint32_t at, uint32_t x) { p[at] = x; }
     DEV static uint32_t next_lane(uint32_t v) {    // lane i: the value of lane i + 1
         return (uint32_t)__builtin_amdgcn_ds_bpermute((int)(((uint32_t)__lane_id() + 1u) << 2), (int)v);
     }
@@ -110,15 +117,40 @@ struct DevWave {
         const uint64_t x = (uint64_t)a, y = (uint64_t)w;
         return (int64_t)((__umul64hi(x, y) << 48) | ((x * y) >> 16));
     }
-    DEV static uint64_t mulhi(uint64_t a, uint64_t b) { return __umul64hi(a, b); }
+    DEV static int64_t mul_sat62(int64_t a, uint32_t b) {     // min(a b, 2^62) for a below 2^41
+        const uint64_t lo = (uint64_t)a * b;
+        return __umul64hi((uint64_t)a, b) != 0 || lo > (1ull << 62) ? (int64_t)1 << 62 : (int64_t)lo;
+    }
+    // keep a uniform value in a vector register; and back
+    template <class T>
+    DEV static T hold(T x) {
+        asm volatile("" : "+v"(x));
+        return x;
+    }
+    DEV static uint32_t uni(uint32_t v) { return rfl(v); }
     DEV static uint64_t udiv(uint64_t a, uint64_t b) { return a / b; }
     DEV static uint32_t ld(Lds p, uint32_t at) { return p[at]; }
     DEV static void st(bool m, Lds p, uint32_t at, uint32_t x) {
         if (m) p[at] = x;
     }
-    DEV void st1(Lds p, uint32_t at, uint32_t x) {
-        if (__lane_id() == 0) p[at] = x;
+    DEV static uint32_t ld_if(bool m, Lds p, uint32_t at) { return m ? p[at] : 0u; }
+    DEV uint32_t ld1(Lds p, uint32_t at) const { return rfl(p[at]); }
+    // one word by lane 0; the others write a word of their own in scratch,
+    // so that no branch or execution mask is needed
+    template <int N>
+    DEV void st1(Lds p, uint32_t at, Lds scratch, uint32_t x, uint32_t y, uint32_t z) const {
+        const Lds to = __lane_id() == 0 ? p + at : scratch + __lane_id();
+        to[0] = x;
+        to[64] = y;
+        if (N > 2) to[128] = z;
     }
+    // a is 0 or 1 (or small), |b| < 2^23
+    DEV static uint32_t mad24(uint32_t a, uint32_t b, uint32_t c) {
+        return (uint32_t)(__mul24((int)a, (int)b) + (int)c);
+    }
+    DEV static int64_t mad64(uint32_t a, int32_t b, int64_t c) { return (int64_t)(int32_t)a * (int64_t)b + c; }
+    DEV static bool likely(bool x) { return __builtin_expect(x, true); }
+    DEV static bool unlikely(bool x) { return __builtin_expect(x, false); }
 };
 
 // ------------------------------------------------------------ analysis
@@ -155,14 +187,15 @@ DEV int32_t find_block(const T *a, int32_t n, uint32_t b, uint32_t T::*blk0) {
 }
 
 // Request r of a trace: false if the general kernel would refuse it (the
-// contract aside, which depends on the instance).
+// contract aside, which depends on the instance), or if its tick is 2^32 or
+// more behind the one before it.
 DEV bool request_ok(const DevTrace &T, int64_t r, int64_t &ko, int64_t &nf) {
     ko = T.key_off[r];
     nf = T.key_off[r + 1] - ko;
     const int64_t t = T.tick ? T.tick[r] : r;
     const int64_t tp = T.tick && r > 0 ? T.tick[r - 1] : 0;
     return !(T.group[r] >= T.n_groups || (int64_t)T.prefix[r] >= T.n_prefix || ko < 0 || nf < 0 ||
-             ko + nf > T.n_keys || nf > T.max_req_blocks || t < 0 || t < tp);
+             ko + nf > T.n_keys || nf > T.max_req_blocks || t < 0 || t < tp || t - tp > (int64_t)0xFFFFFFFF);
 }
 
 // Blocks [0, nb_pos): positions of the key buffers; then requests.
@@ -264,14 +297,14 @@ __global__ __launch_bounds__(kT) void runs_list(RunsArgs A) {
         np += (uint32_t)__popcll(m);
     }
     DevWave::sync();
-    uint32_t pid = 0, dep = 0;
+    uint32_t pid = 0, dep = 0, nn = (uint32_t)nf;
     if (np <= 64u) {
         const bool in = lane < np;
         if (in) { pid = s_id[w][lane]; dep = s_dep[w][lane]; }
         bool dup = false;
+        const uint32_t nx = DevWave::next_lane(dep);
+        const uint32_t len = in ? (lane + 1u < np ? nx : (uint32_t)nf) - dep : 0u;
         if (np > 1u) {
-            const uint32_t nx = DevWave::next_lane(dep);
-            const uint32_t len = (lane + 1u < np ? nx : (uint32_t)nf) - dep;
             for (uint32_t i = 0; i + 1 < np; ++i) {
                 const uint32_t a = DevWave::rdl(pid, (int)i), la = DevWave::rdl(len, (int)i);
                 const bool same = in && lane > i && pid == a;
@@ -290,42 +323,188 @@ __global__ __launch_bounds__(kT) void runs_list(RunsArgs A) {
             if (lane == 0) A.tflag[ti] = 1;
             return;
         }
+        const uint32_t own = dup ? 0u : len;
+        const uint32_t upto = DevWave::scan(own), before = upto - own;
+        nn = DevWave::rdl(upto, 63);
         if (in) {
             RunPiece p;
             p.id = pid;
-            p.depth = dep | (dup ? kPieceDup : 0u);
+            p.len = (len < kPieceLen ? len : kPieceLen) | (dup ? kPieceDup : 0u) |
+                    (before < 0xFFFFu ? before : 0xFFFFu) << 16;
             ((RunPiece *)(A.table + B.tab0))[ko + lane] = p;
         }
     }
     if (lane == 0) {
         RunReq q;
         q.n_full = (uint32_t)nf;
-        q.np = np;
         q.prefix = T.prefix[r];
         q.info = (uint32_t)T.group[r] | ((uint32_t)T.contract[r] << 8) |
-                 (A.first[R.first0 + q.prefix] < (uint32_t)r ? 1u << 16 : 0u);
-        q.tick = T.tick ? T.tick[r] : r;
-        q.ko = (uint32_t)ko;
-        q.pad = 0;
+                 (A.first[R.first0 + q.prefix] < (uint32_t)r ? 1u << 16 : 0u) |
+                 (np <= kRunsMaxPieces ? np : 255u) << 24;
+        q.dt = T.tick ? (uint32_t)(T.tick[r] - (r > 0 ? T.tick[r - 1] : 0)) : r > 0 ? 1u : 0u;
+        q.ko = np > 0 ? (uint32_t)ko : 0u;
+        q.nn = nn;
+        q.pad[0] = q.pad[1] = 0u;
         A.req[R.req0 + r] = q;
     }
 }
 
 // ------------------------------------------------------------ replay
-DEV RunReq load_req(const CONST_AS RunReq *req, int64_t r) {
+// The requests of a trace, as one wavefront goes through them: descriptors
+// come eight at a time (lane 8 j + k: word k of request 8 b + j), a batch
+// ahead, and a request's pieces one request ahead, all by vector loads: a
+// scalar load in flight would make every LDS wait wait for it too.
+struct Feed {
+    const GLOBAL uint32_t *rec;
+    const GLOBAL uint2 *piece;
+    GLOBAL uint32_t *gbits;      // admitted bits in the workspace (PrefixShield, many prefixes)
+    LDS_AS uint32_t *lbits;      // ... or in LDS
+    GLOBAL int4 *pr;             // per-request quadruples, or null
+    int64_t n;
+    int32_t n_words;             // of the admitted bits
+    bool in_lds;
+};
+
+DEV RunReq unpack(uint32_t rec, uint32_t j) {
     RunReq q;
-    q.n_full = req[r].n_full;
-    q.np = req[r].np;
-    q.info = req[r].info;
-    q.prefix = req[r].prefix;
-    q.tick = req[r].tick;
-    q.ko = req[r].ko;
+    const int b = (int)(8u * j);
+    q.n_full = DevWave::rdl(rec, b);
+    q.info = DevWave::rdl(rec, b + 1);
+    q.prefix = DevWave::rdl(rec, b + 2);
+    q.dt = DevWave::rdl(rec, b + 3);
+    q.nn = DevWave::rdl(rec, b + 5);
     return q;
 }
+DEV uint32_t load_batch(const Feed &F, int64_t b, uint32_t lane) {
+    const int64_t i = 64 * b + lane;
+    const uint32_t x = F.rec[i < 8 * F.n ? i : 0];      // (n > 0)
+    return i < 8 * F.n ? x : 0u;
+}
+// (lanes past the last piece read the first one again)
+DEV uint2 load_pieces(const Feed &F, uint32_t ko, uint32_t info, uint32_t lane) {
+    const GLOBAL uint2 *p = F.piece + (ko + (lane < (info >> 24) ? lane : 0u));
+    return make_uint2(p->x, p->y);
+}
 
+// All requests; false if the instance is lost to this form.
+template <int kPol, bool kLdsBits, class X>
+DEV bool all_requests(X &R, const Feed &F) {
+    const uint32_t lane = (uint32_t)__lane_id();
+    const uint32_t n = (uint32_t)F.n;
+    if (n == 0) return true;
+    uint32_t cur = load_batch(F, 0, lane), nxt = load_batch(F, 1, lane);
+    uint2 pc = load_pieces(F, DevWave::rdl(cur, 4), DevWave::rdl(cur, 1), lane);
+    uint32_t word = 0;           // (bits in the workspace: lane 0) admitted bits around q.prefix
+    if (kPol == 2 && !kLdsBits && lane == 0) word = F.gbits[DevWave::rdl(cur, 2) >> 5];
+    for (uint32_t r = 0; r < n; ++r) {
+        const RunReq q = unpack(cur, r & 7u);
+        const uint32_t j = (r + 1) & 7u;
+        if (__builtin_expect(j == 0, 0)) {
+            if (((r + 1) & (X::kFlush - 1u)) == 0) R.flush();
+            cur = nxt;
+            nxt = load_batch(F, ((int64_t)(r + 1) >> 3) + 1, lane);
+        }
+        // the next request's pieces (zeros past the last request)
+        const uint2 pn = load_pieces(F, DevWave::rdl(cur, (int)(8u * j) + 4), DevWave::rdl(cur, (int)(8u * j) + 1), lane);
+        uint32_t np_prefix = 0;
+        if (kPol == 2 && !kLdsBits) np_prefix = DevWave::rdl(cur, (int)(8u * j) + 2);
+        bool adm = false;
+        uint32_t wn = 0;
+        if (kPol == 2) {
+            if (kLdsBits) word = F.lbits[q.prefix >> 5];
+            else if (lane == 0) wn = F.gbits[np_prefix >> 5];
+            adm = (DevWave::rfl(word) >> (q.prefix & 31)) & 1u;
+        }
+        const bool now = R.request(r, q, pc.x, pc.y, adm);
+        if (__builtin_expect(R.over != 0, 0)) return false;
+        if (kPol == 2) {
+            if (now && !adm) {
+                word |= 1u << (q.prefix & 31);
+                if (kLdsBits) F.lbits[q.prefix >> 5] = word;      // (every lane the same word)
+                else if (lane == 0) F.gbits[q.prefix >> 5] = word;
+                DevWave::sync();
+            }
+            if (!kLdsBits) word = (np_prefix >> 5) == (q.prefix >> 5) ? word : wn;
+        }
+        if (__builtin_expect(F.pr != nullptr, 0)) {      // (every lane the same quadruple)
+            GLOBAL int4 *o = F.pr + r;
+            o->x = R.last_h;
+            o->y = R.last_m;
+            o->z = R.last_e;
+            o->w = R.last_o;
+        }
+        pc = pn;
+    }
+    return true;
+}
+
+DEV void clear_bits(const Feed &F) {
+    for (int i = (int)__lane_id(); i < F.n_words; i += 64) {
+        if (F.in_lds) F.lbits[i] = 0u;
+        else F.gbits[i] = 0u;
+    }
+    DevWave::sync();
+    if (!F.in_lds) __threadfence();
+}
+
+// stats record: 64 groups x 17 int64, then the instance block
+template <class X>
+DEV void write_stats(X &R, int64_t n, int G, int64_t *st) {
+    const int lane = (int)__lane_id();
+    R.flush();
+    int64_t *o = st + lane * kGroupFields;
+    const bool grp = lane < G;
+    const int64_t v[kGroupFields] = {R.c_req, R.c_probe, R.c_hit, R.c_probe - R.c_hit, R.c_probe - R.c_hit - R.c_dup,
+                                     R.c_evw, R.c_evc, R.c_promo, R.c_gated, R.c_orph, R.c_dup, R.c_trunc,
+                                     n > 0 ? R.raw_debt() : 0, R.d_max, R.d_sum, (int64_t)R.res, (int64_t)R.res_max};
+#pragma unroll
+    for (int f = 0; f < kGroupFields; ++f) o[f] = grp ? v[f] : 0;
+    // evictions of all groups (every group owns its victims)
+    int64_t ev = R.c_evw;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1)
+        ev += (int64_t)(((uint64_t)(uint32_t)__shfl_xor((int)(uint32_t)((uint64_t)ev >> 32), d) << 32) |
+                        (uint32_t)__shfl_xor((int)(uint32_t)(uint64_t)ev, d));
+    if (lane == 0) {
+        int64_t *qq = st + kInstOffset;
+        qq[0] = ev;
+        qq[1] = R.c_moves;
+        qq[2] = R.c_reins;
+        qq[3] = R.c_ghits;
+        qq[4] = R.c_gins;
+        qq[5] = (int64_t)R.resident;
+        qq[6] = (int64_t)R.rmax;
+        qq[7] = 0;
+    }
+}
+
+template <int kPol, bool kK1, bool kLdsBits>
+DEV bool replay_one(const RunParams &P, const Feed &F, int64_t *st, LDS_AS uint32_t *lds) {
+    DevWave wv;
+    RunReplay<DevWave, kPol, kK1> X(P, wv, lds);
+    if (kPol == 2) clear_bits(F);
+    if (!all_requests<kPol, kLdsBits>(X, F)) return false;
+    write_stats(X, F.n, P.G, st);
+    return true;
+}
+// One instance.  False: left to the general kernel.
 template <int kPol>
-DEV void replay_runs(const RunsArgs &A, const DevInst &I, const DevTrace &T, const DevRunTrace &R, int id, uint8_t *ws,
-                     int64_t *stats, int32_t *per_req, LDS_AS uint32_t *lds) {
+DEV bool replay_policy(const RunParams &P, const Feed &F, int64_t *st, LDS_AS uint32_t *lds) {
+    if (kPol == 2 && !F.in_lds)
+        return P.K == 1 ? replay_one<kPol, true, false>(P, F, st, lds) : replay_one<kPol, false, false>(P, F, st, lds);
+    return P.K == 1 ? replay_one<kPol, true, true>(P, F, st, lds) : replay_one<kPol, false, true>(P, F, st, lds);
+}
+
+__global__ __launch_bounds__(64) void runs_replay(RunsArgs A, const int32_t *__restrict__ order, uint8_t *ws,
+                                                  int64_t *stats, int32_t *per_req) {
+    extern __shared__ __align__(16) uint32_t runs_smem[];
+    const int id = order[blockIdx.x];
+    if (A.wide && A.done[id]) return;
+    const DevInst &I = A.inst[id];
+    const DevRunTrace &R = A.traces[I.run_trace];
+    if (A.tflag[I.run_trace] || A.bflag[2 * R.buf]) return;
+    const DevTrace &T = A.tr[I.trace];
+    LDS_AS uint32_t *lds = (LDS_AS uint32_t *)runs_smem;
     RunParams P;
     P.C = I.capacity;
     P.G = T.n_groups;
@@ -334,7 +513,7 @@ DEV void replay_runs(const RunsArgs &A, const DevInst &I, const DevTrace &T, con
     P.s_cap = I.s_cap;
     P.g_cap = I.g_cap;
     P.move_thr = I.move_thr;
-    P.q = (uint32_t)I.run_ring;
+    P.win = runs_windows(I.policy, I.capacity, A.wide);
     P.eps = I.eps;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -343,95 +522,23 @@ DEV void replay_runs(const RunsArgs &A, const DevInst &I, const DevTrace &T, con
         P.invw[c] = I.invw[c];
     }
     P.n_req = T.n_req;
-    const uint32_t lane = (uint32_t)__lane_id();
-    GLOBAL uint32_t *bits = (GLOBAL uint32_t *)(ws + I.ws_bits);
-    if (kPol == 2) {
-        for (int i = (int)lane; i < I.n_prefix_words; i += 64) bits[i] = 0u;
-        __threadfence();
-    }
-    const DevKeyBuf &B = A.bufs[R.buf];
-    const CONST_AS RunReq *req = (const CONST_AS RunReq *)(uintptr_t)(A.req + R.req0);
-    const GLOBAL uint2 *piece = (const GLOBAL uint2 *)(A.table + B.tab0);
-    int32_t *pr = (per_req && I.per_req_off >= 0) ? per_req + I.per_req_off : nullptr;
-    DevWave wv;
-    RunReplay<DevWave, kPol> X(P, wv, lds);
-    const int64_t n = P.n_req;
-    // request r runs while r + 1's pieces and prefix bit and r + 2's
-    // descriptor are on their way
-    RunReq q = {}, nx = {};
-    uint2 pc = make_uint2(0u, 0u);
-    uint32_t word = 0;           // (lane 0) admitted bits around q.prefix
-    if (n > 0) {
-        q = load_req(req, 0);
-        if (n > 1) nx = load_req(req, 1);
-        if (lane < q.np && q.np <= 64u) pc = make_uint2(piece[q.ko + lane].x, piece[q.ko + lane].y);
-    }
-    for (int64_t r = 0; r < n; ++r) {
-        uint2 pn = make_uint2(0u, 0u);
-        uint32_t wn = 0;
-        RunReq nn = {};
-        if (r + 1 < n) {
-            if (lane < nx.np && nx.np <= 64u) pn = make_uint2(piece[nx.ko + lane].x, piece[nx.ko + lane].y);
-            if (kPol == 2 && lane == 0) wn = bits[nx.prefix >> 5];
-            if (r + 2 < n) nn = load_req(req, r + 2);
-        }
-        bool adm = false;
-        if (kPol == 2) adm = (DevWave::rfl(word) >> (q.prefix & 31)) & 1u;
-        const bool now = X.request((uint32_t)r, q, pc.x, pc.y, adm);
-        if (X.general) return;       // the general kernel replays the instance
-        if (kPol == 2 && now && !adm) {
-            word |= 1u << (q.prefix & 31);
-            if (lane == 0) bits[q.prefix >> 5] = word;
-        }
-        if (kPol == 2 && (nx.prefix >> 5) == (q.prefix >> 5)) wn = word;
-        if (pr && lane == 0) {
-            int32_t *o = pr + 4 * r;
-            o[0] = X.last_h;
-            o[1] = X.last_m;
-            o[2] = X.last_e;
-            o[3] = X.last_o;
-        }
-        q = nx;
-        nx = nn;
-        pc = pn;
-        word = wn;
-    }
-    // stats record: 64 groups x 17 int64, then the instance block
-    int64_t *st = stats + (int64_t)id * kRecordWords;
-    int64_t *o = st + lane * kGroupFields;
-    const bool grp = (int)lane < P.G;
-    const int64_t v[kGroupFields] = {X.c_req, X.c_probe, X.c_hit, X.c_probe - X.c_hit, X.c_probe - X.c_hit - X.c_dup,
-                                     X.evw, X.c_evc, X.c_promo, X.c_gated, X.c_orph, X.c_dup, X.c_trunc,
-                                     n > 0 ? X.raw_debt() : 0, X.d_max, X.d_sum, (int64_t)X.res, (int64_t)X.res_max};
-#pragma unroll
-    for (int f = 0; f < kGroupFields; ++f) o[f] = grp ? v[f] : 0;
-    if (lane == 0) {
-        int64_t *qq = st + kInstOffset;
-        qq[0] = (int64_t)X.ev_total;
-        qq[1] = (int64_t)X.s3_moves;
-        qq[2] = (int64_t)X.s3_reins;
-        qq[3] = (int64_t)X.s3_ghits;
-        qq[4] = (int64_t)X.s3_gins;
-        qq[5] = (int64_t)X.resident;
-        qq[6] = (int64_t)X.rmax;
-        qq[7] = 0;
-        A.done[id] = 1;
-    }
-}
-
-__global__ __launch_bounds__(64) void runs_replay(RunsArgs A, const int32_t *__restrict__ order, uint8_t *ws,
-                                                  int64_t *stats, int32_t *per_req) {
-    extern __shared__ __align__(16) uint32_t runs_smem[];
-    const int id = order[blockIdx.x];
-    const DevInst &I = A.inst[id];
-    const DevRunTrace &R = A.traces[I.run_trace];
-    if (A.tflag[I.run_trace] || A.bflag[2 * R.buf]) return;
-    const DevTrace &T = A.tr[I.trace];
-    LDS_AS uint32_t *lds = (LDS_AS uint32_t *)runs_smem;
-    if (I.policy == kLRU) replay_runs<kLRU>(A, I, T, R, id, ws, stats, per_req, lds);
-    else if (I.policy == kS3) replay_runs<kS3>(A, I, T, R, id, ws, stats, per_req, lds);
-    else if (I.policy == kSQ) replay_runs<kSQ>(A, I, T, R, id, ws, stats, per_req, lds);
-    else replay_runs<kPS>(A, I, T, R, id, ws, stats, per_req, lds);
+    Feed F;
+    F.rec = (const GLOBAL uint32_t *)(A.req + R.req0);
+    F.piece = (const GLOBAL uint2 *)(A.table + A.bufs[R.buf].tab0);
+    F.gbits = (GLOBAL uint32_t *)(ws + I.ws_bits);
+    F.in_lds = T.n_prefix <= kRunsLdsPrefix;
+    F.n_words = I.n_prefix_words;
+    F.lbits = lds + runs_lds_bytes(I.policy, P.win, 0) / 4;
+    F.pr = (per_req && I.per_req_off >= 0) ? (GLOBAL int4 *)(per_req + I.per_req_off) : nullptr;
+    F.n = T.n_req;
+    int64_t *st = (int64_t *)DevWave::hold((uint64_t)(stats + (int64_t)id * kRecordWords));
+    int32_t *done = (int32_t *)DevWave::hold((uint64_t)(A.done + id));
+    bool ok;
+    if (I.policy == kLRU) ok = replay_policy<kLRU>(P, F, st, lds);
+    else if (I.policy == kS3) ok = replay_policy<kS3>(P, F, st, lds);
+    else if (I.policy == kSQ) ok = replay_policy<kSQ>(P, F, st, lds);
+    else ok = replay_policy<kPS>(P, F, st, lds);
+    if (ok && threadIdx.x == 0) *done = 1;
 }
 
 }  // namespace

@@ -4,6 +4,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
+#include <type_traits>
 #include <unordered_map>
 #include <vector>
 
@@ -36,7 +37,7 @@ V<T> splat(T x) {
     auto operator op(const V<T> &a, S b) -> V<T> {                                                       \
         return zip(a, splat<T>((T)b), [](T x, T y) { return T(x op y); });                               \
     }
-PC_OP(+) PC_OP(-) PC_OP(&) PC_OP(|)
+PC_OP(+) PC_OP(-) PC_OP(&) PC_OP(|) PC_OP(*)
 #define PC_CMP(op)                                                                                       \
     template <class T>                                                                                   \
     V<bool> operator op(const V<T> &a, const V<T> &b) {                                                  \
@@ -52,7 +53,6 @@ V<T> operator<<(const V<T> &a, int s) { return zip(a, a, [s](T x, T) { return T(
 template <class T>
 V<T> operator>>(const V<T> &a, int s) { return zip(a, a, [s](T x, T) { return T(x >> s); }); }
 V<int64_t> operator-(const V<int64_t> &a) { return zip(a, a, [](int64_t x, int64_t) { return -x; }); }
-V<bool> operator!(const V<bool> &a) { return zip(a, a, [](bool x, bool) { return !x; }); }
 
 uint32_t *g_lds;
 int64_t g_lds_words;
@@ -108,7 +108,6 @@ struct HostWave {
     static V<T> vmin(const V<T> &a, const V<T> &b) { return zip(a, b, [](T x, T y) { return x < y ? x : y; }); }
     template <class T>
     static V<T> vmax(const V<T> &a, const V<T> &b) { return zip(a, b, [](T x, T y) { return x > y ? x : y; }); }
-    static vl vmin(const vl &a, int64_t b) { return vmin(a, splat<int64_t>(b)); }
     static vl vmax(const vl &a, int64_t b) { return vmax(a, splat<int64_t>(b)); }
     static vu scan(const vu &a) {
         vu r = a;
@@ -131,11 +130,6 @@ struct HostWave {
         for (int i = 0; i < kLanes; ++i) r.v[i] = (uint32_t)__builtin_popcountll(m & ((1ull << i) - 1));
         return r;
     }
-    static vu next_lane(const vu &a) {
-        vu r;
-        for (int i = 0; i < kLanes; ++i) r.v[i] = i + 1 < kLanes ? a.v[i + 1] : 0u;
-        return r;
-    }
     static vl widen(const vu &a) {
         vl r;
         for (int i = 0; i < kLanes; ++i) r.v[i] = (int64_t)a.v[i];
@@ -144,7 +138,15 @@ struct HostWave {
     static vl mul_shr16(const vl &a, int64_t w) {
         return zip(a, a, [w](int64_t x, int64_t) { return (int64_t)(((__int128)x * w) >> 16); });
     }
-    static uint64_t mulhi(uint64_t a, uint64_t b) { return (uint64_t)(((unsigned __int128)a * b) >> 64); }
+    static vl mul_sat62(const vl &a, uint32_t b) {
+        return zip(a, a, [b](int64_t x, int64_t) {
+            const __int128 v = (__int128)x * b;
+            return v > ((__int128)1 << 62) ? (int64_t)1 << 62 : (int64_t)v;
+        });
+    }
+    template <class T>
+    static T hold(const T &x) { return x; }
+    static uint32_t uni(const vu &v) { return v.v[0]; }
     static uint64_t udiv(uint64_t a, uint64_t b) { return a / b; }
     static vu ld(const uint32_t *p, const vu &at) {
         vu r;
@@ -161,10 +163,43 @@ struct HostWave {
                 p[at.v[i]] = x.v[i];
             }
     }
-    void st1(uint32_t *p, uint32_t at, uint32_t x) {
-        check(p + at);
-        p[at] = x;
+    static void st_all(uint32_t *p, const vu &at, const vu &x) { st(splat(true), p, at, x); }
+    template <int N>
+    void st1(uint32_t *p, uint32_t at, uint32_t *scratch, uint32_t x, uint32_t y, uint32_t z) {
+        check(scratch + 64 * N - 1);
+        const uint32_t v[3] = {x, y, z};
+        for (int i = 0; i < N; ++i) {
+            check(p + at + 64 * i);
+            p[at + 64 * i] = v[i];
+        }
     }
+    static vu setlane(vu a, int l, uint32_t x) {
+        if (l < 0 || l >= kLanes) die("lane out of range");
+        a.v[l] = x;
+        return a;
+    }
+    static vu ld_if(const vb &m, const uint32_t *p, const vu &at) {
+        vu r = splat<uint32_t>(0);
+        for (int i = 0; i < kLanes; ++i)
+            if (m.v[i]) {
+                check(p + at.v[i]);
+                r.v[i] = p[at.v[i]];
+            }
+        return r;
+    }
+    uint32_t ld1(const uint32_t *p, uint32_t at) const {
+        check(p + at);
+        return p[at];
+    }
+    static vu mad24(const vu &a, uint32_t b, const vu &c) {
+        if ((int32_t)b >= 1 << 23 || (int32_t)b < -(1 << 23)) die("mad24 factor");
+        return zip(a, c, [b](uint32_t x, uint32_t z) { return x * b + z; });
+    }
+    static vl mad64(const vu &a, int32_t b, const vl &c) {
+        return zip(a, c, [b](uint32_t x, int64_t z) { return (int64_t)x * b + z; });
+    }
+    static bool likely(bool x) { return x; }
+    static bool unlikely(bool x) { return x; }
 };
 }  // namespace
 
@@ -210,36 +245,40 @@ Analysis analyse(const uint64_t *keys, const int64_t *off, const uint8_t *group,
     std::unordered_map<uint32_t, int> seen;
     for (int64_t r = 0; r < n_req; ++r) {
         const auto p = pieces(r);
+        const uint32_t nf = (uint32_t)(off[r + 1] - off[r]);
+        uint32_t nn = 0;
         for (size_t a = 0; a < p.size(); ++a) {
             bool dup = false;
             for (size_t b = 0; b < a; ++b) dup = dup || p[a].first == p[b].first;
-            A.piece[off[r] + a] = {p[a].first, p[a].second | (dup ? pcr::kPieceDup : 0u)};
+            const uint32_t len = (a + 1 < p.size() ? p[a + 1].second : nf) - p[a].second;
+            A.piece[off[r] + a] = {p[a].first, (len < pcr::kPieceLen ? len : pcr::kPieceLen) |
+                                                   (dup ? pcr::kPieceDup : 0u) | (nn < 0xFFFFu ? nn : 0xFFFFu) << 16};
+            if (!dup) nn += len;
         }
         const bool before = !seen.emplace(prefix[r], 1).second;
-        A.req.push_back({(uint32_t)(off[r + 1] - off[r]), (uint32_t)p.size(),
-                         group[r] | ((uint32_t)contract[r] << 8) | (before ? 1u << 16 : 0u), prefix[r],
-                         tick ? tick[r] : r, (uint32_t)off[r], 0});
+        const uint32_t np = p.size() <= pcr::kRunsMaxPieces ? (uint32_t)p.size() : 255u;
+        A.req.push_back({nf, group[r] | ((uint32_t)contract[r] << 8) | (before ? 1u << 16 : 0u) | np << 24, prefix[r],
+                         (uint32_t)(tick ? tick[r] - (r ? tick[r - 1] : 0) : r ? 1 : 0), (uint32_t)off[r], nn, {}});
     }
     return A;
 }
 
-template <int kPol>
-int replay(const Analysis &A, const pcr::RunParams &P, int64_t n_prefix, int64_t *gs, int64_t *is, int32_t *pr) {
-    std::vector<uint32_t> lds(pcr::runs_lds_bytes(kPol, (int32_t)P.q) / 4, 0xDEADBEEFu);
-    g_lds = lds.data();
-    g_lds_words = (int64_t)lds.size();
-    HostWave wv;
-    pcr::RunReplay<HostWave, kPol> R(P, wv, lds.data());
+// All requests; false if a window was too small.
+template <class X>
+bool all_requests(X &R, const Analysis &A, int64_t n, int64_t n_prefix, int32_t *pr) {
     std::vector<uint8_t> adm(n_prefix + 1, 0);
-    for (int64_t r = 0; r < P.n_req; ++r) {
+    for (int64_t r = 0; r < n; ++r) {
         const pcr::RunReq &q = A.req[r];
-        V<uint32_t> id = splat<uint32_t>(0), dep = splat<uint32_t>(0);
-        for (uint32_t i = 0; i < q.np && i < 64; ++i) {
-            id.v[i] = A.piece[q.ko + i].id;
-            dep.v[i] = A.piece[q.ko + i].depth;
+        V<uint32_t> id = splat<uint32_t>(0), len = splat<uint32_t>(0);
+        const uint32_t np = q.info >> 24;
+        for (uint32_t i = 0; i < 64 && np > 0 && np <= 64; ++i) {
+            const pcr::RunPiece &p = A.piece[q.ko + (i < np ? i : 0)];
+            id.v[i] = p.id;
+            len.v[i] = p.len;
         }
-        adm[q.prefix] = R.request((uint32_t)r, q, id, dep, adm[q.prefix] != 0);
-        if (R.general) return 1;
+        adm[q.prefix] = R.request((uint32_t)r, q, id, len, adm[q.prefix] != 0);
+        if (R.over) return false;
+        if ((r + 1) % 100 == 0) R.flush();
         if (pr) {
             pr[4 * r] = R.last_h;
             pr[4 * r + 1] = R.last_m;
@@ -247,30 +286,48 @@ int replay(const Analysis &A, const pcr::RunParams &P, int64_t n_prefix, int64_t
             pr[4 * r + 3] = R.last_o;
         }
     }
+    return true;
+}
+
+template <class X>
+void results(X &R, const pcr::RunParams &P, int64_t *gs, int64_t *is) {
+    R.flush();
     const auto dend = R.raw_debt();
     for (int g = 0; g < P.G; ++g) {
         const int64_t probe = R.c_probe.v[g], hit = R.c_hit.v[g], dup = R.c_dup.v[g];
-        const int64_t f[17] = {R.c_req.v[g], probe, hit, probe - hit, probe - hit - dup, R.evw.v[g], R.c_evc.v[g],
+        const int64_t f[17] = {R.c_req.v[g], probe, hit, probe - hit, probe - hit - dup, R.c_evw.v[g], R.c_evc.v[g],
                                R.c_promo.v[g], R.c_gated.v[g], R.c_orph.v[g], dup, R.c_trunc.v[g],
                                P.n_req ? dend.v[g] : 0, R.d_max.v[g], R.d_sum.v[g], (int64_t)R.res.v[g],
                                (int64_t)R.res_max.v[g]};
         for (int k = 0; k < 17; ++k) gs[17 * g + k] = f[k];
     }
-    const int64_t f[7] = {(int64_t)R.ev_total, (int64_t)R.s3_moves, (int64_t)R.s3_reins, (int64_t)R.s3_ghits,
-                          (int64_t)R.s3_gins, R.resident, R.rmax};
+    int64_t ev = 0;
+    for (int64_t x : R.c_evw.v) ev += x;
+    const int64_t f[7] = {ev, R.c_moves.v[0], R.c_reins.v[0], R.c_ghits.v[0], R.c_gins.v[0], R.resident, R.rmax.v[0]};
     for (int k = 0; k < 7; ++k) is[k] = f[k];
-    return 0;
+}
+
+template <int kPol, bool kK1>
+bool replay_in(const Analysis &A, const pcr::RunParams &P, int64_t n_prefix, int64_t *gs, int64_t *is, int32_t *pr) {
+    std::vector<uint32_t> lds(pcr::runs_lds_bytes(kPol, P.win, 0) / 4, 0xDEADBEEFu);
+    g_lds = lds.data();
+    g_lds_words = (int64_t)lds.size();
+    HostWave wv;
+    pcr::RunReplay<HostWave, kPol, kK1> R(P, wv, lds.data());
+    if (!all_requests(R, A, P.n_req, n_prefix, pr)) return false;
+    results(R, P, gs, is);
+    return true;
 }
 
 }  // namespace
 
-// The oracle's signature; `ring` overrides the ring size (0: the planner's).
-// Returns 0, or 1 when the instance is left to the general kernel.
+// The oracle's signature; `window` overrides the windows' size (0 and -1: the
+// planner's, the widest).  Returns 1 when the instance is left.
 extern "C" int runs_host_replay(const uint64_t *keys, const int64_t *off, const uint8_t *group,
                                 const uint8_t *contract, const uint32_t *prefix, const int64_t *tick, int64_t n_req,
                                 int32_t G, int64_t n_prefix, int32_t policy, int64_t C, int32_t flags, int32_t K,
                                 const int64_t *rho, const int64_t *beta, int64_t eps, int32_t permille,
-                                int32_t move_thr, int32_t ring, int64_t *gs, int64_t *is, int32_t *pr) {
+                                int32_t move_thr, int32_t window, int64_t *gs, int64_t *is, int32_t *pr) {
     const Analysis A = analyse(keys, off, group, contract, prefix, tick, n_req);
     pcr::RunParams P{};
     P.C = (int32_t)C;
@@ -282,7 +339,8 @@ extern "C" int runs_host_replay(const uint64_t *keys, const int64_t *off, const 
     P.s_cap = (int32_t)sc;
     P.g_cap = (int32_t)(C - sc);
     P.move_thr = move_thr;
-    P.q = (uint32_t)(ring ? ring : pcr::runs_ring((int32_t)C));
+    P.win = pcr::runs_windows(policy, (int32_t)C, window < 0);
+    for (int32_t &n : P.win.n) n = window > 0 ? (policy == 1 || &n == P.win.n ? window : 0) : n;
     P.eps = eps;
     P.n_req = n_req;
     int64_t rmin = rho[0];
@@ -292,10 +350,16 @@ extern "C" int runs_host_replay(const uint64_t *keys, const int64_t *off, const 
         P.beta[c] = beta[c];
         P.invw[c] = (rmin << 16) / rho[c];
     }
+    auto go = [&](auto pol) {
+        constexpr int kPol = decltype(pol)::value;
+        const bool ok = K == 1 ? replay_in<kPol, true>(A, P, n_prefix, gs, is, pr)
+                               : replay_in<kPol, false>(A, P, n_prefix, gs, is, pr);
+        return ok ? 0 : 1;
+    };
     switch (policy) {
-        case 0: return replay<0>(A, P, n_prefix, gs, is, pr);
-        case 1: return replay<1>(A, P, n_prefix, gs, is, pr);
-        case 2: return replay<2>(A, P, n_prefix, gs, is, pr);
-        default: return replay<3>(A, P, n_prefix, gs, is, pr);
+        case 0: return go(std::integral_constant<int, 0>());
+        case 1: return go(std::integral_constant<int, 1>());
+        case 2: return go(std::integral_constant<int, 2>());
+        default: return go(std::integral_constant<int, 3>());
     }
 }
