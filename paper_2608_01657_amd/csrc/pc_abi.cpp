@@ -603,7 +603,7 @@ void fill_header(const Plan &P, int32_t n_traces, int32_t n_inst, uint8_t *h) {
 // back into the caller's stream with events.  One set per device.  A process
 // has four hardware queues: the caller's stream takes launches too, and three
 // more streams get the other queues (a fourth shares one, and its launch
-// begins when the other's has ended: 289 instead of 190 ms for 960
+// begins when the other's has ended: 294 instead of 201 ms for 960
 // conversation instances).
 constexpr int kForkStreams = 3;
 struct ForkStreams {

@@ -116,8 +116,9 @@ __device__ __forceinline__ int64_t wave_scan_add64(int64_t x) {
 }
 
 // ---------------------------------------------------------------- offsets
-// Three launches: per-chunk sums (written where the chunk ends), a scan of
-// the chunk sums in place, then each chunk's exclusive scan from its base.
+// Past kSmallMax requests three launches: per-chunk sums (written where the
+// chunk ends), a scan of the chunk sums in place, then each chunk's exclusive
+// scan from its base.
 // Thread t of a chunk owns its requests 4t..4t+3 (coalesced), and every
 // length load is issued before any is used.
 constexpr int kScanThreads = 256;
@@ -203,9 +204,45 @@ __global__ __launch_bounds__(kScanThreads) void offsets_fill(const int32_t *__re
     }
 }
 
+// All of it in one launch for a few requests (a scheduler tick of an engine):
+// one workgroup, its chunks one after another.  Bound by launches and, past
+// 4,096 requests, by one CU: 2.7 us instead of 7.0 at 48 requests, 5.8 instead
+// of 8.4 at 8,192; at 16,384 it takes 10.1 and the three launches 7.7.
+constexpr int kSmallThreads = 1024;
+constexpr int64_t kSmallMax = 2 * 4 * kSmallThreads;
+__global__ __launch_bounds__(kSmallThreads) void offsets_small(const int32_t *__restrict__ len, int64_t n,
+                                                               int64_t *__restrict__ key_off) {
+    __shared__ int64_t sh[kSmallThreads / 64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int64_t base = 0;
+    for (int64_t start = 0; start < n; start += 4 * kSmallThreads) {
+        int64_t nb[4];
+        chunk_blocks(len, start, n, nb);
+        const int64_t loc = nb[0] + nb[1] + nb[2] + nb[3];
+        const int64_t incl = wave_scan_add64(loc);
+        if (lane == 63) sh[w] = incl;
+        __syncthreads();
+        int64_t run = base + incl - loc;
+#pragma unroll
+        for (int i = 0; i < kSmallThreads / 64; ++i) {
+            const int64_t s = sh[i];
+            run += i < w ? s : 0;
+            base += s;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int64_t e = start + 4 * threadIdx.x + i;
+            if (e < n) key_off[e] = run;
+            run += nb[i];
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) key_off[n] = base;
+}
+
 // ---------------------------------------------------------------- keys
-// Workgroup sizes of the key kernel (wavefronts), chosen per call by how
-// often the tokens are read (launch_hash).
+// Workgroup sizes of the one-wavefront-a-request kernel (wavefronts), chosen
+// per call by how often the tokens are read (launch_hash).
 constexpr int kHashWavesStream = 16;
 constexpr int kHashWavesReuse = 4;
 
@@ -261,6 +298,70 @@ __device__ __forceinline__ void step_keys(const Step &S, int nblk, int lane, int
     out[lane < nblk ? lane : nblk - 1] = fmix64(lane < nblk ? v : H);
 }
 
+// Powers of A^-64: the chain over whole steps.
+constexpr uint64_t pow_ainv64() {
+    uint64_t r = kAinv;
+    for (int i = 0; i < 6; ++i) r *= r;
+    return r;
+}
+constexpr uint64_t kAinv64 = pow_ainv64();
+__constant__ PowTab kAinv64L = PowTab(kAinv64);
+
+// All keys of one request by a workgroup: wavefront w takes steps w,
+// w + kWaves, ...  With T_i = A^63 sum_{j<64} A^-j c_j of wavefront i's step,
+// the chain value ahead of wavefront w's step is
+//   H_w = A^(64 w) (H + sum_{i<w} A^(-64 (i+1)) T_i),
+// a prefix sum that every wavefront takes over the totals that all of them
+// left in LDS: one barrier for 64 kWaves blocks.  Bound by the 64-bit
+// products of one CU: 16 wavefronts take 1.7 us for 1,024 blocks (16,000 blocks
+// 28 us; one wavefront 113).
+template <int kWaves>
+__device__ __forceinline__ void hash_request_team(const GLOBAL int32_t *__restrict__ tok, int32_t nb, uint64_t H,
+                                                  GLOBAL uint64_t *__restrict__ out, int lane, int w,
+                                                  uint64_t (*sh)[kWaves]) {
+    const int r4 = lane & 3, bq = lane >> 2;
+    const uint32_t k0 = kNH[4 * r4], k1 = kNH[4 * r4 + 1], k2 = kNH[4 * r4 + 2], k3 = kNH[4 * r4 + 3];
+    const int src = 4 * (lane & 15) + (lane >> 4);
+    const uint64_t apw = kApowL.v[lane], ainv = kAinvL.v[lane];
+    const uint64_t f = lane < kWaves ? kAinv64L.v[lane + 1] : 0ull;
+    uint64_t aw = kA;           // A^(64 w + 1): the first block's factor of H_w's sum
+    for (int i = 0; i < w; ++i) aw *= pow_a(64);
+    Step S;
+    issue(S, tok, 64 * w, nb, bq, r4);      // (past the end: the last block again)
+    int buf = 0;
+    for (int32_t it = 0; it < nb; it += 64 * kWaves) {
+        const Step C = S;
+        const int32_t b0 = it + 64 * w;
+        issue(S, tok, b0 + 64 * kWaves, nb, bq, r4);
+        uint64_t dsel = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            uint64_t part = (uint64_t)(C.v[q].x + k0) * (uint64_t)(C.v[q].y + k1) +
+                            (uint64_t)(C.v[q].z + k2) * (uint64_t)(C.v[q].w + k3);
+            part = quad_add<0xB1>(part);
+            part = quad_add<0x4E>(part);
+            if (q == r4) dsel = part;
+        }
+        const uint64_t sum = (uint64_t)wave_scan_add64((int64_t)(shfl64(fmix64(dsel), src) * ainv));
+        const uint64_t T = readlane64(sum, 63) * pow_a(63);
+        if (lane == 0) sh[buf][w] = T;
+        __syncthreads();
+        // prefix sum over the first row of 16 lanes (kWaves <= 16)
+        uint64_t t = (lane < kWaves ? sh[buf][lane] : 0ull) * f;
+        t += dpp64<0x111, 0xF>(t);
+        t += dpp64<0x112, 0xF>(t);
+        if (kWaves > 4) t += dpp64<0x114, 0xF>(t);
+        if (kWaves > 8) t += dpp64<0x118, 0xF>(t);
+        const uint64_t before = w > 0 ? readlane64(t, w - 1) : 0ull;
+        const uint64_t v = (sum + aw * (H + before)) * apw;
+        H = pow_a(64 * kWaves) * (H + readlane64(t, kWaves - 1));
+        if (b0 + lane < nb) out[b0 + lane] = fmix64(v);
+        // the other buffer: a wavefront still reading this one has not come
+        // to the next barrier, and this one is written only after that
+        buf ^= 1;
+    }
+}
+
 // All keys of one request, two steps in flight: the loads of step s+1 are
 // issued before step s is computed (two buffers, so no register copy has
 // to wait for a load).
@@ -309,9 +410,37 @@ __global__ __launch_bounds__(64 * kWaves) void hash_kernel(
     hash_request((const GLOBAL int32_t *)(tokens + off), (int32_t)nb, H, (GLOBAL uint64_t *)(keys + ko), lane);
 }
 
+// One workgroup per request, for calls with few or long ones (launch_hash).
+template <int kWaves>
+__global__ __launch_bounds__(64 * kWaves) void hash_team(
+    const int32_t *__restrict__ tokens, int64_t n_tokens, const int64_t *__restrict__ tok_off,
+    const int32_t *__restrict__ req_len, const int32_t *__restrict__ req_ns,
+    const int64_t *__restrict__ key_off, uint64_t *__restrict__ keys, int64_t n_keys, int32_t *__restrict__ status) {
+    __shared__ uint64_t sh[2][kWaves];
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t r = blockIdx.x;
+    const int64_t off = tok_off[r];
+    const int32_t len = req_len[r];
+    const int64_t ko = key_off[r];
+    const int64_t nb = len > 0 ? len / 16 : 0;
+    if (len < 0 || len >= (1 << 30) || off < 0 || off + (int64_t)len > n_tokens || ko < 0 || ko + nb > n_keys) {
+        if (threadIdx.x == 0) atomicExch(status, -1);
+        return;
+    }
+    if (nb == 0) return;
+    const uint64_t H = fmix64((uint64_t)(uint32_t)req_ns[r] + 1u);
+    hash_request_team<kWaves>((const GLOBAL int32_t *)(tokens + off), (int32_t)nb, H, (GLOBAL uint64_t *)(keys + ko),
+                              lane, w, sh);
+}
+
 }  // namespace
 
 hipError_t launch_block_offsets(const int32_t *len, int64_t n_req, int64_t *key_off, hipStream_t s) {
+    if (n_req <= kSmallMax) {
+        hipLaunchKernelGGL(offsets_small, dim3(1), dim3(kSmallThreads), 0, s, len, n_req, key_off);
+        return hipGetLastError();
+    }
     const int64_t nchunks = (n_req + kScanChunk - 1) / kScanChunk;
     if (nchunks > 0)
         hipLaunchKernelGGL(offsets_reduce, dim3((unsigned)nchunks), dim3(kScanThreads), 0, s, len, n_req, key_off);
@@ -325,17 +454,43 @@ hipError_t launch_hash(const int32_t *tokens, int64_t n_tokens, const int64_t *t
                        const int32_t *ns, const int64_t *key_off, int64_t n_req, uint64_t *keys,
                        int64_t n_keys, int32_t *status, hipStream_t s) {
     if (n_req <= 0) return hipSuccess;
-    // Requests that each read their own tokens (n_keys full blocks cover at
-    // most about twice the token buffer) stream them from HBM: there, 16
-    // wavefronts per workgroup take 4 % less time than 4 (a quarter of the
-    // workgroups to dispatch; 1.67 vs 1.74 ms on 16 x 50,000 one-touch
-    // requests, 8.6 GB).  Requests that re-read shared token ranges (prefix
-    // reuse: the re-reads come from L2) are many and short: there, 4-wave
-    // workgroups take 18 % less time (5.4 vs 6.6 ms on 64 x 100,000 chat
-    // requests), since a workgroup keeps its CU slots until its longest
-    // request ends.
+    // stream: requests that each read their own tokens (n_keys full blocks
+    // cover at most about twice the token buffer), from HBM; else they re-read
+    // shared ranges (prefix reuse), which come from L2.
     const bool stream = n_keys <= 2 * (n_tokens / 16);
-    if (stream) {
+    const int64_t avg = n_keys / n_req;
+    // A wavefront takes 0.45 us for a step of 64 blocks, so a call with few
+    // or long requests waits for its longest one while the chip idles: there
+    // a workgroup takes a request.  It costs a workgroup's wavefronts also
+    // for a request of one step, hence the lines (us, one wavefront a request
+    // -> a workgroup; lengths uniform in 1 .. 2 avg):
+    //  - up to 512 requests: 4 wavefronts (96 of 100 blocks 3.9 -> 3.1, 512 of
+    //    44 3.5 -> 3.3), 8 from 384 blocks (96: 8.1 -> 4.2; 4 take 4.5), 16
+    //    from 1536 (96 of 16,000 230 -> 55; 8 take 62).
+    //  - more: 4 from 512 blocks, 8 from 768 (2048 of 768 22.9 -> 21.5, 8192
+    //    103 -> 88; at 384 equal lengths lose, 4096: 18.6 -> 19.8); not for
+    //    more than 4096 that re-read (8192 of 768: 53 -> 57).
+    if (n_req <= 512 || (avg >= 512 && (stream ? n_req < (1 << 22) : n_req <= 4096))) {
+        const dim3 g((unsigned)n_req);
+        if (avg >= 1536 && n_req <= 512)
+            hipLaunchKernelGGL(hash_team<16>, g, dim3(64 * 16), 0, s, tokens, n_tokens, tok_off, len, ns, key_off,
+                               keys, n_keys, status);
+        else if (avg >= (n_req <= 512 ? 384 : 768))
+            hipLaunchKernelGGL(hash_team<8>, g, dim3(64 * 8), 0, s, tokens, n_tokens, tok_off, len, ns, key_off,
+                               keys, n_keys, status);
+        else
+            hipLaunchKernelGGL(hash_team<4>, g, dim3(64 * 4), 0, s, tokens, n_tokens, tok_off, len, ns, key_off,
+                               keys, n_keys, status);
+        return hipGetLastError();
+    }
+    // One wavefront a request.  Many that stream: 16 wavefronts per workgroup
+    // take 4 % less time than 4 (a quarter of the workgroups to dispatch;
+    // 1.67 vs 1.74 ms on 16 x 50,000 one-touch requests, 8.6 GB).  Otherwise
+    // 4: few requests spread over more CUs (1024 of 128 blocks 5.2 -> 3.6 us,
+    // 20,000 of 44 15.6 -> 13.4 us), and re-read ones gain 18 % (5.4 vs 6.6 ms
+    // on 64 x 100,000 chat requests), since a workgroup keeps its CU slots
+    // until its longest request ends.
+    if (stream && n_req >= 32768) {
         const int64_t blocks = (n_req + kHashWavesStream - 1) / kHashWavesStream;
         hipLaunchKernelGGL(hash_kernel<kHashWavesStream>, dim3((unsigned)blocks), dim3(64 * kHashWavesStream), 0, s,
                            tokens, n_tokens, tok_off, len, ns, key_off, n_req, keys, n_keys, status);
