@@ -104,6 +104,7 @@ struct RunsPlan {
     std::vector<Launch> launches;
     int64_t table_words = 0, id_words = 0, bit_words = 0, first_words = 0, n_req = 0;
     uint32_t nb_pos = 0, nb_req = 0, nb_list = 0;
+    int32_t alone = 0;                // a wavefront has its SIMD for itself
     int32_t wide_lds = 0;             // of the second launch (widest windows)
     int64_t o_kb = 0, o_rt = 0, o_order = 0;                              // header
     int64_t o_table = 0, o_first = 0, ones = 0;                           // set to ones
@@ -197,22 +198,41 @@ void plan_runs(const pc_trace_desc *traces, int32_t n_traces, const pc_instance_
     R.nb_list = (uint32_t)nb_list;
 }
 
-// Launches of the instances that are replayed on runs: one per class of LDS
-// (ten, six, five or three wavefronts to a CU), the largest class and the
-// costliest instances first.  Four classes, since four launches run side by
-// side.  A launch asks for the LDS of its largest instance, and a workgroup
-// waits for the shader engine that it was dealt to, even while another has
-// room: with 1,008 PrefixShield and S3-FIFO instances in one class of four to
-// a CU, the 16 LRU instances of the bench batch began when those had ended
-// (194 against 131 ms).
-void plan_run_launches(Plan &P, const std::vector<double> &cost, int32_t n_inst) {
+// Launches of the instances that are replayed on runs, costliest first.
+//
+// Up to one instance to a SIMD, every wavefront gets a SIMD for itself (the
+// kernel that no second wavefront fits beside): left to the dispatcher, 140 of
+// 992 shared one of 70 SIMDs, took up to 128 ms instead of 111, and the batch
+// waited for them; launches side by side stack up to three.  A workgroup waits
+// for the shader engine that it was dealt to, even while another has room, and
+// each launch deals from the first engine on, so this holds only where no
+// engine is dealt more wavefronts than it has SIMDs: with launches of 16, 16
+// and 992 some waited for whole instances (150 -> 167 ms).  Hence
+//  - one launch, if a quarter of a CU's LDS holds the largest instance:
+//    1,024 one-touch instances 150 -> 132 ms;
+//  - else one per class of LDS (ten, six, five or three wavefronts to a CU;
+//    four classes, since four launches run side by side), largest first, each
+//    wavefront alone if the engines have room: 960 conversation instances
+//    222 -> 181 ms.
+// More instances than SIMDs share them, a launch per class (1,536 take 1.3
+// times as long as 1,024).
+void plan_run_launches(Plan &P, const std::vector<double> &cost, int32_t n_inst, int64_t lds_cu, int64_t n_cu) {
     RunsPlan &R = P.runs;
     static const int32_t kClass[] = {16 << 10, 26 << 10, 32 << 10, 54 << 10};
     auto bytes_of = [&](int32_t i, int wide = 0) {
         const pcr::DevInst &d = P.di[i];
         return pcr::runs_lds_bytes(d.policy, pcr::runs_windows(d.policy, d.capacity, wide), P.dt[d.trace].n_prefix);
     };
+    int64_t n_run = 0;
+    int32_t most = 0;
+    for (int i = 0; i < n_inst; ++i)
+        if (P.di[i].run_trace >= 0) {
+            ++n_run;
+            most = std::max(most, bytes_of(i));
+        }
+    const bool one = n_run <= 4 * n_cu && 4 * (int64_t)most <= lds_cu;
     auto class_of = [&](int32_t i) {
+        if (one) return 0;
         int c = 0;
         while (c < 3 && bytes_of(i) > kClass[c]) ++c;
         return c;
@@ -236,6 +256,9 @@ void plan_run_launches(Plan &P, const std::vector<double> &cost, int32_t n_inst)
         R.launches.push_back(L);
     }
     for (int32_t i : ids) R.wide_lds = std::max(R.wide_lds, bytes_of(i, 1));
+    int64_t per_engine = 0;          // wavefronts that the first engine (8 CUs of 4 SIMDs) is dealt at most
+    for (const Launch &L : R.launches) per_engine += (L.count + n_cu / 8 - 1) / (n_cu / 8);
+    R.alone = per_engine <= 32;
     R.order = ids;
 }
 
@@ -463,7 +486,7 @@ int32_t validate_and_plan(const pc_trace_desc *traces, int32_t n_traces, const p
         R.zeros = off - R.o_start;
         R.o_id = take(4 * R.id_words);
         R.o_req = take((int64_t)sizeof(pcr::RunReq) * R.n_req);
-        plan_run_launches(P, cost, n_inst);
+        plan_run_launches(P, cost, n_inst, lds_cu, n_cu);
     }
     P.ws_bytes = std::max<int64_t>(off, 256);
     // launches: one per (layout, instances per CU), each sized to its
@@ -719,16 +742,17 @@ int32_t launch_planned(const Plan &P, int32_t n_traces, int32_t n_inst, uint8_t 
         if (e != hipSuccess) return hip_fail(e, "trace analysis launch");
         e = pcr::runs_set_lds_limit(160 * 1024);
         if (e != hipSuccess) return hip_fail(e, "replay LDS limit");
+        const int32_t alone = R.alone;
         const int32_t *d_rord = (const int32_t *)(ws + R.o_order);
         std::vector<Task> tasks;
         for (const Launch &L : R.launches)
             tasks.push_back({L.est, [=](hipStream_t q) {
-                return pcr::launch_runs_replay(A, d_rord + L.first, L.count, L.lds_bytes, ws, stats, d_per_request, q);
+                return pcr::launch_runs_replay(A, d_rord + L.first, L.count, L.lds_bytes, alone, ws, stats, d_per_request, q);
             }});
         rc = run_tasks(tasks, s, fork);
         if (rc != PC_OK) return rc;
         A.wide = 1;      // (with every instance done, a few us)
-        e = pcr::launch_runs_replay(A, d_rord, (int32_t)R.order.size(), R.wide_lds, ws, stats, d_per_request, s);
+        e = pcr::launch_runs_replay(A, d_rord, (int32_t)R.order.size(), R.wide_lds, 0, ws, stats, d_per_request, s);
         if (e != hipSuccess) return hip_fail(e, "replay launch");
         done = A.done;
     }

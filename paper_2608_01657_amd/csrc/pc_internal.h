@@ -259,7 +259,7 @@ hipError_t launch_runs_analysis(const RunsArgs &A, uint4 *ones, int64_t n_ones, 
                                 uint32_t nb_req, uint32_t nb_list, hipStream_t s);
 hipError_t runs_set_lds_limit(int32_t lds_bytes);
 hipError_t launch_runs_replay(const RunsArgs &A, const int32_t *d_order, int32_t n_launch, int32_t lds_bytes,
-                              uint8_t *ws, int64_t *stats, int32_t *per_req, hipStream_t s);
+                              int32_t alone, uint8_t *ws, int64_t *stats, int32_t *per_req, hipStream_t s);
 
 // Launchers (defined in the .hip files; host-callable).
 hipError_t launch_block_offsets(const int32_t *len, int64_t n_req, int64_t *key_off,

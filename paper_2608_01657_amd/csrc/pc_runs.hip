@@ -495,8 +495,8 @@ DEV bool replay_policy(const RunParams &P, const Feed &F, int64_t *st, LDS_AS ui
     return P.K == 1 ? replay_one<kPol, true, true>(P, F, st, lds) : replay_one<kPol, false, true>(P, F, st, lds);
 }
 
-__global__ __launch_bounds__(64) void runs_replay(RunsArgs A, const int32_t *__restrict__ order, uint8_t *ws,
-                                                  int64_t *stats, int32_t *per_req) {
+DEV void replay_instance(const RunsArgs &A, const int32_t *__restrict__ order, uint8_t *ws, int64_t *stats,
+                         int32_t *per_req) {
     extern __shared__ __align__(16) uint32_t runs_smem[];
     const int id = order[blockIdx.x];
     if (A.wide && A.done[id]) return;
@@ -540,6 +540,16 @@ __global__ __launch_bounds__(64) void runs_replay(RunsArgs A, const int32_t *__r
     else ok = replay_policy<kPS>(P, F, st, lds);
     if (ok && threadIdx.x == 0) *done = 1;
 }
+__global__ __launch_bounds__(64) void runs_replay(RunsArgs A, const int32_t *__restrict__ order, uint8_t *ws,
+                                                  int64_t *stats, int32_t *per_req) {
+    replay_instance(A, order, ws, stats, per_req);
+}
+// The same with so many registers asked for that a second wavefront of this
+// kernel does not fit on the SIMD (others do): see plan_run_launches.
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) void runs_replay_alone(
+    RunsArgs A, const int32_t *__restrict__ order, uint8_t *ws, int64_t *stats, int32_t *per_req) {
+    replay_instance(A, order, ws, stats, per_req);
+}
 
 }  // namespace
 
@@ -556,14 +566,21 @@ hipError_t launch_runs_analysis(const RunsArgs &A, uint4 *ones, int64_t n_ones, 
 }
 
 hipError_t runs_set_lds_limit(int32_t lds_bytes) {
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(&runs_replay),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&runs_replay),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+    if (e != hipSuccess) return e;
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(&runs_replay_alone),
                                hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
 }
 
 hipError_t launch_runs_replay(const RunsArgs &A, const int32_t *d_order, int32_t n_launch, int32_t lds_bytes,
-                              uint8_t *ws, int64_t *stats, int32_t *per_req, hipStream_t s) {
-    hipLaunchKernelGGL(runs_replay, dim3((unsigned)n_launch), dim3(64), (size_t)lds_bytes, s, A, d_order, ws, stats,
-                       per_req);
+                              int32_t alone, uint8_t *ws, int64_t *stats, int32_t *per_req, hipStream_t s) {
+    if (alone)
+        hipLaunchKernelGGL(runs_replay_alone, dim3((unsigned)n_launch), dim3(64), (size_t)lds_bytes, s, A, d_order,
+                           ws, stats, per_req);
+    else
+        hipLaunchKernelGGL(runs_replay, dim3((unsigned)n_launch), dim3(64), (size_t)lds_bytes, s, A, d_order, ws,
+                           stats, per_req);
     return hipGetLastError();
 }
 
