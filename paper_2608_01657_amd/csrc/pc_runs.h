@@ -292,6 +292,9 @@ struct RunReplay {
     PC_RUNS_FN void put3(const Window &r, uint32_t at, uint32_t lo, uint32_t w, uint32_t x) {
         wv.template st1<kX ? 3 : 2>(r.p, at, scratch, lo, w, x);
     }
+    PC_RUNS_FN void put_at(Lds p, uint32_t at, uint32_t lo, uint32_t w, uint32_t x) {
+        wv.template st1<3>(p, at, scratch, lo, w, x);
+    }
     PC_RUNS_FN void push(Window &r, uint32_t lo, uint32_t w, uint32_t x) {
         put3(r, entry(r.tail), lo, w, x);
         r.tail += 1;
@@ -544,98 +547,108 @@ struct RunReplay {
     // at a time in registers; at the end of a chunk it is read again, for
     // what was appended to it meanwhile, before the next one.
     struct Cursor {
-        vu lo, w;
+        vu lo, w, x;
         uint64_t m;
         uint32_t c;
     };
-    PC_RUNS_FN void fill(const Window &r, uint32_t pin, Cursor &q) {
+    PC_RUNS_FN void load(const Window &r, Cursor &q) const {
         W::sync();
         const vu at = lane + q.c * kStep;
         q.lo = W::ld(r.p, at);
         q.w = W::ld(r.p + kW, at);
-        q.m = W::ballot(W::ld(r.p + kXo, at) != pin) & W::ballot(q.lo != kNone);
+        q.x = W::ld(r.p + kXo, at);
     }
-    PC_RUNS_FN bool next(const Window &r, uint32_t pin, Cursor &q) {
-        if (W::likely(q.m != 0)) return true;
-        fill(r, pin, q);
+    PC_RUNS_FN void choose(uint32_t pin, Cursor &q) const {
+        q.m = W::ballot(q.x != pin) & W::ballot(q.lo != kNone);
+    }
+    // The next chunk with such a run; there is one (the counts of blocks that
+    // are not pinned say so).
+    PC_RUNS_FN void advance(const Window &r, uint32_t pin, Cursor &q, uint32_t &rem) {
+        load(r, q);
+        choose(pin, q);
         while (q.m == 0) {
             q.c += 1;
-            if (64u * q.c >= r.tail) return false;
-            fill(r, pin, q);
+            if (64u * q.c >= r.tail) {      // cannot happen
+                over = 1;
+                rem = 0;
+                q.c = 0;
+                q.m = 1;
+                return;
+            }
+            load(r, q);
+            choose(pin, q);
         }
-        return true;
     }
     // The deepest k blocks of the run in lane l (word w, first id lo) leave it.
     PC_RUNS_FN void shorten(Window &r, Cursor &q, int l, uint32_t lo, uint32_t w, uint32_t k) {
         const bool all = k == (w & kLen);
         const uint32_t nw = all ? kDead : w - k;
         q.w = W::setlane(q.w, l, nw);
-        if (all) q.m &= q.m - 1;
-        put2(r, entry(64u * q.c + (uint32_t)l), all ? kNone : lo, nw);
+        q.m = all ? q.m & (q.m - 1) : q.m;
+        put2(r, entry(64u * q.c) + (uint32_t)l, all ? kNone : lo, nw);
     }
-    PC_RUNS_FN void evict_s3(uint32_t e, uint32_t pin) {
+    // S, M: the first chunks of the small and the main queue, as they are.
+    // Whether a run moves on or leaves is told by selects: a step has one
+    // branch, for the queue that it looks at.
+    PC_RUNS_FN void evict_s3(uint32_t e, uint32_t pin, Cursor &S, Cursor &M) {
         uint32_t rem = e;
-        if (!room_for(q1, 32) || !ghost_room(32)) { over = 1; return; }
-        Cursor S, M;
-        S.c = M.c = 0;
-        M.m = 0;
-        M.lo = M.w = wv.vu0(0);
-        fill(q0, pin, S);
-        while (rem > 0) {
-            if (W::unlikely(q1.tail > q1.lim + kSlack / 2 || gh.tail > gh.lim + kSlack / 2)) {
-                if (!room_for(q1, 1) || !ghost_room(1)) { over = 1; return; }
+        const uint32_t tail = q1.tail;
+        if (W::unlikely(!room_for(q1, 32) || !ghost_room(32))) { over = 1; return; }
+        if (W::unlikely(q1.tail != tail)) load(q1, M);       // (compacted)
+        choose(pin, S);
+        choose(pin, M);
+        uint32_t steps = 32 + kSlack / 2;       // each appends a run to either window at most
+        do {
+            if (W::unlikely(--steps == 0)) {
+                if (!room_for(q1, 1) || !ghost_room(1)) { over = 1; rem = 0; }
                 M.c = 0;         // (positions changed)
                 M.m = 0;
+                steps = kSlack / 2;
             }
-            uint32_t lo, w, k, again = 0;       // again: enter the main queue's tail
             if (W::likely((s_size >= P.s_cap && s_unp > 0) || m_unp == 0)) {
-                if (!next(q0, pin, S)) { over = 1; return; }
+                if (W::unlikely(S.m == 0)) advance(q0, pin, S, rem);
                 const int l = W::ffs(S.m);
-                lo = W::rdl(S.lo, l);
-                w = W::rdl(S.w, l);
+                const uint32_t lo = W::rdl(S.lo, l), w = W::rdl(S.w, l), len = w & kLen;
                 // how many of the run's blocks (deepest first) go before the
-                // one-at-a-time rule would look at the main queue
-                const uint32_t len = w & kLen;
+                // one-at-a-time rule would look at the main queue (the first
+                // move gives the main queue an unpinned block)
+                const bool mv = (int32_t)((w >> kFrqS) & 3u) >= P.move_thr;
                 const int32_t la = s_size - P.s_cap + 1 < s_unp ? s_size - P.s_cap + 1 : s_unp;
-                if ((int32_t)((w >> kFrqS) & 3u) >= P.move_thr) {
-                    // (the first move gives the main queue an unpinned block)
-                    k = umin(len, m_unp == 0 ? (la > 1 ? (uint32_t)la : 1u) : (uint32_t)la);
-                    again = k | (w & kAttr & ~(3u << kFrqS));
-                    n_moves = n_moves + k;
-                    m_unp += (int32_t)k;
-                } else {
-                    k = umin(len, rem);
-                    if (m_unp > 0) k = umin(k, (uint32_t)la);
-                    if (P.g_cap > 0) push(gh, lo + len - k, k, gseq);
-                    gseq += k;
-                    n_gins = n_gins + k;
-                }
+                const uint32_t few = (uint32_t)(mv ? (m_unp == 0 && la < 1 ? 1 : la) : (m_unp > 0 ? la : 0x7FFFFFFF));
+                uint32_t k = umin(len, few);
+                k = mv ? k : umin(k, rem);
+                const uint32_t gone = mv ? 0u : k;
+                const Lds to = mv ? q1.p : gh.p;
+                put_at(to, entry(mv ? q1.tail : gh.tail), lo + len - k,
+                       mv ? k | (w & kAttr & ~(3u << kFrqS)) : k, mv ? pin - 1u : gseq);
+                q1.tail += mv ? 1u : 0u;
+                gh.tail += mv || P.g_cap <= 0 ? 0u : 1u;      // (without a ghost nothing reads what is there)
+                m_unp += (int32_t)(k - gone);
+                gseq += gone;
+                n_moves = n_moves + (k - gone);
+                n_gins = n_gins + gone;
                 s_size -= (int32_t)k;
                 s_unp -= (int32_t)k;
                 shorten(q0, S, l, lo, w, k);
+                victims(is_lane(u_owner(w)), gone);
+                rem -= gone;
             } else {
-                if (!next(q1, pin, M)) { over = 1; return; }
+                if (W::unlikely(M.m == 0)) advance(q1, pin, M, rem);
                 const int l = W::ffs(M.m);
-                lo = W::rdl(M.lo, l);
-                w = W::rdl(M.w, l);
-                const uint32_t len = w & kLen;
-                if ((w >> kFrqS) & 3u) {
-                    k = len;
-                    again = w - (1u << kFrqS);
-                    n_reins = n_reins + len;
-                } else {
-                    k = umin(umin(len, rem), (uint32_t)m_unp);
-                    m_unp -= (int32_t)k;
-                }
+                const uint32_t lo = W::rdl(M.lo, l), w = W::rdl(M.w, l), len = w & kLen;
+                const bool mv = ((w >> kFrqS) & 3u) != 0;
+                const uint32_t k = mv ? len : umin(umin(len, rem), (uint32_t)m_unp);
+                const uint32_t gone = mv ? 0u : k;
                 shorten(q1, M, l, lo, w, k);
+                // (what leaves from here is written nowhere)
+                put_at(mv ? q1.p : scratch, mv ? entry(q1.tail) : 0u, lo, w - (1u << kFrqS), pin - 1u);
+                q1.tail += mv ? 1u : 0u;
+                n_reins = n_reins + (k - gone);
+                m_unp -= (int32_t)gone;
+                victims(is_lane(u_owner(w)), gone);
+                rem -= gone;
             }
-            if (again) {
-                push(q1, lo + (w & kLen) - k, again, pin - 1u);
-            } else {
-                victims(is_lane(u_owner(w)), k);
-                rem -= k;
-            }
-        }
+        } while (rem > 0);
         resident -= (int32_t)e;
     }
     // Room for k more ghost runs: ids that have left the ghost (older than
@@ -678,6 +691,27 @@ struct RunReplay {
             pm |= any ? 1ull << i : 0ull;
         } while (++i < np);
         return pm;
+    }
+    // The same for S3-FIFO's three windows at once (`far`: of the ghost only
+    // whether; what an eviction of this request adds there meets no piece of it).
+    PC_RUNS_FN void meets3(const Four &a4, const Four &b4, const Four &c4, uint32_t np, vu pa, vu pl, uint64_t &pa4,
+                           uint64_t &pb4, bool &far) const {
+        uint64_t ma = 0, mb = 0, mc = 0;
+        uint32_t i = 0;
+        do {
+            const uint32_t a = W::rdl(pa, (int)i), L = W::rdl(pl, (int)i);
+            const uint64_t x = (W::ballot(a4.v[0] - a < L) | W::ballot(a4.v[1] - a < L)) |
+                               (W::ballot(a4.v[2] - a < L) | W::ballot(a4.v[3] - a < L));
+            const uint64_t y = (W::ballot(b4.v[0] - a < L) | W::ballot(b4.v[1] - a < L)) |
+                               (W::ballot(b4.v[2] - a < L) | W::ballot(b4.v[3] - a < L));
+            mc |= (W::ballot(c4.v[0] - a < L) | W::ballot(c4.v[1] - a < L)) |
+                  (W::ballot(c4.v[2] - a < L) | W::ballot(c4.v[3] - a < L));
+            ma |= x ? 1ull << i : 0ull;
+            mb |= y ? 1ull << i : 0ull;
+        } while (++i < np);
+        pa4 = ma;
+        pb4 = mb;
+        far = mc != 0;
     }
     // Runs of window r, group b (ids lo), that the pieces of mask pm meet:
     // their leading part is filed with its depth in the request and taken off
@@ -748,13 +782,22 @@ struct RunReplay {
         // and ghost are looked at where they grow)
         if (W::unlikely(np > kRunsMaxPieces || c >= (uint32_t)K())) { over = 1; return adm; }
         if (W::unlikely(q0.tail + np > q0.lim) && !room_for(q0, np)) { over = 1; return adm; }
-        Four m4;                     // S3-FIFO: ids of the main queue's first group
+        // S3-FIFO: ids of the first groups of the main queue and the ghost, and
+        // the first chunks of the two queues, for the eviction (loaded here,
+        // so that it need not wait for them)
+        Four m4, g4;
+        Cursor S, M;
         if (kPol != S3) {
             reload();
         } else {
             lo4 = load4(q0, 0, 0);
             m4 = load4(q1, 0, 0);
+            g4 = load4(gh, 0, 0);
+            S.c = M.c = 0;
+            load(q0, S);
+            load(q1, M);
         }
+        const uint32_t gtail = kPol == S3 ? gh.tail : 0u;
         refill(q.dt);
         const uint32_t room = (uint32_t)(kPol == SQ ? P.C / P.G : P.C);
         const uint32_t n = umin(q.n_full, room);
@@ -776,10 +819,11 @@ struct RunReplay {
         // ---- lookup
         nm = 0;
         uint32_t found = 0, far = 0;
+        bool ghosts = false;         // S3-FIFO: the ghost may remember blocks of the request
         {
-            const uint64_t pm = meets(lo4, np, pid, pl);
             if (kPol == S3) {
-                const uint64_t pm1 = meets(m4, np, pid, pl);
+                uint64_t pm, pm1;
+                meets3(lo4, m4, g4, np, pid, pl, pm, pm1, ghosts);
                 if (W::unlikely((pm | pm1) != 0)) {
                     meet<true, false>(q0, 0, lo4, pm, 0, pid, pl, pc, found, far);
                     meet<true, false>(q1, 0, m4, pm1, 1, pid, pl, pc, found, far);
@@ -789,6 +833,7 @@ struct RunReplay {
                     meet_from<true, false>(q1, 256, 1, np, pid, pl, pc, found, far);
                 }
             } else {
+                const uint64_t pm = meets(lo4, np, pid, pl);
                 if (W::unlikely(pm != 0)) meet<false, false>(q0, 0, lo4, pm, 0, pid, pl, pc, found, far);
                 if (W::unlikely(q0.tail > 256)) meet_from<false, false>(q0, 256, 0, np, pid, pl, pc, found, far);
             }
@@ -833,7 +878,11 @@ struct RunReplay {
                     }
                 }
             }
-            if (kPol == S3) touch_s3(r, hits, hitS, hitM);
+            if (kPol == S3) {
+                touch_s3(r, hits, hitS, hitM);
+                load(q0, S);
+                load(q1, M);
+            }
         }
         const uint32_t m = nn - hend;
 
@@ -845,7 +894,7 @@ struct RunReplay {
             if (kPol == LRU) take(0u, 0u, -1, 0u, (uint32_t)e);
             else if (kPol == PS) evict_ps((uint32_t)e);
             else if (kPol == SQ) take(kOwnM, g << kOwnS, (int32_t)g, 0u, (uint32_t)e);
-            else evict_s3((uint32_t)e, r + 1u);
+            else evict_s3((uint32_t)e, r + 1u, S, M);
             n_evc = W::mad24(me, (uint32_t)e, n_evc);
         } else {
             e = 0;
@@ -869,7 +918,7 @@ struct RunReplay {
 
         // ---- new blocks and released blocks enter the queue, deepest first
         if (kPol == S3) {
-            if (m > 0) insert_s3(r, np, pid, pl, pc, hend, nw, m);
+            if (m > 0) insert_s3(r, np, pid, pl, pc, hend, nw, m, ghosts || gtail > 256);
             s_unp += (int32_t)hitS;
             m_unp += (int32_t)hitM;
         } else {
@@ -1007,14 +1056,15 @@ struct RunReplay {
     }
     // New blocks enter the small queue, or the main queue where the ghost
     // remembers them, deepest first.
-    PC_RUNS_FN void insert_s3(uint32_t r, uint32_t np, vu pid, vu pl, vu pc, uint32_t hend, uint32_t nw, uint32_t m) {
+    PC_RUNS_FN void insert_s3(uint32_t r, uint32_t np, vu pid, vu pl, vu pc, uint32_t hend, uint32_t nw, uint32_t m,
+                              bool ghosts) {
         const vu zu = wv.vu0(0);
         const vb isn = (pl > 0u) & (pc + pl > hend);
         const vu off = W::sel(pc < hend, wv.vu0(hend) - pc, zu);
         const vu a = pid + off, L = W::sel(isn, pl - off, zu);
         nm = 0;
         uint32_t nghost = 0, far = 0;
-        if (P.g_cap > 0) meet_from<false, true>(gh, 0, 0, np, a, L, zu, nghost, far);
+        if (W::unlikely(ghosts && P.g_cap > 0)) meet_from<false, true>(gh, 0, 0, np, a, L, zu, nghost, far);
         uint64_t nmask = W::ballot(isn);
         uint64_t inl = 0;
         if (W::unlikely(nm > 0)) {
