@@ -384,55 +384,10 @@ struct RunReplay {
         uint32_t rem = k;
         uint32_t b = 0;
         for (;;) {
-            uint64_t m4[4];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) m4[c] = W::ballot((w4.v[c] & (mask | kDead)) == pat);
-#pragma unroll
-            for (uint32_t c = 0; c < 4; ++c) {
-                uint64_t m = m4[c];
-                if (m == 0) continue;
-                // the first runs one by one (mostly a take ends inside the
-                // second), many small ones by a prefix sum
-                int it = 0;
-                do {
-                    const int l = W::ffs(m);
-                    m &= m - 1;
-                    const uint32_t wl = W::rdl(w4.v[c], l), len = wl & kLen;
-                    const bool all = len <= rem;
-                    const uint32_t n = all ? len : rem;
-                    w4.v[c] = W::setlane(w4.v[c], l, all ? kDead : wl - n);
-                    lo4.v[c] = W::setlane(lo4.v[c], l, all ? kNone : W::rdl(lo4.v[c], l));
-                    rem -= n;
-                    if (!(kQ && x >= 0)) {
-                        const vu o = is_lane(u_owner(wl));
-                        victims(o, n);
-                        if (kQ) count_queue(o, seg_of(wl), 0u - n);
-                    }
-                } while (rem > 0 && m && ++it < 6);
-                if (W::unlikely(rem > 0 && m)) {
-                    const vu len = W::sel(W::of_mask(m), w4.v[c] & kLen, wv.vu0(0));
-                    const vu upto = W::scan(len), before = upto - len;
-                    const vu tk = W::sel(before < rem, W::vmin(len, wv.vu0(rem) - before), wv.vu0(0));
-                    rem -= umin(W::rdl(upto, 63), rem);
-                    if (!(kQ && x >= 0))
-                        for (uint64_t vm = W::ballot(tk > 0u); vm; vm &= vm - 1) {
-                            const int l = W::ffs(vm);
-                            const uint32_t wl = W::rdl(w4.v[c], l), n = W::rdl(tk, l);
-                            const vu o = is_lane(u_owner(wl));
-                            victims(o, n);
-                            if (kQ) count_queue(o, seg_of(wl), 0u - n);
-                        }
-                    const vb all = (tk > 0u) & (tk == len);
-                    lo4.v[c] = W::sel(all, wv.vu0(kNone), lo4.v[c]);
-                    w4.v[c] = W::sel(all, wv.vu0(kDead), w4.v[c] - tk);
-                }
-                store(q0, b, c, 0, lo4.v[c]);
-                store(q0, b, c, kW, w4.v[c]);
-                if (W::likely(rem == 0)) break;
-            }
+            take_chunk<0>(b, mask, pat, x, rem);
             if (W::likely(rem == 0)) break;
             b += 256;
-            if (b >= q0.tail) { over = 1; break; }   // cannot happen: the counts say that the queue holds k
+            if (W::unlikely(b >= q0.tail)) { over = 1; rem = 0; break; }   // cannot happen: the counts say that the queue holds k
             lo4 = load4(q0, b, 0);
             w4 = load4(q0, b, kW);
         }
@@ -443,6 +398,34 @@ struct RunReplay {
             count_queue(o, seg, 0u - k);
         }
         resident -= (int32_t)k;
+    }
+    // ... from chunk c of the group at b on.  A prefix sum over the chunk tells
+    // how much of every run goes: cheaper than two runs one by one.
+    template <int c>
+    PC_RUNS_FN void take_chunk(uint32_t b, uint32_t mask, uint32_t pat, int32_t x, uint32_t &rem) {
+        const vb in = (w4.v[c] & (mask | kDead)) == pat;
+        if (W::ballot(in) != 0) {
+            const vu len = W::sel(in, w4.v[c] & kLen, wv.vu0(0));
+            const vu upto = W::scan(len), before = upto - len;
+            const vu tk = W::sel(before < rem, W::vmin(len, wv.vu0(rem) - before), wv.vu0(0));
+            const vb all = in & (tk == len);
+            const uint32_t tot = W::rdl(upto, 63);
+            if (!(kQ && x >= 0))
+                for (uint64_t vm = W::ballot(tk > 0u); vm; vm &= vm - 1) {
+                    const int l = W::ffs(vm);
+                    const uint32_t wl = W::rdl(w4.v[c], l), n = W::rdl(tk, l);
+                    const vu o = is_lane(u_owner(wl));
+                    victims(o, n);
+                    if (kQ) count_queue(o, seg_of(wl), 0u - n);
+                }
+            lo4.v[c] = W::sel(all, wv.vu0(kNone), lo4.v[c]);
+            w4.v[c] = W::sel(all, wv.vu0(kDead), w4.v[c] - tk);
+            store(q0, b, c, 0, lo4.v[c]);
+            store(q0, b, c, kW, w4.v[c]);
+            rem = rem > tot ? rem - tot : 0u;
+            if (W::likely(rem == 0)) return;
+        }
+        if constexpr (c < 3) take_chunk<c + 1>(b, mask, pat, x, rem);
     }
     // the queue's first group again
     PC_RUNS_FN void reload() {

@@ -90,14 +90,20 @@ struct DevWave {
         v = vmax(v, dpp<0x143, 0xC>(0u, v));
         return rdl(v, 63);
     }
-    DEV static int64_t wmax64(int64_t v) {     // a lane without a source lane keeps its own value
-        v = vmax(v, dpp64<0x111, 0xF>(v));
-        v = vmax(v, dpp64<0x112, 0xF>(v));
-        v = vmax(v, dpp64<0x114, 0xF>(v));
-        v = vmax(v, dpp64<0x118, 0xF>(v));
-        v = vmax(v, dpp64<0x142, 0xA>(v));
-        v = vmax(v, dpp64<0x143, 0xC>(v));
-        return rdl64(v, 63);
+    // (upper words first, then the lower words of those that have the most:
+    // half the instructions of six steps on 64-bit values)
+    DEV static int64_t wmax64(int64_t v) {
+        const int32_t hi = (int32_t)(v >> 32);
+        int32_t h = hi;
+        h = vmax(h, (int32_t)dpp<0x111, 0xF>(0x80000000u, (uint32_t)h));
+        h = vmax(h, (int32_t)dpp<0x112, 0xF>(0x80000000u, (uint32_t)h));
+        h = vmax(h, (int32_t)dpp<0x114, 0xF>(0x80000000u, (uint32_t)h));
+        h = vmax(h, (int32_t)dpp<0x118, 0xF>(0x80000000u, (uint32_t)h));
+        h = vmax(h, (int32_t)dpp<0x142, 0xA>(0x80000000u, (uint32_t)h));
+        h = vmax(h, (int32_t)dpp<0x143, 0xC>(0x80000000u, (uint32_t)h));
+        const int32_t top = (int32_t)rdl((uint32_t)h, 63);
+        const uint32_t lo = wmax(hi == top ? (uint32_t)(uint64_t)v : 0u);
+        return (int64_t)(((uint64_t)(uint32_t)top << 32) | lo);
     }
     DEV static uint32_t mbcnt(uint64_t m) {
         return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
