@@ -363,10 +363,10 @@ struct RunReplay {
 
     // d more (or, as a two's complement, fewer) blocks in a queue
     PC_RUNS_FN void count_queue(vu is_owner, uint32_t seg, uint32_t d) {
-        cnt0 = W::mad24(is_owner, kPol == SQ || seg == 0 ? d : 0u, cnt0);
+        cnt0 = W::mad01(is_owner, kPol == SQ || seg == 0 ? d : 0u, cnt0);
         if (kPol == PS) {
-            cnt1 = W::mad24(is_owner, seg == 1 ? d : 0u, cnt1);
-            cnt2 = W::mad24(is_owner, seg == 2 ? d : 0u, cnt2);
+            cnt1 = W::mad01(is_owner, seg == 1 ? d : 0u, cnt1);
+            cnt2 = W::mad01(is_owner, seg == 2 ? d : 0u, cnt2);
         }
     }
     PC_RUNS_FN vu is_lane(uint32_t l) const { return W::sel(lane == l, wv.vu0(1), wv.vu0(0)); }
@@ -374,8 +374,9 @@ struct RunReplay {
         return (kPol == PS && !(P.flags & 1)) ? u_cls(w) : 0u;
     }
     PC_RUNS_FN void victims(vu is_owner, uint32_t n) {
-        evw = W::mad24(is_owner, n, evw);
-        res = W::mad24(is_owner, 0u - n, res);
+        const vu t = W::mad01(is_owner, n, wv.vu0(0));
+        evw = evw + t;
+        res = res - t;
     }
 
     // k victims from the queue, oldest first: those whose word, under `mask`,
@@ -546,7 +547,9 @@ struct RunReplay {
     }
     // The next chunk with such a run; there is one (the counts of blocks that
     // are not pinned say so).
+    template <bool kSmall>
     PC_RUNS_FN void advance(const Window &r, uint32_t pin, Cursor &q, uint32_t &rem) {
+        if (kSmall) write_back(q);
         load(r, q);
         choose(pin, q);
         while (q.m == 0) {
@@ -563,12 +566,23 @@ struct RunReplay {
         }
     }
     // The deepest k blocks of the run in lane l (word w, first id lo) leave it.
-    PC_RUNS_FN void shorten(Window &r, Cursor &q, int l, uint32_t lo, uint32_t w, uint32_t k) {
+    // The small queue's chunk, which nothing is appended to meanwhile, is
+    // changed in registers and written back at its end; the main queue's in
+    // the window.
+    PC_RUNS_FN void write_back(const Cursor &q) const {
+        const vu at = lane + q.c * kStep;
+        W::st_all(q0.p, at, q.lo);
+        W::st_all(q0.p + kW, at, q.w);
+        W::sync();
+    }
+    template <bool kSmall>
+    PC_RUNS_FN void shorten(Cursor &q, int l, uint32_t lo, uint32_t w, uint32_t k) {
         const bool all = k == (w & kLen);
         const uint32_t nw = all ? kDead : w - k;
         q.w = W::setlane(q.w, l, nw);
+        if (kSmall) q.lo = W::setlane(q.lo, l, all ? kNone : lo);
+        else put2(q1, entry(64u * q.c) + (uint32_t)l, all ? kNone : lo, nw);
         q.m = all ? q.m & (q.m - 1) : q.m;
-        put2(r, entry(64u * q.c) + (uint32_t)l, all ? kNone : lo, nw);
     }
     // S, M: the first chunks of the small and the main queue, as they are.
     // Whether a run moves on or leaves is told by selects: a step has one
@@ -581,6 +595,7 @@ struct RunReplay {
         choose(pin, S);
         choose(pin, M);
         uint32_t steps = 32 + kSlack / 2;       // each appends a run to either window at most
+        const uint32_t ghost = P.g_cap > 0 ? 1u : 0u;
         do {
             if (W::unlikely(--steps == 0)) {
                 if (!room_for(q1, 1) || !ghost_room(1)) { over = 1; rem = 0; }
@@ -588,41 +603,44 @@ struct RunReplay {
                 M.m = 0;
                 steps = kSlack / 2;
             }
-            if (W::likely((s_size >= P.s_cap && s_unp > 0) || m_unp == 0)) {
-                if (W::unlikely(S.m == 0)) advance(q0, pin, S, rem);
+            // blocks of the small queue (deepest first) that go before the
+            // one-at-a-time rule would look at the main queue
+            const int32_t la = s_size - P.s_cap + 1 < s_unp ? s_size - P.s_cap + 1 : s_unp;
+            const int32_t none = m_unp == 0 ? 1 : 0;
+            if (W::likely((la > none ? la : none) > 0)) {
+                if (W::unlikely(S.m == 0)) advance<true>(q0, pin, S, rem);
                 const int l = W::ffs(S.m);
                 const uint32_t lo = W::rdl(S.lo, l), w = W::rdl(S.w, l), len = w & kLen;
-                // how many of the run's blocks (deepest first) go before the
-                // one-at-a-time rule would look at the main queue (the first
-                // move gives the main queue an unpinned block)
+                // (the first move gives the main queue an unpinned block)
                 const bool mv = (int32_t)((w >> kFrqS) & 3u) >= P.move_thr;
-                const int32_t la = s_size - P.s_cap + 1 < s_unp ? s_size - P.s_cap + 1 : s_unp;
                 const uint32_t few = (uint32_t)(mv ? (m_unp == 0 && la < 1 ? 1 : la) : (m_unp > 0 ? la : 0x7FFFFFFF));
-                uint32_t k = umin(len, few);
+                // (kept apart: three minima in a row become one vector
+                // instruction, and what depends on it moves to vector registers)
+                uint32_t k = W::keep(umin(len, few));
                 k = mv ? k : umin(k, rem);
                 const uint32_t gone = mv ? 0u : k;
                 const Lds to = mv ? q1.p : gh.p;
                 put_at(to, entry(mv ? q1.tail : gh.tail), lo + len - k,
                        mv ? k | (w & kAttr & ~(3u << kFrqS)) : k, mv ? pin - 1u : gseq);
                 q1.tail += mv ? 1u : 0u;
-                gh.tail += mv || P.g_cap <= 0 ? 0u : 1u;      // (without a ghost nothing reads what is there)
+                gh.tail += mv ? 0u : ghost;      // (without a ghost nothing reads what is there)
                 m_unp += (int32_t)(k - gone);
                 gseq += gone;
                 n_moves = n_moves + (k - gone);
                 n_gins = n_gins + gone;
                 s_size -= (int32_t)k;
                 s_unp -= (int32_t)k;
-                shorten(q0, S, l, lo, w, k);
+                shorten<true>(S, l, lo, w, k);
                 victims(is_lane(u_owner(w)), gone);
                 rem -= gone;
             } else {
-                if (W::unlikely(M.m == 0)) advance(q1, pin, M, rem);
+                if (W::unlikely(M.m == 0)) advance<false>(q1, pin, M, rem);
                 const int l = W::ffs(M.m);
                 const uint32_t lo = W::rdl(M.lo, l), w = W::rdl(M.w, l), len = w & kLen;
                 const bool mv = ((w >> kFrqS) & 3u) != 0;
-                const uint32_t k = mv ? len : umin(umin(len, rem), (uint32_t)m_unp);
+                const uint32_t k = mv ? len : umin(W::keep(umin(len, rem)), (uint32_t)m_unp);
                 const uint32_t gone = mv ? 0u : k;
-                shorten(q1, M, l, lo, w, k);
+                shorten<false>(M, l, lo, w, k);
                 // (what leaves from here is written nowhere)
                 put_at(mv ? q1.p : scratch, mv ? entry(q1.tail) : 0u, lo, w - (1u << kFrqS), pin - 1u);
                 q1.tail += mv ? 1u : 0u;
@@ -632,6 +650,7 @@ struct RunReplay {
                 rem -= gone;
             }
         } while (rem > 0);
+        write_back(S);
         resident -= (int32_t)e;
     }
     // Room for k more ghost runs: ids that have left the ghost (older than
@@ -839,7 +858,7 @@ struct RunReplay {
                 hits = W::ballot(md < hend) & inl;
                 for (uint64_t om = inl & ~hits; om; om &= om - 1) {
                     const uint32_t w = W::rdl(mw, W::ffs(om));
-                    res = W::mad24(is_lane(u_owner(w)), 0u - (w & kLen), res);
+                    res = W::mad01(is_lane(u_owner(w)), 0u - (w & kLen), res);
                 }
                 resident -= (int32_t)norph;
             }
@@ -878,7 +897,7 @@ struct RunReplay {
             else if (kPol == PS) evict_ps((uint32_t)e);
             else if (kPol == SQ) take(kOwnM, g << kOwnS, (int32_t)g, 0u, (uint32_t)e);
             else evict_s3((uint32_t)e, r + 1u, S, M);
-            n_evc = W::mad24(me, (uint32_t)e, n_evc);
+            n_evc = W::mad01(me, (uint32_t)e, n_evc);
         } else {
             e = 0;
         }
@@ -896,7 +915,7 @@ struct RunReplay {
                     nw |= (c << kConS) | (cl << kClsS);
                 }
             }
-        res = W::mad24(me, m, res);
+        res = W::mad01(me, m, res);
         resident += (int32_t)m;
 
         // ---- new blocks and released blocks enter the queue, deepest first
@@ -911,14 +930,14 @@ struct RunReplay {
 
         // ---- counters and the accounting of every group
         n_req = n_req + me;
-        n_probe = W::mad24(me, n, n_probe);
-        n_hit = W::mad24(me, hend, n_hit);
+        n_probe = W::mad01(me, n, n_probe);
+        n_hit = W::mad01(me, hend, n_hit);
         if (W::unlikely(((nn ^ n) | (n ^ q.n_full) | norph | npromo | ngated) != 0)) {
-            c_dup = c_dup + W::widen(W::mad24(me, n - nn, zu));
+            c_dup = c_dup + W::widen(W::mad01(me, n - nn, zu));
             c_trunc = c_trunc + W::widen(me) * (int64_t)(q.n_full - n);
-            c_orph = c_orph + W::widen(W::mad24(me, norph, zu));
-            c_promo = c_promo + W::widen(W::mad24(me, npromo, zu));
-            c_gated = c_gated + W::widen(W::mad24(me, ngated, zu));
+            c_orph = c_orph + W::widen(W::mad01(me, norph, zu));
+            c_promo = c_promo + W::widen(W::mad01(me, npromo, zu));
+            c_gated = c_gated + W::widen(W::mad01(me, ngated, zu));
         }
         const vl d = raw_debt();
         d_sum = d_sum + d;

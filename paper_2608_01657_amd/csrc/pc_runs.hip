@@ -150,10 +150,9 @@ struct DevWave {
         to[64] = y;
         if (N > 2) to[128] = z;
     }
-    // a is 0 or 1 (or small), |b| < 2^23
-    DEV static uint32_t mad24(uint32_t a, uint32_t b, uint32_t c) {
-        return (uint32_t)(__mul24((int)a, (int)b) + (int)c);
-    }
+    DEV static uint32_t mad01(uint32_t a, uint32_t b, uint32_t c) { return (a ? b : 0u) + c; }      // a is 0 or 1
+    // a uniform value that stays in a scalar register
+    DEV static uint32_t keep(uint32_t x) { return rfl(x); }
     DEV static int64_t mad64(uint32_t a, int32_t b, int64_t c) { return (int64_t)(int32_t)a * (int64_t)b + c; }
     DEV static bool likely(bool x) { return __builtin_expect(x, true); }
     DEV static bool unlikely(bool x) { return __builtin_expect(x, false); }

@@ -191,10 +191,12 @@ struct HostWave {
         check(p + at);
         return p[at];
     }
-    static vu mad24(const vu &a, uint32_t b, const vu &c) {
-        if ((int32_t)b >= 1 << 23 || (int32_t)b < -(1 << 23)) die("mad24 factor");
+    static vu mad01(const vu &a, uint32_t b, const vu &c) {
+        for (uint32_t x : a.v)
+            if (x > 1) die("mad01 factor");
         return zip(a, c, [b](uint32_t x, uint32_t z) { return x * b + z; });
     }
+    static uint32_t keep(uint32_t x) { return x; }
     static vl mad64(const vu &a, int32_t b, const vl &c) {
         return zip(a, c, [b](uint32_t x, int64_t z) { return (int64_t)x * b + z; });
     }
