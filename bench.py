@@ -31,10 +31,10 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 # device copy) and LDS / occupancy figures.  Each is valid only for the batch
 # and the kernel source it was measured on.
 PROFILES = os.path.join(ROOT, "profiles")
-# what the replay kernel is built from: its sources and its compiler flags
+# what the replay kernels are built from: their sources and compiler flags
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2608_01657_amd", *f) for f in
-                  (("csrc", "pc_replay.hip"), ("csrc", "pc_replay_global.hip"), ("csrc", "pc_internal.h"),
-                   ("build.py",))]
+                  (("csrc", "pc_runs.hip"), ("csrc", "pc_runs.h"), ("csrc", "pc_replay.hip"),
+                   ("csrc", "pc_replay_global.hip"), ("csrc", "pc_internal.h"), ("build.py",))]
 HASH_BYTES_PER_BLOCK = 64 + 8  # 16 int32 tokens in, one uint64 key out
 HASH_BYTES_PER_REQ = 8 + 4 + 4 + 8 + 8   # tok_off, len, ns, key_off read, key_off write
 REPLAY_BYTES_PER_PROBE = 8     # the key
@@ -208,11 +208,14 @@ def main():
     hash_bytes = n_blocks_hash * HASH_BYTES_PER_BLOCK + n_req_hash * HASH_BYTES_PER_REQ
     hash_gbs = hash_bytes / (hash_ms * 1e-3) / 1e9
     dominant = "replay" if replay_ms >= hash_ms else "hash"
-    # the replay kernel of the layout most instances use (one launch per
-    # footprint class; a single class runs on the caller's stream)
+    # the replay stage is the trace analysis and the replay on runs; the
+    # phase-counter build and instances that do not fit that form take the
+    # general kernel of the layout given by layout_instances
     _, layouts = P.pc_replay_state_bytes(batch.tdesc, batch.idesc)
     lay = max(set(layouts), key=layouts.count)
-    roof = {"kernel": f"replay_kernel<{lay}> ({P.LAYOUT_NAMES[lay]} layout)" if dominant == "replay" else "hash_kernel",
+    general = f"replay_kernel<{lay}> ({P.LAYOUT_NAMES[lay]} layout)"
+    roof = {"kernel": ("hash_kernel" if dominant != "replay" else general if args.phase_profile else
+                       "runs_replay (one wavefront per instance) after the trace analysis"),
             "layout_instances": {P.LAYOUT_NAMES[x]: layouts.count(x) for x in sorted(set(layouts))},
             "bound": "hbm",
             "achieved": round(replay_gbs if dominant == "replay" else hash_gbs, 3),

@@ -38,7 +38,8 @@
 // the CPU, lane by lane.
 //
 // An instance that needs more runs than its windows hold is replayed again,
-// with windows that take a CU's whole LDS; one that needs more than those, or
+// with windows that take a CU's whole LDS (960 conversation instances 222 ms;
+// 281 with the general kernel instead of that); one that needs more than those, or
 // more pieces per request than lanes, is left to the general kernel
 // (pc_replay.hip).
 #pragma once

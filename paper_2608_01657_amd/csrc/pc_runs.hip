@@ -10,10 +10,16 @@
 //   runs_list     per request: its pieces, duplicates among them, RunReq
 //   runs_relist   the same again where duplicates added cuts (rare)
 // Bound: runs_insert and runs_link make one random table access per key; the
-// rest streams.
+// rest streams.  16 one-touch traces (800,000 requests, 120 M keys): insert
+// 5.0 ms, link 2.0, list 0.6, fill 0.15; 64 traces of conversations: insert
+// 6.5, link 1.9, list 1.2, fill 0.2.
 //
 // Replay: one wavefront per instance, no barriers; bound by the chain of
-// dependent instructions of a request.
+// dependent instructions of a request, whatever its number of blocks.  1,024
+// one-touch instances of 4,096 blocks, 50,000 requests each: 117 ms with keys
+// and analysis, 2.1 to 2.3 us a request; the general kernels, a workgroup of
+// four wavefronts and a step per 256 blocks, take 939 ms (two instances to a
+// CU, 18.8 us a request).
 #include "pc_internal.h"
 
 #define PC_RUNS_FN __device__ __forceinline__
