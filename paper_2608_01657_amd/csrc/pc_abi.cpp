@@ -135,12 +135,15 @@ constexpr bool kHaveRuns = true;
 #endif
 
 // What the replay on runs takes: positions and table slots below 2^31, and
-// prefix bitmaps and requests that one wavefront goes through in a moment.  A batch whose
-// longest trace is shorter than kRunsMinReq requests is over before the
-// analysis would have paid (about six launches against some 9 us a request).
+// prefix bitmaps and requests that one wavefront goes through in a moment.  A
+// batch whose longest trace is shorter than kRunsMinReq requests may be over
+// before the analysis has paid (48 instances on 16 traces, us, general kernels
+// and on runs: 8 requests of 4 blocks 84 and 98, of 200 blocks 747 and 286; 12
+// of 4 blocks 106 and 105; 16 of 4 blocks 127 and 107, of 200 blocks 2782 and
+// 1037).
 constexpr int64_t kRunsMaxKeys = (int64_t)1 << 30, kRunsMaxPrefix = (int64_t)1 << 22;
 constexpr int32_t kRunsMaxBlocks = 1 << 20;
-constexpr int64_t kRunsMinReq = 64;
+constexpr int64_t kRunsMinReq = 16;
 constexpr int64_t kRunsMaxBytes = (int64_t)16 << 30;
 
 // Which traces are analysed for the replay on runs, and the sizes of it.

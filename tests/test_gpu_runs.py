@@ -36,7 +36,7 @@ def test_unchained_documents_and_duplicates(seed):
     run_key_traces([chunk_trace(seed, n_req=700)], [_insts((25, 300, 3000))])
 
 
-@pytest.mark.parametrize("n_req", [63, 64, 65])
+@pytest.mark.parametrize("n_req", [1, 15, 16, 17, 63, 64, 65])
 def test_shortest_traces_on_runs(n_req):
     run_key_traces([chunk_trace(50 + n_req, n_req=n_req)], [_insts((1, 7, 64, 4096))])
 
