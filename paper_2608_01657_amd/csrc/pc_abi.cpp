@@ -108,7 +108,7 @@ struct RunsPlan {
     int32_t wide_lds = 0;             // of the second launch (widest windows)
     int64_t o_kb = 0, o_rt = 0, o_order = 0;                              // header
     int64_t o_table = 0, o_first = 0, ones = 0;                           // set to ones
-    int64_t o_start = 0, o_weak = 0, o_flags = 0, o_done = 0, zeros = 0;  // set to zeros
+    int64_t o_start = 0, o_weak = 0, o_cuts = 0, o_flags = 0, o_done = 0, zeros = 0;  // set to zeros
     int64_t o_id = 0, o_req = 0;
 };
 
@@ -192,7 +192,7 @@ void plan_runs(const pc_trace_desc *traces, int32_t n_traces, const pc_instance_
         nb_list += (t.n_req + pcr::kRunsListBlock - 1) / pcr::kRunsListBlock;
         R.trace_run[i] = (int32_t)R.rt.size();
         R.rt.push_back(d);
-        bytes = 4 * (R.table_words + R.id_words + 2 * R.bit_words + R.first_words) + 32 * R.n_req;
+        bytes = 4 * (R.table_words + R.id_words + 3 * R.bit_words + R.first_words) + 32 * R.n_req;
         if (bytes > kRunsMaxBytes || nb_pos + nb_req > INT32_MAX || nb_list > INT32_MAX) break;
     }
     R.on = longest >= kRunsMinReq && bytes <= kRunsMaxBytes && nb_pos + nb_req <= INT32_MAX && nb_list <= INT32_MAX;
@@ -484,6 +484,7 @@ int32_t validate_and_plan(const pc_trace_desc *traces, int32_t n_traces, const p
         R.ones = off - R.o_table;
         R.o_start = take(4 * R.bit_words);
         R.o_weak = take(4 * R.bit_words);
+        R.o_cuts = take(4 * R.bit_words);
         R.o_flags = take(4 * (int64_t)(R.rt.size() + 2 * R.kb.size()));
         R.o_done = take(4 * (int64_t)n_inst);
         R.zeros = off - R.o_start;
@@ -732,6 +733,7 @@ int32_t launch_planned(const Plan &P, int32_t n_traces, int32_t n_inst, uint8_t 
         A.id = (uint32_t *)(ws + R.o_id);
         A.start = (uint32_t *)(ws + R.o_start);
         A.weak = (uint32_t *)(ws + R.o_weak);
+        A.cuts = (uint32_t *)(ws + R.o_cuts);
         A.first = (uint32_t *)(ws + R.o_first);
         A.req = (pcr::RunReq *)(ws + R.o_req);
         A.tflag = (int32_t *)(ws + R.o_flags);

@@ -228,7 +228,7 @@ struct DevKeyBuf {
     int64_t n;
     int64_t tab0;          // first word of its table (2 n words; later its pieces, 8 bytes each)
     int64_t id0;           // first word of its ids (n)
-    int64_t bits0;         // first word of its start and weak-link bitmaps
+    int64_t bits0;         // first word of its bitmaps (starts, weak links, cuts)
     uint32_t slots;        // table entries
     uint32_t blk0;         // first block of runs_insert and runs_link
 };
@@ -244,7 +244,7 @@ struct RunsArgs {
     const DevTrace *tr;
     const DevKeyBuf *bufs;
     const DevRunTrace *traces;
-    uint32_t *table, *id, *start, *weak, *first;
+    uint32_t *table, *id, *start, *weak, *cuts, *first;
     RunReq *req;
     int32_t *tflag;        // per analysed trace: left to the general kernel
     int32_t *bflag;        // per key buffer: [2 b] no table, [2 b + 1] cuts were added

@@ -99,6 +99,90 @@ constexpr int32_t runs_lds_bytes(int policy, RunWindows w, int64_t n_prefix) {
     return (int32_t)(4 * (kRunsScratch + words + bits));
 }
 
+// ------------------------------------------------------------ analysis
+// What is known of a key buffer when its requests are cut into pieces.
+struct RunsBuf {
+    const uint32_t *id;       // per position: its id (bit 31 is not part of it)
+    const uint32_t *weak;     // bitmap over ids: weak links
+    uint32_t *cuts;           // bitmap over ids: links cut for the sake of duplicates
+    const uint32_t *start;    // bitmap over positions: a request starts here
+    uint32_t *piece;          // per position: two words (RunPiece)
+};
+constexpr uint32_t kRunsResolved = 0x80000000u;    // id[pos] holds the id, not yet the table slot
+struct RunsListed {
+    uint32_t np, nn;          // pieces; blocks that are no duplicates
+    bool cut;                 // added a cut
+    bool left;                // not for this form
+};
+// The pieces of the request of nf blocks at position ko, by one wavefront;
+// `s`: 128 words of LDS.
+//
+// Where pieces with the same first id differ in length (a document in full
+// and its beginning), the longer one is cut where the shorter ends, or it
+// could not be told which of its blocks are duplicates.  The first pass finds
+// these cuts and the second (kAgain), where there are any, lists every request
+// again.  The second adds none and needs none: the first reads `weak`, which
+// nobody writes meanwhile, so all of its lists follow from the same links.  A
+// block at a new cut has no weak link, so every request that holds it got to
+// it through the piece that was cut; so the pieces that begin there are ends
+// of pieces with one first id, each cut wherever another of them ends.
+template <class W, bool kAgain>
+PC_RUNS_FN RunsListed list_request(W &wv, const RunsBuf &B, uint32_t ko, uint32_t nf, typename W::Lds s) {
+    using vu = typename W::vu;
+    using vb = typename W::vb;
+    const vu lane = wv.lane(), zu = wv.vu0(0);
+    RunsListed R{0u, nf, false, false};
+    for (uint32_t j0 = 0; j0 < nf; j0 += 64) {
+        const vu j = lane + j0;
+        const vb in = j < nf;
+        const vu x = W::gld(in, B.id, j + ko) & ~kRunsResolved;
+        vu links = W::gld(in, B.weak, x >> 5);
+        if (kAgain) links = links | W::gld(in, B.cuts, x >> 5);
+        const vb cut = in & W::bit(links, x);
+        const uint64_t m = W::ballot(cut);
+        const vu k = W::mbcnt(m) + R.np;
+        const vb keep = cut & (k < 64u);
+        W::st(keep, s, k, x);
+        W::st(keep, s, k + 64u, j);
+        R.np += (uint32_t)W::popc(m);
+    }
+    W::sync();
+    if (R.np > kRunsMaxPieces) return R;
+    const vb in = lane < R.np;
+    const vu pid = W::ld_if(in, s, lane), dep = W::ld_if(in, s, lane + 64u);
+    const vu end = W::sel(lane + 1u < R.np, W::next_lane(dep), wv.vu0(nf));
+    const vu len = W::sel(in, end - dep, zu);
+    vb dup = lane < 0u;
+    for (uint32_t i = 0; i + 1 < R.np; ++i) {
+        const uint32_t a = W::rdl(pid, (int)i), la = W::rdl(len, (int)i);
+        const vb same = in & (lane > i) & (pid == a);
+        dup = dup | same;
+        const vb differ = same & (len != la);
+        if (W::ballot(differ) == 0) continue;
+        if (kAgain) {      // cannot happen, see above
+            R.left = true;
+            return R;
+        }
+        W::gor_bit(differ, B.cuts, W::vmin(len, wv.vu0(la)) + a);
+        R.cut = true;
+    }
+    // the pieces are kept at the request's own key positions; another
+    // trace's request may start among them when traces overlap
+    const vu at = lane + ko;
+    const vb behind = in & (lane > 0u);
+    if (W::ballot(behind & W::bit(W::gld(behind, B.start, at >> 5), at)) != 0) {
+        R.left = true;
+        return R;
+    }
+    const vu own = W::sel(dup, zu, len);
+    const vu upto = W::scan(own), before = upto - own;
+    R.nn = W::rdl(upto, 63);
+    W::gst2(in, B.piece, at, pid,
+            W::vmin(len, wv.vu0(kPieceLen)) | W::sel(dup, wv.vu0(kPieceDup), zu) |
+                (W::vmin(before, wv.vu0(0xFFFFu)) << 16));
+    return R;
+}
+
 // Replay parameters of one instance (uniform).
 struct RunParams {
     int32_t C, G, K, flags;

@@ -8,7 +8,7 @@
 //                 and each prefix's first request
 //   runs_link     ids of all positions; weak links
 //   runs_list     per request: its pieces, duplicates among them, RunReq
-//   runs_relist   the same again where duplicates added cuts (rare)
+//   runs_list     again (kAgain) where duplicates added cuts (rare)
 // Bound: runs_insert and runs_link make one random table access per key; the
 // rest streams.  16 one-touch traces (800,000 requests, 120 M keys): insert
 // 5.0 ms, link 2.0, list 0.6, fill 0.15; 64 traces of conversations: insert
@@ -114,9 +114,6 @@ struct DevWave {
     DEV static uint32_t mbcnt(uint64_t m) {
         return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
     }
-    DEV static uint32_t prev_lane(uint32_t v) {    // lane i: the value of lane i - 1
-        return (uint32_t)__builtin_amdgcn_ds_bpermute((int)(((uint32_t)__lane_id() - 1u) << 2), (int)v);
-    }
     DEV static uint32_t setlane(uint32_t v, int l, uint32_t x) {
         return pc_writelane(x, (uint32_t)l, v);
     }
@@ -124,6 +121,15 @@ struct DevWave {
     DEV static uint32_t next_lane(uint32_t v) {    // lane i: the value of lane i + 1
         return (uint32_t)__builtin_amdgcn_ds_bpermute((int)(((uint32_t)__lane_id() + 1u) << 2), (int)v);
     }
+    // device memory, lanes m; gor_bit: one bit of a bitmap
+    DEV static uint32_t gld(bool m, const uint32_t *p, uint32_t at) { return m ? p[at] : 0u; }
+    DEV static void gst2(bool m, uint32_t *p, uint32_t at, uint32_t x, uint32_t y) {
+        if (m) ((uint2 *)p)[at] = make_uint2(x, y);
+    }
+    DEV static void gor_bit(bool m, uint32_t *p, uint32_t i) {
+        if (m) atomicOr(p + (i >> 5), 1u << (i & 31));
+    }
+    DEV static bool bit(uint32_t w, uint32_t i) { return (w >> (i & 31)) & 1u; }
     DEV static int64_t widen(uint32_t v) { return (int64_t)(uint64_t)v; }
     DEV static int64_t mul_shr16(int64_t a, int64_t w) {      // a, w >= 0 in the lanes that use it
         const uint64_t x = (uint64_t)a, y = (uint64_t)w;
@@ -170,7 +176,6 @@ constexpr int kT = 256;
 // (its traces are left to the general kernel): at load 1/2 only keys made to
 // collide get there.
 constexpr uint32_t kMaxProbe = 2048;
-constexpr uint32_t kResolved = 0x80000000u;    // id[pos] holds the id, not yet the table slot
 
 __global__ __launch_bounds__(kT) void runs_fill(uint4 *ones, int64_t n_ones, uint4 *zeros, int64_t n_zeros) {
     const int64_t i0 = (int64_t)blockIdx.x * kT + threadIdx.x, step = (int64_t)gridDim.x * kT;
@@ -264,10 +269,10 @@ __global__ __launch_bounds__(kT) void runs_link(RunsArgs A) {
     uint32_t before = (uint32_t)__shfl_up((int)x, 1);
     if ((threadIdx.x & 63) == 0 && in && pos > 0) {
         const uint32_t s = __hip_atomic_load(id + pos - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        before = (s & kResolved) ? s & ~kResolved : tab[s];
+        before = (s & kRunsResolved) ? s & ~kRunsResolved : tab[s];
     }
     if (!in) return;
-    __hip_atomic_store(id + pos, x | kResolved, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(id + pos, x | kRunsResolved, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const bool st = (A.start[B.bits0 + (pos >> 5)] >> (pos & 31)) & 1u;
     if (pos == 0 || st || before + 1u != x) atomicOr(A.weak + B.bits0 + (x >> 5), 1u << (x & 31));
 }
@@ -275,7 +280,7 @@ __global__ __launch_bounds__(kT) void runs_link(RunsArgs A) {
 // One wavefront per request.  kAgain: only where a first pass added cuts.
 template <bool kAgain>
 __global__ __launch_bounds__(kT) void runs_list(RunsArgs A) {
-    __shared__ uint32_t s_id[kT / 64][64], s_dep[kT / 64][64];
+    __shared__ uint32_t s_list[kT / 64][128];
     const int32_t ti = find_block(A.traces, A.n_traces, blockIdx.x, &DevRunTrace::blk1);
     const DevRunTrace &R = A.traces[ti];
     const DevKeyBuf &B = A.bufs[R.buf];
@@ -288,73 +293,30 @@ __global__ __launch_bounds__(kT) void runs_list(RunsArgs A) {
     if (r >= T.n_req) return;
     int64_t ko, nf;
     request_ok(T, r, ko, nf);          // (valid: the flag above is clear)
-    const uint32_t *id = A.id + B.id0;
-    const uint32_t *weak = A.weak + B.bits0;
-    uint32_t np = 0;
-    for (int64_t j0 = 0; j0 < nf; j0 += 64) {
-        const int64_t j = j0 + lane;
-        uint32_t x = 0;
-        bool cut = false;
-        if (j < nf) {
-            x = id[ko + j] & ~kResolved;
-            cut = (weak[x >> 5] >> (x & 31)) & 1u;
-        }
-        const uint64_t m = __ballot(cut);
-        const uint32_t k = np + DevWave::mbcnt(m);
-        if (cut && k < 64u) {
-            s_id[w][k] = x;
-            s_dep[w][k] = (uint32_t)j;
-        }
-        np += (uint32_t)__popcll(m);
+    RunsBuf V;
+    V.id = A.id + B.id0;
+    V.weak = A.weak + B.bits0;
+    V.cuts = A.cuts + B.bits0;
+    V.start = A.start + B.bits0;
+    V.piece = A.table + B.tab0;
+    DevWave wv;
+    const RunsListed L = list_request<DevWave, kAgain>(wv, V, (uint32_t)ko, (uint32_t)nf,
+                                                       (LDS_AS uint32_t *)s_list[w]);
+    if (L.left) {
+        if (lane == 0) A.tflag[ti] = 1;
+        return;
     }
-    DevWave::sync();
-    uint32_t pid = 0, dep = 0, nn = (uint32_t)nf;
-    if (np <= 64u) {
-        const bool in = lane < np;
-        if (in) { pid = s_id[w][lane]; dep = s_dep[w][lane]; }
-        bool dup = false;
-        const uint32_t nx = DevWave::next_lane(dep);
-        const uint32_t len = in ? (lane + 1u < np ? nx : (uint32_t)nf) - dep : 0u;
-        if (np > 1u) {
-            for (uint32_t i = 0; i + 1 < np; ++i) {
-                const uint32_t a = DevWave::rdl(pid, (int)i), la = DevWave::rdl(len, (int)i);
-                const bool same = in && lane > i && pid == a;
-                dup = dup || same;
-                if (!kAgain && same && len != la) {     // cut where the shorter of the two ends
-                    const uint32_t c = a + (len < la ? len : la);
-                    atomicOr(A.weak + B.bits0 + (c >> 5), 1u << (c & 31));
-                    A.bflag[2 * R.buf + 1] = 1;
-                }
-            }
-        }
-        // the pieces are kept at the request's own key positions; another
-        // trace's request may start among them when traces overlap
-        const bool clash = in && lane > 0 && ((A.start[B.bits0 + ((ko + lane) >> 5)] >> ((ko + lane) & 31)) & 1u);
-        if (__ballot(clash)) {
-            if (lane == 0) A.tflag[ti] = 1;
-            return;
-        }
-        const uint32_t own = dup ? 0u : len;
-        const uint32_t upto = DevWave::scan(own), before = upto - own;
-        nn = DevWave::rdl(upto, 63);
-        if (in) {
-            RunPiece p;
-            p.id = pid;
-            p.len = (len < kPieceLen ? len : kPieceLen) | (dup ? kPieceDup : 0u) |
-                    (before < 0xFFFFu ? before : 0xFFFFu) << 16;
-            ((RunPiece *)(A.table + B.tab0))[ko + lane] = p;
-        }
-    }
+    if (L.cut && lane == 0) A.bflag[2 * R.buf + 1] = 1;
     if (lane == 0) {
         RunReq q;
         q.n_full = (uint32_t)nf;
         q.prefix = T.prefix[r];
         q.info = (uint32_t)T.group[r] | ((uint32_t)T.contract[r] << 8) |
                  (A.first[R.first0 + q.prefix] < (uint32_t)r ? 1u << 16 : 0u) |
-                 (np <= kRunsMaxPieces ? np : 255u) << 24;
+                 (L.np <= kRunsMaxPieces ? L.np : 255u) << 24;
         q.dt = T.tick ? (uint32_t)(T.tick[r] - (r > 0 ? T.tick[r - 1] : 0)) : r > 0 ? 1u : 0u;
-        q.ko = np > 0 ? (uint32_t)ko : 0u;
-        q.nn = nn;
+        q.ko = L.np > 0 ? (uint32_t)ko : 0u;
+        q.nn = L.nn;
         q.pad[0] = q.pad[1] = 0u;
         A.req[R.req0 + r] = q;
     }

@@ -1,9 +1,12 @@
-// runs_host.cpp -- the run-based replay (csrc/pc_runs.h) on the CPU: the
-// wavefront is a structure of 64 lanes, LDS an array with bounds checks, and
-// the trace analysis a plain map.  Built and driven by test_runs_cpu.py.
+// runs_host.cpp -- the run-based replay and the listing of requests
+// (csrc/pc_runs.h) on the CPU: the wavefront is a structure of 64 lanes, LDS
+// and device memory are arrays with bounds checks; ids and weak links come
+// from a plain map.  Built and driven by test_runs_cpu.py.
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
+#include <functional>
+#include <random>
 #include <type_traits>
 #include <unordered_map>
 #include <vector>
@@ -62,6 +65,20 @@ int64_t g_lds_words;
 }
 void check(const uint32_t *p) {
     if (p < g_lds || p >= g_lds + g_lds_words) die("LDS access out of range");
+}
+
+// Device memory of the analysis; a read of `before` runs the hook first.
+struct Region {
+    const uint32_t *p;
+    size_t n;
+};
+std::vector<Region> g_mem;
+std::function<void()> g_hook;
+const uint32_t *g_hook_at;
+void check_mem(const uint32_t *p, size_t words = 1) {
+    for (const Region &r : g_mem)
+        if (p >= r.p && p + words <= r.p + r.n) return;
+    die("device memory access out of range");
 }
 
 struct HostWave {
@@ -196,6 +213,40 @@ struct HostWave {
             if (x > 1) die("mad01 factor");
         return zip(a, c, [b](uint32_t x, uint32_t z) { return x * b + z; });
     }
+    static vu next_lane(const vu &a) {
+        vu r;
+        for (int i = 0; i < kLanes; ++i) r.v[i] = a.v[(i + 1) % kLanes];
+        return r;
+    }
+    static vu gld(const vb &m, const uint32_t *p, const vu &at) {
+        if (p == g_hook_at && g_hook) g_hook();
+        vu r = splat<uint32_t>(0);
+        for (int i = 0; i < kLanes; ++i)
+            if (m.v[i]) {
+                check_mem(p + at.v[i]);
+                r.v[i] = p[at.v[i]];
+            }
+        return r;
+    }
+    static void gst2(const vb &m, uint32_t *p, const vu &at, const vu &x, const vu &y) {
+        for (int i = 0; i < kLanes; ++i)
+            if (m.v[i]) {
+                uint32_t *q = p + 2 * (size_t)at.v[i];
+                check_mem(q, 2);
+                q[0] = x.v[i];
+                q[1] = y.v[i];
+            }
+    }
+    static void gor_bit(const vb &m, uint32_t *p, const vu &i) {
+        for (int k = 0; k < kLanes; ++k)
+            if (m.v[k]) {
+                check_mem(p + (i.v[k] >> 5));
+                p[i.v[k] >> 5] |= 1u << (i.v[k] & 31);
+            }
+    }
+    static vb bit(const vu &w, const vu &i) {
+        return zip(w, i, [](uint32_t x, uint32_t k) { return ((x >> (k & 31)) & 1u) != 0; });
+    }
     static uint32_t keep(uint32_t x) { return x; }
     static vl mad64(const vu &a, int32_t b, const vl &c) {
         return zip(a, c, [b](uint32_t x, int64_t z) { return (int64_t)x * b + z; });
@@ -209,59 +260,103 @@ struct HostWave {
 
 namespace {
 
-// Trace analysis on the host: ids, cuts, pieces (see pc_runs.h).
+// A trace on the key buffer (group to tick: of the one that is replayed).
+struct TraceIn {
+    const int64_t *off;
+    int64_t n_req;
+    const uint8_t *group, *contract;
+    const uint32_t *prefix;
+    const int64_t *tick;
+};
 struct Analysis {
-    std::vector<uint32_t> id;
-    std::vector<uint8_t> weak;
-    std::vector<pcr::RunReq> req;
+    std::vector<uint32_t> id, start, weak, cuts;
     std::vector<pcr::RunPiece> piece;
+    std::vector<pcr::RunReq> req;      // of the trace that is replayed
+    bool left = false;                 // it is not for this form
 };
 
-Analysis analyse(const uint64_t *keys, const int64_t *off, const uint8_t *group, const uint8_t *contract,
-                 const uint32_t *prefix, const int64_t *tick, int64_t n_req) {
+// Analysis of a key buffer that `ts` read, their requests listed in this
+// order; ts[main] is replayed.  With `interleave` (a seed) the first pass lists
+// another request ahead of every step of 64 blocks of one, as other wavefronts
+// may at any time.
+Analysis analyse(const uint64_t *keys, int64_t n, const std::vector<TraceIn> &ts, size_t main, int interleave) {
     Analysis A;
-    const int64_t n = n_req ? off[n_req] : 0;
+    const size_t words = (size_t)(n + 31) / 32;
     A.id.resize(n);
-    A.weak.assign(n, 0);
+    A.start.assign(words, 0);
+    A.weak.assign(words, 0);
+    A.cuts.assign(words, 0);
     A.piece.resize(n);
+    auto bit = [](const std::vector<uint32_t> &b, int64_t i) { return (b[i >> 5] >> (i & 31)) & 1u; };
     std::unordered_map<uint64_t, uint32_t> first;
     for (int64_t i = 0; i < n; ++i) A.id[i] = first.emplace(keys[i], (uint32_t)i).first->second;
-    for (int64_t r = 0; r < n_req; ++r)
-        for (int64_t i = off[r]; i < off[r + 1]; ++i)
-            if (i == off[r] || A.id[i - 1] + 1 != A.id[i]) A.weak[A.id[i]] = 1;
-    auto pieces = [&](int64_t r) {
-        std::vector<std::pair<uint32_t, uint32_t>> p;    // id, depth
-        for (int64_t i = off[r]; i < off[r + 1]; ++i)
-            if (A.weak[A.id[i]]) p.push_back({A.id[i], (uint32_t)(i - off[r])});
-        return p;
+    for (const TraceIn &t : ts)
+        for (int64_t r = 0; r < t.n_req; ++r)
+            if (t.off[r + 1] > t.off[r]) A.start[t.off[r] >> 5] |= 1u << (t.off[r] & 31);
+    for (int64_t i = 0; i < n; ++i)
+        if (i == 0 || bit(A.start, i) || A.id[i - 1] + 1 != A.id[i]) A.weak[A.id[i] >> 5] |= 1u << (A.id[i] & 31);
+    for (uint32_t &x : A.id) x |= pcr::kRunsResolved;
+
+    pcr::RunsBuf B;
+    B.id = A.id.data();
+    B.weak = A.weak.data();
+    B.cuts = A.cuts.data();
+    B.start = A.start.data();
+    B.piece = (uint32_t *)A.piece.data();
+    g_mem = {{B.id, A.id.size()}, {B.weak, words}, {B.cuts, words}, {B.start, words}, {B.piece, 2 * A.piece.size()}};
+    HostWave wv;
+    bool cut = false;
+    std::vector<uint8_t> left(ts.size(), 0);
+    auto list = [&](auto again, size_t t, int64_t r) {
+        uint32_t lds[128];
+        uint32_t *const outer = g_lds;
+        const int64_t outer_words = g_lds_words;
+        g_lds = lds;
+        g_lds_words = 128;
+        const auto L = pcr::list_request<HostWave, decltype(again)::value>(
+            wv, B, (uint32_t)ts[t].off[r], (uint32_t)(ts[t].off[r + 1] - ts[t].off[r]), lds);
+        g_lds = outer;
+        g_lds_words = outer_words;
+        cut = cut || L.cut;
+        if (L.left) left[t] = 1;
+        return L;
     };
-    for (int64_t r = 0; r < n_req; ++r) {                // cuts where one of two equal starts ends
-        const auto p = pieces(r);
-        const uint32_t nf = (uint32_t)(off[r + 1] - off[r]);
-        auto len = [&](size_t i) { return (i + 1 < p.size() ? p[i + 1].second : nf) - p[i].second; };
-        for (size_t a = 0; a < p.size(); ++a)
-            for (size_t b = 0; b < a; ++b)
-                if (p[a].first == p[b].first && len(a) != len(b))
-                    A.weak[p[a].first + (len(a) < len(b) ? len(a) : len(b))] = 1;
-    }
+    // every request once; the hook lists one that has not begun yet
+    std::vector<std::pair<size_t, int64_t>> todo;
+    for (size_t t = ts.size(); t-- > 0;)
+        for (int64_t r = ts[t].n_req; r-- > 0;) todo.push_back({t, r});
+    std::mt19937 rng(interleave);
+    auto list_one = [&](size_t k) {
+        const auto q = todo[k];
+        todo.erase(todo.begin() + (int64_t)k);
+        list(std::false_type(), q.first, q.second);
+    };
+    bool nested = false;
+    g_hook_at = B.weak;
+    if (interleave)
+        g_hook = [&] {
+            if (nested || todo.empty()) return;
+            nested = true;
+            list_one(rng() % todo.size());
+            nested = false;
+        };
+    while (!todo.empty()) list_one(todo.size() - 1);
+    g_hook = nullptr;
     std::unordered_map<uint32_t, int> seen;
-    for (int64_t r = 0; r < n_req; ++r) {
-        const auto p = pieces(r);
-        const uint32_t nf = (uint32_t)(off[r + 1] - off[r]);
-        uint32_t nn = 0;
-        for (size_t a = 0; a < p.size(); ++a) {
-            bool dup = false;
-            for (size_t b = 0; b < a; ++b) dup = dup || p[a].first == p[b].first;
-            const uint32_t len = (a + 1 < p.size() ? p[a + 1].second : nf) - p[a].second;
-            A.piece[off[r] + a] = {p[a].first, (len < pcr::kPieceLen ? len : pcr::kPieceLen) |
-                                                   (dup ? pcr::kPieceDup : 0u) | (nn < 0xFFFFu ? nn : 0xFFFFu) << 16};
-            if (!dup) nn += len;
-        }
-        const bool before = !seen.emplace(prefix[r], 1).second;
-        const uint32_t np = p.size() <= pcr::kRunsMaxPieces ? (uint32_t)p.size() : 255u;
-        A.req.push_back({nf, group[r] | ((uint32_t)contract[r] << 8) | (before ? 1u << 16 : 0u) | np << 24, prefix[r],
-                         (uint32_t)(tick ? tick[r] - (r ? tick[r - 1] : 0) : r ? 1 : 0), (uint32_t)off[r], nn, {}});
-    }
+    for (int pass = cut ? 1 : 0; pass >= 0; --pass)      // (without cuts the same lists again)
+        for (size_t t = 0; t < ts.size(); ++t)
+            for (int64_t r = 0; r < ts[t].n_req && !left[t]; ++r) {
+                const auto L = cut ? list(std::true_type(), t, r) : list(std::false_type(), t, r);
+                if (pass > 0 || t != main) continue;
+                const TraceIn &T = ts[t];
+                const bool before = !seen.emplace(T.prefix[r], 1).second;
+                A.req.push_back({(uint32_t)(T.off[r + 1] - T.off[r]),
+                                 T.group[r] | ((uint32_t)T.contract[r] << 8) | (before ? 1u << 16 : 0u) |
+                                     (L.np <= pcr::kRunsMaxPieces ? L.np : 255u) << 24,
+                                 T.prefix[r], (uint32_t)(T.tick ? T.tick[r] - (r ? T.tick[r - 1] : 0) : r ? 1 : 0),
+                                 (uint32_t)T.off[r], L.nn, {}});
+            }
+    A.left = left[main] != 0;
     return A;
 }
 
@@ -324,13 +419,20 @@ bool replay_in(const Analysis &A, const pcr::RunParams &P, int64_t n_prefix, int
 }  // namespace
 
 // The oracle's signature; `window` overrides the windows' size (0 and -1: the
-// planner's, the widest).  Returns 1 when the instance is left.
+// planner's, the widest).  The key buffer has n_keys keys; off2 (or null): a
+// second trace that reads it, listed behind the first, or ahead of it
+// (ahead2).  Returns 1 when the instance is left.
 extern "C" int runs_host_replay(const uint64_t *keys, const int64_t *off, const uint8_t *group,
                                 const uint8_t *contract, const uint32_t *prefix, const int64_t *tick, int64_t n_req,
                                 int32_t G, int64_t n_prefix, int32_t policy, int64_t C, int32_t flags, int32_t K,
                                 const int64_t *rho, const int64_t *beta, int64_t eps, int32_t permille,
-                                int32_t move_thr, int32_t window, int64_t *gs, int64_t *is, int32_t *pr) {
-    const Analysis A = analyse(keys, off, group, contract, prefix, tick, n_req);
+                                int32_t move_thr, int32_t window, int64_t n_keys, const int64_t *off2,
+                                int64_t n_req2, int32_t ahead2, int32_t interleave, int64_t *gs, int64_t *is,
+                                int32_t *pr) {
+    std::vector<TraceIn> ts{{off, n_req, group, contract, prefix, tick}};
+    if (off2) ts.insert(ahead2 ? ts.begin() : ts.end(), {off2, n_req2, nullptr, nullptr, nullptr, nullptr});
+    const Analysis A = analyse(keys, n_keys, ts, off2 && ahead2 ? 1 : 0, interleave);
+    if (A.left) return 1;
     pcr::RunParams P{};
     P.C = (int32_t)C;
     P.G = G;

@@ -12,7 +12,7 @@ import paper_2608_01657_amd as P
 from gpu_util import POLICIES, assert_same, run_key_traces
 from paper_2608_01657_amd import device as dv
 from paper_2608_01657_amd import tracegen as tg
-from test_runs_cpu import chunk_trace
+from test_runs_cpu import chunk_trace, partial_repeats
 
 pytestmark = pytest.mark.gpu
 
@@ -34,6 +34,12 @@ def _trace(reqs, n_groups=3, seed=0):
 @pytest.mark.parametrize("seed", range(3))
 def test_unchained_documents_and_duplicates(seed):
     run_key_traces([chunk_trace(seed, n_req=700)], [_insts((25, 300, 3000))])
+
+
+@pytest.mark.parametrize("seed", range(3))
+def test_partial_repeats_far_apart_in_a_request(seed):
+    """Every request adds cuts to documents that other wavefronts are listing."""
+    run_key_traces([partial_repeats(seed, n_req=3000, docs=1500)], [_insts((60, 700, 4096))])
 
 
 @pytest.mark.parametrize("n_req", [1, 15, 16, 17, 63, 64, 65])

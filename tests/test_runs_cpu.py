@@ -28,7 +28,7 @@ def host(tmp_path_factory):
     L = ctypes.CDLL(so)
     L.runs_host_replay.restype = ctypes.c_int
     L.runs_host_replay.argtypes = [P, P, P, P, P, P, i64, i32, i64, i32, i64, i32, i32, P, P, i64, i32, i32, i32,
-                                   P, P, P]
+                                   i64, P, i64, i32, i32, P, P, P]
     return L
 
 
@@ -36,8 +36,10 @@ def _ptr(a):
     return None if a is None else a.ctypes.data_as(P)
 
 
-def run_host(L, kt, inst, window=0):
-    """(groups, inst, per_request), or None when left to the general kernel."""
+def run_host(L, kt, inst, window=0, other=None, ahead=0, interleave=0):
+    """(groups, inst, per_request), or None when left to the general kernel.
+    other: key offsets of a second trace on the same key buffer, analysed
+    behind this one or ahead of it."""
     a = [np.ascontiguousarray(x, t) for x, t in ((kt.keys if kt.keys.size else np.zeros(1), np.uint64),
                                                  (kt.key_off, np.int64), (kt.group, np.uint8),
                                                  (kt.contract, np.uint8), (kt.prefix, np.uint32))]
@@ -45,20 +47,22 @@ def run_host(L, kt, inst, window=0):
     rho = np.array([c[0] for c in inst.contracts], np.int64)
     beta = np.array([c[1] for c in inst.contracts], np.int64)
     R = kt.n_req
+    off2 = None if other is None else np.ascontiguousarray(other, np.int64)
     gs = np.zeros((kt.n_groups, len(GROUP_FIELDS)), np.int64)
     st = np.zeros(len(INST_FIELDS), np.int64)
     pr = np.zeros((R, 4), np.int32)
     rc = L.runs_host_replay(*map(_ptr, a), _ptr(tick), R, kt.n_groups, kt.n_prefix, inst.policy, inst.capacity,
                             inst.flags, len(inst.contracts), _ptr(rho), _ptr(beta), inst.eps_q16,
-                            inst.s3_small_permille, inst.s3_move_threshold, window, _ptr(gs), _ptr(st), _ptr(pr))
+                            inst.s3_small_permille, inst.s3_move_threshold, window, kt.keys.size, _ptr(off2),
+                            0 if other is None else len(other) - 1, ahead, interleave, _ptr(gs), _ptr(st), _ptr(pr))
     if rc:
         return None
     return [dict(zip(GROUP_FIELDS, map(int, row))) for row in gs], dict(zip(INST_FIELDS, map(int, st))), pr
 
 
-def compare(L, kt, inst, window=0, label=""):
+def compare(L, kt, inst, window=0, label="", **shared):
     """1 if the instance finished, equal to the oracle's; 0 if it was left."""
-    got = run_host(L, kt, inst, window)
+    got = run_host(L, kt, inst, window, **shared)
     if got is None:
         return 0
     o = oracle.replay_key_trace(kt, inst, per_request=True)
@@ -189,3 +193,31 @@ def test_widest_windows(host):
     for pol in POLICIES:
         assert compare(host, kt, tg.Instance(0, pol, 6000 if pol == tg.POLICY_STATICQUOTA else 2500)) == 0
         assert compare(host, kt, tg.Instance(0, pol, 2500), -1) == 1
+
+
+def partial_repeats(seed, n_req=120, docs=60):
+    """Requests that hold a document's beginning and, more than 64 blocks of
+    their own later, the whole document (or the other way round).  Few of
+    them share a document, so that a cut that one misses is missed."""
+    rng = np.random.default_rng(seed)
+    reqs = []
+    for r in range(n_req):
+        d = 1000 * (1 + r % docs)
+        parts = [np.arange(d, d + int(rng.integers(1, 11))), np.arange(d, d + 10)]
+        own = 100_000 + 500 * r + np.arange(int(rng.integers(60, 140)))
+        a, b = parts if rng.random() < 0.7 else parts[::-1]
+        reqs.append(np.concatenate([a, own, b]))
+    group = rng.integers(0, 3, n_req)
+    return tg.KeyTrace(np.concatenate(reqs).astype(np.uint64) * np.uint64(0x9E3779B97F4A7C15),
+                       np.cumsum([0] + [len(x) for x in reqs]).astype(np.int64), group.astype(np.uint8),
+                       np.zeros(n_req, np.uint8), group.astype(np.uint32), 3, 3)
+
+
+@pytest.mark.parametrize("interleave", [0, 1, 2, 3])
+def test_partial_repeats_while_other_requests_add_cuts(host, interleave):
+    """Cuts that other wavefronts add between two steps of a request's listing
+    change nothing in it."""
+    kt = partial_repeats(interleave)
+    for pol in POLICIES:
+        for cap in (60, 700):
+            assert compare(host, kt, tg.Instance(0, pol, cap), 0, "repeats", interleave=interleave) == 1
