@@ -105,10 +105,21 @@ struct RunsBuf {
     const uint32_t *id;       // per position: its id (bit 31 is not part of it)
     const uint32_t *weak;     // bitmap over ids: weak links
     uint32_t *cuts;           // bitmap over ids: links cut for the sake of duplicates
-    const uint32_t *start;    // bitmap over positions: a request starts here
+    const uint32_t *start;    // bitmap over positions: request_marks
     uint32_t *piece;          // per position: two words (RunPiece)
 };
 constexpr uint32_t kRunsResolved = 0x80000000u;    // id[pos] holds the id, not yet the table slot
+// Positions whose link is weak for the sake of a request of nf blocks at ko:
+// where it starts, and where it ends if it is its trace's last (any other ends
+// where the next one starts).  Two traces may cut one key buffer differently
+// and keep their pieces in one array; since ends are marked too, requests
+// that start at the same position have the same pieces up to where the shorter
+// ends.
+template <class F>
+PC_RUNS_FN void request_marks(int64_t ko, int64_t nf, bool last, int64_t n_keys, F mark) {
+    if (nf > 0) mark(ko);
+    if (last && ko + nf < n_keys) mark(ko + nf);
+}
 struct RunsListed {
     uint32_t np, nn;          // pieces; blocks that are no duplicates
     bool cut;                 // added a cut
@@ -166,8 +177,9 @@ PC_RUNS_FN RunsListed list_request(W &wv, const RunsBuf &B, uint32_t ko, uint32_
         W::gor_bit(differ, B.cuts, W::vmin(len, wv.vu0(la)) + a);
         R.cut = true;
     }
-    // the pieces are kept at the request's own key positions; another
-    // trace's request may start among them when traces overlap
+    // the pieces are kept at the request's own key positions; another trace's
+    // request may start (or end) among them when traces overlap.  One that
+    // starts at ko itself writes the same pieces there.
     const vu at = lane + ko;
     const vb behind = in & (lane > 0u);
     if (W::ballot(behind & W::bit(W::gld(behind, B.start, at >> 5), at)) != 0) {

@@ -228,7 +228,9 @@ __global__ __launch_bounds__(kT) void runs_insert(RunsArgs A) {
             A.tflag[ti] = 1;
             return;
         }
-        if (nf > 0) atomicOr(A.start + A.bufs[R.buf].bits0 + (ko >> 5), 1u << (ko & 31));
+        uint32_t *marks = A.start + A.bufs[R.buf].bits0;
+        request_marks(ko, nf, r + 1 == T.n_req, T.n_keys,
+                      [&](int64_t at) { atomicOr(marks + (at >> 5), 1u << (at & 31)); });
         atomicMin(A.first + R.first0 + T.prefix[r], (uint32_t)r);
         return;
     }

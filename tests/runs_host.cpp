@@ -292,7 +292,8 @@ Analysis analyse(const uint64_t *keys, int64_t n, const std::vector<TraceIn> &ts
     for (int64_t i = 0; i < n; ++i) A.id[i] = first.emplace(keys[i], (uint32_t)i).first->second;
     for (const TraceIn &t : ts)
         for (int64_t r = 0; r < t.n_req; ++r)
-            if (t.off[r + 1] > t.off[r]) A.start[t.off[r] >> 5] |= 1u << (t.off[r] & 31);
+            pcr::request_marks(t.off[r], t.off[r + 1] - t.off[r], r + 1 == t.n_req, n,
+                               [&](int64_t at) { A.start[at >> 5] |= 1u << (at & 31); });
     for (int64_t i = 0; i < n; ++i)
         if (i == 0 || bit(A.start, i) || A.id[i - 1] + 1 != A.id[i]) A.weak[A.id[i] >> 5] |= 1u << (A.id[i] & 31);
     for (uint32_t &x : A.id) x |= pcr::kRunsResolved;

@@ -12,7 +12,7 @@ import paper_2608_01657_amd as P
 from gpu_util import POLICIES, assert_same, run_key_traces
 from paper_2608_01657_amd import device as dv
 from paper_2608_01657_amd import tracegen as tg
-from test_runs_cpu import chunk_trace, partial_repeats
+from test_runs_cpu import chunk_trace, ends_inside, partial_repeats, random_cuts
 
 pytestmark = pytest.mark.gpu
 
@@ -108,6 +108,25 @@ def test_traces_that_share_and_overlap_in_one_key_buffer():
         pr = b.per_request_arrays()
         for k, (res, x) in enumerate(zip(b.results(), insts)):
             w = oracle.replay_key_trace(ks[x.trace], x, per_request=True)
+            assert_same(res, w, f"instance {k}")
+            assert np.array_equal(pr[k], w.per_request)
+
+
+@pytest.mark.parametrize("order", [(0, 1), (1, 0)])
+def test_equal_starts_with_different_ends(order):
+    """The last request of a trace ends inside another trace's request that
+    starts where it does; and random cuts of one key buffer."""
+    for kts in ends_inside(), random_cuts(0), random_cuts(1):
+        dts = [dv.upload_keys(k) for k in kts]
+        for d in dts:
+            d.keys = dts[0].keys
+        kts, dts = [kts[i] for i in order], [dts[i] for i in order]
+        insts = [tg.Instance(t, p, c) for t in range(2) for p in POLICIES for c in (7, 64, 300)]
+        b = dv.ReplayBatch(dts, insts, per_request=True)
+        b.launch()
+        pr = b.per_request_arrays()
+        for k, (res, x) in enumerate(zip(b.results(), insts)):
+            w = oracle.replay_key_trace(kts[x.trace], x, per_request=True)
             assert_same(res, w, f"instance {k}")
             assert np.array_equal(pr[k], w.per_request)
 

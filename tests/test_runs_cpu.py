@@ -221,3 +221,44 @@ def test_partial_repeats_while_other_requests_add_cuts(host, interleave):
     for pol in POLICIES:
         for cap in (60, 700):
             assert compare(host, kt, tg.Instance(0, pol, cap), 0, "repeats", interleave=interleave) == 1
+
+
+def _on_keys(keys, off):
+    n = len(off) - 1
+    g = np.arange(n) % 3
+    return tg.KeyTrace(keys, np.asarray(off, np.int64), g.astype(np.uint8), np.zeros(n, np.uint8),
+                       g.astype(np.uint32), 3, 3)
+
+
+def ends_inside():
+    """Two traces of 20 requests on one key buffer, the same ten keys again and
+    again; the last request of the second one ends half way."""
+    keys = np.tile(np.arange(1, 11), 20).astype(np.uint64)
+    off = 10 * np.arange(21)
+    return _on_keys(keys, off), _on_keys(keys, np.concatenate([off[:-1], [195]]))
+
+
+def random_cuts(seed):
+    """Two traces on one key buffer of repeated documents, cut at random (some
+    starts in common); the last request of the second starts where one of the
+    first does."""
+    rng = np.random.default_rng(seed)
+    keys = np.concatenate([1000 * d + np.arange(1, 25) for d in rng.integers(0, 9, 90)]).astype(np.uint64)
+    off, other = (np.unique(np.concatenate([[0], 12 * rng.integers(0, 178, n)])) for n in (50, 40))
+    k = int(rng.choice(np.flatnonzero(np.isin(other, off))[1:]))
+    return _on_keys(keys, off), _on_keys(keys, np.concatenate([other[:k + 1], [other[k] + rng.integers(1, 30)]]))
+
+
+@pytest.mark.parametrize("ahead", [0, 1])
+def test_equal_starts_with_different_ends(host, ahead):
+    """Requests of two traces that start at one position and end at different
+    ones keep their pieces in the same place: whichever is listed last, an
+    instance of either is exact."""
+    done = n = 0
+    for pair in [ends_inside()] + [random_cuts(s) for s in range(12)]:
+        for kt, other in (pair, pair[::-1]):
+            for pol in POLICIES:
+                for cap in (7, 64, 300):
+                    done += compare(host, kt, tg.Instance(0, pol, cap), 0, "shared", other=other.key_off, ahead=ahead)
+                    n += 1
+    assert done >= n // 2
