@@ -145,6 +145,8 @@ constexpr int64_t kRunsMaxKeys = (int64_t)1 << 30, kRunsMaxPrefix = (int64_t)1 <
 constexpr int32_t kRunsMaxBlocks = 1 << 20;
 constexpr int64_t kRunsMinReq = 16;
 constexpr int64_t kRunsMaxBytes = (int64_t)16 << 30;
+// (a launch holds less than 2^32 work items; blocks of the analysis have 256)
+constexpr int64_t kRunsMaxGrid = (((int64_t)1 << 32) - 1) / 256;
 
 // Which traces are analysed for the replay on runs, and the sizes of it.
 void plan_runs(const pc_trace_desc *traces, int32_t n_traces, const pc_instance_desc *inst, int32_t n_inst,
@@ -193,9 +195,10 @@ void plan_runs(const pc_trace_desc *traces, int32_t n_traces, const pc_instance_
         R.trace_run[i] = (int32_t)R.rt.size();
         R.rt.push_back(d);
         bytes = 4 * (R.table_words + R.id_words + 3 * R.bit_words + R.first_words) + 32 * R.n_req;
-        if (bytes > kRunsMaxBytes || nb_pos + nb_req > INT32_MAX || nb_list > INT32_MAX) break;
+        if (bytes > kRunsMaxBytes || nb_pos + nb_req > kRunsMaxGrid || nb_list > kRunsMaxGrid) break;
     }
-    R.on = longest >= kRunsMinReq && bytes <= kRunsMaxBytes && nb_pos + nb_req <= INT32_MAX && nb_list <= INT32_MAX;
+    R.on = longest >= kRunsMinReq && bytes <= kRunsMaxBytes && nb_pos + nb_req <= kRunsMaxGrid &&
+           nb_list <= kRunsMaxGrid;
     R.nb_pos = (uint32_t)nb_pos;
     R.nb_req = (uint32_t)nb_req;
     R.nb_list = (uint32_t)nb_list;

@@ -116,6 +116,21 @@ def test_trace_validation(field, value):
     assert _ws(_trace(**{field: value}), _inst()) == P.PC_EINVAL
 
 
+@pytest.mark.parametrize("n_traces", [1, 4])
+def test_no_analysis_past_the_largest_launch(n_traces):
+    """The analysis lists a request with 64 work items, and a launch holds less
+    than 2^32 of them: from 2^26 requests on, a batch is planned (and replayed)
+    without it."""
+    def size(n_req):
+        t = [_trace(n_req=n_req // n_traces) for _ in range(n_traces)]
+        i = [_inst(trace=k) for k in range(n_traces)]
+        return P.lib().pc_replay_workspace_bytes((P.pc_trace_desc * n_traces)(*t), n_traces,
+                                                 (P.pc_instance_desc * n_traces)(*i), n_traces)
+    below = (1 << 26) - 4 * n_traces
+    assert size(below) > 32 * below
+    assert 0 < size(1 << 26) < 1 << 20
+
+
 def test_replay_rejects_small_or_misaligned_workspace():
     lib = P.lib()
     T = (P.pc_trace_desc * 1)(_trace())
