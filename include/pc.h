@@ -164,8 +164,9 @@ typedef struct {
 
 /* Workspace bytes for this batch (< 0: invalid input, see pc_last_error).
  * They include the trace analysis of the replay on runs: some 12 bytes per
- * key of every distinct key buffer and 32 per request, where that is at most
- * 16 GiB.  pc_replay_batch also takes a workspace that only lacks this part
+ * key of every distinct key buffer, or, where its traces can read only part of
+ * it, per key that they can (n_req * max_req_blocks); and 32 per request; where
+ * that is at most 16 GiB.  pc_replay_batch also takes a workspace that only lacks this part
  * and then replays with the general kernels alone. */
 int64_t pc_replay_workspace_bytes(const pc_trace_desc *traces, int32_t n_traces,
                                   const pc_instance_desc *inst, int32_t n_inst);

@@ -222,15 +222,18 @@ struct DevTrace {
 };
 
 // ---- trace analysis of the replay on runs (pc_runs.hip).  A key buffer is
-// analysed once for all traces that read it.
+// analysed once for all traces that read it, or, where they read little of it,
+// for each of them alone (`trace`) the part between its first and last key.
 struct DevKeyBuf {
     const uint64_t *keys;
-    int64_t n;
+    int64_t n;             // keys; of a trace's part, at most
     int64_t tab0;          // first word of its table (2 n words; later its pieces, 8 bytes each)
     int64_t id0;           // first word of its ids (n)
     int64_t bits0;         // first word of its bitmaps (starts, weak links, cuts)
     uint32_t slots;        // table entries
     uint32_t blk0;         // first block of runs_insert and runs_link
+    int32_t trace;         // trace descriptor whose part this is, or -1
+    int32_t pad;
 };
 struct DevRunTrace {
     int32_t trace, buf;    // trace descriptor, key buffer

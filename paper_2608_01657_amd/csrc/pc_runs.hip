@@ -214,6 +214,20 @@ DEV bool request_ok(const DevTrace &T, int64_t r, int64_t &ko, int64_t &nf) {
              ko + nf > T.n_keys || nf > T.max_req_blocks || t < 0 || t < tp || t - tp > (int64_t)0xFFFFFFFF);
 }
 
+// The keys of a buffer that are analysed: [base, base + n) of it.  Positions
+// and ids count from base on.
+struct Span {
+    int64_t base, n;
+};
+DEV Span span_of(const RunsArgs &A, const DevKeyBuf &B) {
+    if (B.trace < 0) return {0, B.n};
+    const DevTrace &T = A.tr[B.trace];
+    const int64_t a = T.key_off[0], e = T.key_off[T.n_req];
+    // (else some request is malformed, and the trace is left)
+    const bool ok = a >= 0 && e >= a && e <= T.n_keys && e - a <= B.n;
+    return {a, ok ? e - a : 0};
+}
+
 // Blocks [0, nb_pos): positions of the key buffers; then requests.
 __global__ __launch_bounds__(kT) void runs_insert(RunsArgs A) {
     if (blockIdx.x >= A.nb_pos) {
@@ -223,22 +237,25 @@ __global__ __launch_bounds__(kT) void runs_insert(RunsArgs A) {
         const DevTrace &T = A.tr[R.trace];
         const int64_t r = (int64_t)(b - R.blk0) * kT + threadIdx.x;
         if (r >= T.n_req) return;
+        const DevKeyBuf &B = A.bufs[R.buf];
+        const Span S = span_of(A, B);
         int64_t ko, nf;
-        if (!request_ok(T, r, ko, nf)) {
+        if (!request_ok(T, r, ko, nf) || ko < S.base || ko - S.base + nf > S.n) {
             A.tflag[ti] = 1;
             return;
         }
-        uint32_t *marks = A.start + A.bufs[R.buf].bits0;
-        request_marks(ko, nf, r + 1 == T.n_req, T.n_keys,
+        uint32_t *marks = A.start + B.bits0;
+        request_marks(ko - S.base, nf, r + 1 == T.n_req, S.n,
                       [&](int64_t at) { atomicOr(marks + (at >> 5), 1u << (at & 31)); });
         atomicMin(A.first + R.first0 + T.prefix[r], (uint32_t)r);
         return;
     }
     const int32_t bi = find_block(A.bufs, A.n_bufs, blockIdx.x, &DevKeyBuf::blk0);
     const DevKeyBuf &B = A.bufs[bi];
+    const Span S = span_of(A, B);
     const int64_t pos = (int64_t)(blockIdx.x - B.blk0) * kT + threadIdx.x;
-    if (pos >= B.n) return;
-    const GLOBAL uint64_t *keys = (const GLOBAL uint64_t *)B.keys;
+    if (pos >= S.n) return;
+    const GLOBAL uint64_t *keys = (const GLOBAL uint64_t *)B.keys + S.base;
     uint32_t *tab = A.table + B.tab0;
     const uint64_t k = keys[pos];
     uint32_t at = key_slot(k, B.slots);
@@ -264,7 +281,7 @@ __global__ __launch_bounds__(kT) void runs_link(RunsArgs A) {
     const uint32_t *tab = A.table + B.tab0;
     uint32_t *id = A.id + B.id0;
     uint32_t x = 0;
-    const bool in = pos < B.n;
+    const bool in = pos < span_of(A, B).n;
     if (in) x = tab[id[pos]];
     // the id before it: the lane before, or for lane 0 from memory, where
     // another wavefront may have replaced the slot by the id already
@@ -295,6 +312,7 @@ __global__ __launch_bounds__(kT) void runs_list(RunsArgs A) {
     if (r >= T.n_req) return;
     int64_t ko, nf;
     request_ok(T, r, ko, nf);          // (valid: the flag above is clear)
+    ko -= span_of(A, B).base;
     RunsBuf V;
     V.id = A.id + B.id0;
     V.weak = A.weak + B.bits0;

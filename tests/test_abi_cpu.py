@@ -131,6 +131,26 @@ def test_no_analysis_past_the_largest_launch(n_traces):
     assert 0 < size(1 << 26) < 1 << 20
 
 
+def test_analysis_is_sized_by_what_the_traces_can_read():
+    """A few requests of a large key buffer: the analysis is planned for the
+    keys that they can hold, not for the buffer; for the whole buffer, once,
+    where the traces may read all of it."""
+    def size(n_keys, views):
+        n = len(views)
+        t = [_trace(n_req=r, max_req_blocks=m, n_keys=n_keys) for r, m in views]
+        i = [_inst(trace=k) for k in range(n)]
+        return P.lib().pc_replay_workspace_bytes((P.pc_trace_desc * n)(*t), n, (P.pc_instance_desc * n)(*i), n)
+    big = 120_000_000
+    few = size(big, [(100, 512)])
+    assert 12 * 51_200 < few < 16 * 51_200 + (1 << 20)
+    assert few <= size(51_200, [(100, 512)]) + 4096
+    assert size(big, [(100, 512), (50, 256)]) < 16 * 64_000 + (1 << 20)
+    assert size(big, [(100, 512), (50_000, 512)]) < 16 * 25_651_200 + 32 * 50_100 + (1 << 20)
+    whole = size(big, [(1_000_000, 512)])
+    assert 12 * big < whole < 13 * big + 32 * 1_000_000
+    assert size(big, [(1_000_000, 512), (100, 512)]) < whole + (1 << 20)
+
+
 def test_replay_rejects_small_or_misaligned_workspace():
     lib = P.lib()
     T = (P.pc_trace_desc * 1)(_trace())

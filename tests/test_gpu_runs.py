@@ -112,6 +112,34 @@ def test_traces_that_share_and_overlap_in_one_key_buffer():
             assert np.array_equal(pr[k], w.per_request)
 
 
+def test_small_views_of_a_large_key_buffer():
+    """Traces that can read a part of their key buffer only are analysed over
+    that part: at its start, inside, overlapping, at its end; malformed
+    offsets leave their trace alone."""
+    kt = chunk_trace(22, n_req=3000)
+    dt = dv.upload_keys(kt)
+    views, kts = _views(kt, dt, [(0, 40), (100, 140), (130, 150), (2000, 2100), (2984, 3000)])
+    assert sum(k.n_req * dt.max_req_blocks for k in kts) < dt.n_keys
+    for k, wrong in ((0, -5), (16, dt.n_keys + 9), (3, 0), (0, dt.n_keys + 40)):
+        bad, badk = _views(kt, dt, [(500, 516)])
+        off = badk[0].key_off.copy()
+        off[k] = wrong
+        bad[0].key_off = torch.from_numpy(off).to(dt.key_off.device)
+        views += bad
+        kts.append(None)
+    insts = [tg.Instance(t, p, c) for t in range(len(views)) for p in POLICIES for c in (60, 700)]
+    b = dv.ReplayBatch(views, insts, per_request=True)
+    b.launch()
+    pr = b.per_request_arrays()
+    for k, (res, x) in enumerate(zip(b.results(), insts)):
+        if kts[x.trace] is None:
+            assert res[2] == P.PC_EINVAL
+            continue
+        w = oracle.replay_key_trace(kts[x.trace], x, per_request=True)
+        assert_same(res, w, f"instance {k}")
+        assert np.array_equal(pr[k], w.per_request)
+
+
 @pytest.mark.parametrize("order", [(0, 1), (1, 0)])
 def test_equal_starts_with_different_ends(order):
     """The last request of a trace ends inside another trace's request that
