@@ -171,6 +171,13 @@ typedef struct {
 int64_t pc_replay_workspace_bytes(const pc_trace_desc *traces, int32_t n_traces,
                                   const pc_instance_desc *inst, int32_t n_inst);
 
+/* The same without the trace analysis: the least that pc_replay_batch takes,
+ * for where device memory is short.  From here up to
+ * pc_replay_workspace_bytes the general kernels alone replay the batch, with
+ * the same results in a multiple of the time. */
+int64_t pc_replay_workspace_min_bytes(const pc_trace_desc *traces, int32_t n_traces,
+                                      const pc_instance_desc *inst, int32_t n_inst);
+
 /* Per-instance replay state (the cache metadata: block keys and metadata,
  * stamps, the free-queue log, the block and ghost tables, per-request
  * scratch) that pc_replay_batch's general kernels would use for this batch:

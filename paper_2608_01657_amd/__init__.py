@@ -79,7 +79,7 @@ class pc_instance_stats(ctypes.Structure):
 
 
 EXPORTS = ["pc_last_error", "pc_block_offsets", "pc_hash_blocks", "pc_replay_workspace_bytes",
-           "pc_replay_state_bytes", "pc_replay_batch", "pc_replay_batch_static", "pc_get_stats"]
+           "pc_replay_workspace_min_bytes", "pc_replay_state_bytes", "pc_replay_batch", "pc_replay_batch_static", "pc_get_stats"]
 PC_STATIC_WORKSPACE_BYTES = 64 << 20
 
 _lib = None
@@ -131,9 +131,9 @@ def lib():
         L.pc_block_offsets.argtypes = [P, i64, i32, P, P]
         L.pc_hash_blocks.restype = i32
         L.pc_hash_blocks.argtypes = [P, i64, P, P, P, P, i64, i32, P, i64, P, P]
-        L.pc_replay_workspace_bytes.restype = i64
-        L.pc_replay_workspace_bytes.argtypes = [ctypes.POINTER(pc_trace_desc), i32,
-                                                ctypes.POINTER(pc_instance_desc), i32]
+        for f in (L.pc_replay_workspace_bytes, L.pc_replay_workspace_min_bytes):
+            f.restype = i64
+            f.argtypes = [ctypes.POINTER(pc_trace_desc), i32, ctypes.POINTER(pc_instance_desc), i32]
         L.pc_replay_state_bytes.restype = i32
         L.pc_replay_state_bytes.argtypes = [ctypes.POINTER(pc_trace_desc), i32, ctypes.POINTER(pc_instance_desc),
                                             i32, ctypes.POINTER(ctypes.c_int64), ctypes.POINTER(ctypes.c_int32)]
@@ -198,6 +198,14 @@ def _descs(traces: Sequence[pc_trace_desc], instances: Sequence[pc_instance_desc
 def pc_replay_workspace_bytes(traces: Sequence[pc_trace_desc], instances: Sequence[pc_instance_desc]) -> int:
     T, I = _descs(traces, instances)
     v = lib().pc_replay_workspace_bytes(T, len(traces), I, len(instances))
+    if v < 0:
+        raise PCError(int(v), pc_last_error())
+    return int(v)
+
+
+def pc_replay_workspace_min_bytes(traces: Sequence[pc_trace_desc], instances: Sequence[pc_instance_desc]) -> int:
+    T, I = _descs(traces, instances)
+    v = lib().pc_replay_workspace_min_bytes(T, len(traces), I, len(instances))
     if v < 0:
         raise PCError(int(v), pc_last_error())
     return int(v)

@@ -10,7 +10,8 @@ import numpy as np
 import torch
 
 from . import (make_instance_desc, phase_counters, make_trace_desc, pc_block_offsets, pc_get_stats, pc_hash_blocks,
-               pc_replay_batch, pc_replay_workspace_bytes, stats_to_dicts, PC_STATS_RECORD_BYTES)
+               pc_replay_batch, pc_replay_workspace_bytes, pc_replay_workspace_min_bytes, stats_to_dicts,
+               PC_STATS_RECORD_BYTES)
 
 
 @dataclass
@@ -123,7 +124,9 @@ def trace_desc(t):
 class ReplayBatch:
     """Holds the descriptors, workspace and stats buffer of one batch so the
     same replay can be launched repeatedly (each launch starts from an empty
-    cache)."""
+    cache).  Where device memory has no room for the trace analysis, the
+    workspace is allocated without it (the general kernels then replay the
+    batch)."""
 
     def __init__(self, dtraces: Sequence, instances: Sequence, per_request: bool = False):
         self.dtraces = list(dtraces)
@@ -131,8 +134,11 @@ class ReplayBatch:
         self.tdesc = [trace_desc(t) for t in self.dtraces]
         self.idesc = [make_instance_desc(i) for i in self.instances]
         dev = self.dtraces[0].key_off.device
-        nbytes = pc_replay_workspace_bytes(self.tdesc, self.idesc)
-        self.workspace = torch.empty((nbytes + 255) // 256 * 32, dtype=torch.int64, device=dev)
+        empty = lambda nbytes: torch.empty((nbytes + 255) // 256 * 32, dtype=torch.int64, device=dev)
+        try:
+            self.workspace = empty(pc_replay_workspace_bytes(self.tdesc, self.idesc))
+        except torch.OutOfMemoryError:
+            self.workspace = empty(pc_replay_workspace_min_bytes(self.tdesc, self.idesc))
         self.stats = torch.zeros(len(self.instances) * PC_STATS_RECORD_BYTES // 8, dtype=torch.int64, device=dev)
         self.per_request = None
         if per_request:

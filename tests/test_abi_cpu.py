@@ -6,8 +6,10 @@ import os
 import re
 
 import pytest
+import torch
 
 import paper_2608_01657_amd as P
+from paper_2608_01657_amd import device as dv
 from paper_2608_01657_amd import tracegen as tg
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -149,6 +151,28 @@ def test_analysis_is_sized_by_what_the_traces_can_read():
     whole = size(big, [(1_000_000, 512)])
     assert 12 * big < whole < 13 * big + 32 * 1_000_000
     assert size(big, [(1_000_000, 512), (100, 512)]) < whole + (1 << 20)
+
+
+def test_batch_that_has_no_room_for_the_analysis(monkeypatch):
+    """The least workspace lacks the analysis alone, one byte less is refused,
+    and ReplayBatch takes it where the full one does not fit."""
+    kt = tg.random_key_trace(1, n_req=2000, max_blocks=40, n_groups=2, n_prefix=8, n_contracts=1, key_universe=5000)
+    t = dv.upload_keys(kt, device="cpu")
+    insts = [tg.Instance(0, p, 64) for p in range(4)]
+    b = dv.ReplayBatch([t], insts)
+    full, least = (f(b.tdesc, b.idesc) for f in (P.pc_replay_workspace_bytes, P.pc_replay_workspace_min_bytes))
+    assert full > least + 12 * t.n_keys and b.workspace.numel() * 8 >= full
+    T, I = (P.pc_trace_desc * 1)(*b.tdesc), (P.pc_instance_desc * 4)(*b.idesc)
+    assert P.lib().pc_replay_batch(T, 1, I, 4, FAKE, least - 1, FAKE, None, None) == P.PC_ENOMEM
+    assert str(least) in P.pc_last_error()
+    empty = torch.empty
+
+    def short_of_memory(n, **kw):
+        if 8 * n > least + 255:
+            raise torch.OutOfMemoryError("no room")
+        return empty(n, **kw)
+    monkeypatch.setattr(dv.torch, "empty", short_of_memory)
+    assert least <= dv.ReplayBatch([t], insts).workspace.numel() * 8 < least + 256
 
 
 def test_replay_rejects_small_or_misaligned_workspace():
