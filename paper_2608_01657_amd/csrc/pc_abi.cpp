@@ -503,7 +503,7 @@ int32_t validate_and_plan(const pc_trace_desc *traces, int32_t n_traces, const p
         R.o_start = take(4 * R.bit_words);
         R.o_weak = take(4 * R.bit_words);
         R.o_cuts = take(4 * R.bit_words);
-        R.o_flags = take(4 * (int64_t)(R.rt.size() + 2 * R.kb.size()));
+        R.o_flags = take(4 * (int64_t)(2 * R.rt.size() + 2 * R.kb.size()));
         R.o_done = take(4 * (int64_t)n_inst);
         R.zeros = off - R.o_start;
         R.o_id = take(4 * R.id_words);
@@ -765,6 +765,7 @@ int32_t launch_planned(const Plan &P, int32_t n_traces, int32_t n_inst, uint8_t 
         A.req = (pcr::RunReq *)(ws + R.o_req);
         A.tflag = (int32_t *)(ws + R.o_flags);
         A.bflag = A.tflag + R.rt.size();
+        A.cmax = A.bflag + 2 * R.kb.size();
         A.done = (int32_t *)(ws + R.o_done);
         A.n_bufs = (int32_t)R.kb.size();
         A.n_traces = (int32_t)R.rt.size();

@@ -251,6 +251,7 @@ struct RunsArgs {
     RunReq *req;
     int32_t *tflag;        // per analysed trace: left to the general kernel
     int32_t *bflag;        // per key buffer: [2 b] no table, [2 b + 1] cuts were added
+    int32_t *cmax;         // per analysed trace: its largest contract index
     int32_t *done;         // per instance: replayed on runs
     int32_t n_bufs, n_traces;
     uint32_t nb_pos;       // blocks of runs_insert and runs_link over positions

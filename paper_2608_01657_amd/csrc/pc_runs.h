@@ -39,9 +39,10 @@
 //
 // An instance that needs more runs than its windows hold is replayed again,
 // with windows that take a CU's whole LDS (960 conversation instances 222 ms;
-// 281 with the general kernel instead of that); one that needs more than those, or
-// more pieces per request than lanes, is left to the general kernel
-// (pc_replay.hip).
+// 281 with the general kernel instead of that); one that needs more than those
+// is left to the general kernel (pc_replay.hip).  What the analysis can tell
+// is left to it at once: the instances of a trace with a request of more
+// pieces than lanes, and those with fewer contracts than a request names.
 #pragma once
 #include <stdint.h>
 
@@ -51,14 +52,14 @@ namespace pcr {
 // instance of the trace, eight requests to a wavefront load.
 struct RunReq {
     uint32_t n_full;     // full blocks
-    uint32_t info;       // bits 0-7 group, 8-15 contract, 16: its prefix was referenced before, 24-31 pieces
+    uint32_t info;       // bits 0-7 group, 8-15 contract, 16: its prefix was referenced before, 24-30 pieces
     uint32_t prefix;
     uint32_t dt;         // ticks since the request before it
     uint32_t ko;         // its pieces start at pieces[ko] of the trace's key buffer
     uint32_t nn;         // blocks that are no duplicates
     uint32_t pad[2];
 };
-constexpr uint32_t kRunsMaxPieces = 64;      // more: 255 is stored, and the request is not for this form
+constexpr uint32_t kRunsMaxPieces = 64;      // a lane each; a trace with a request of more is left
 // One piece: its first id; its length (bits 0-14, at most 32,767), whether an
 // earlier piece of the request holds the same blocks (bit 15: duplicates,
 // skipped), and how many blocks that are no duplicates come before it (bits
@@ -158,7 +159,10 @@ PC_RUNS_FN RunsListed list_request(W &wv, const RunsBuf &B, uint32_t ko, uint32_
         R.np += (uint32_t)W::popc(m);
     }
     W::sync();
-    if (R.np > kRunsMaxPieces) return R;
+    if (R.np > kRunsMaxPieces) {
+        R.left = true;
+        return R;
+    }
     const vb in = lane < R.np;
     const vu pid = W::ld_if(in, s, lane), dep = W::ld_if(in, s, lane + 64u);
     const vu end = W::sel(lane + 1u < R.np, W::next_lane(dep), wv.vu0(nf));
@@ -879,7 +883,6 @@ struct RunReplay {
         const uint32_t np = q.info >> 24;
         // (the only place that compacts the free queue; S3-FIFO's main queue
         // and ghost are looked at where they grow)
-        if (W::unlikely(np > kRunsMaxPieces || c >= (uint32_t)K())) { over = 1; return adm; }
         if (W::unlikely(q0.tail + np > q0.lim) && !room_for(q0, np)) { over = 1; return adm; }
         // S3-FIFO: ids of the first groups of the main queue and the ghost, and
         // the first chunks of the two queues, for the eviction (loaded here,

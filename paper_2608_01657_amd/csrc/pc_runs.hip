@@ -245,6 +245,8 @@ __global__ __launch_bounds__(kT) void runs_insert(RunsArgs A) {
             return;
         }
         uint32_t *marks = A.start + B.bits0;
+        const int32_t c = T.contract[r];
+        if (c > A.cmax[ti]) atomicMax(A.cmax + ti, c);
         request_marks(ko - S.base, nf, r + 1 == T.n_req, S.n,
                       [&](int64_t at) { atomicOr(marks + (at >> 5), 1u << (at & 31)); });
         atomicMin(A.first + R.first0 + T.prefix[r], (uint32_t)r);
@@ -333,7 +335,7 @@ __global__ __launch_bounds__(kT) void runs_list(RunsArgs A) {
         q.prefix = T.prefix[r];
         q.info = (uint32_t)T.group[r] | ((uint32_t)T.contract[r] << 8) |
                  (A.first[R.first0 + q.prefix] < (uint32_t)r ? 1u << 16 : 0u) |
-                 (L.np <= kRunsMaxPieces ? L.np : 255u) << 24;
+                 L.np << 24;
         q.dt = T.tick ? (uint32_t)(T.tick[r] - (r > 0 ? T.tick[r - 1] : 0)) : r > 0 ? 1u : 0u;
         q.ko = L.np > 0 ? (uint32_t)ko : 0u;
         q.nn = L.nn;
@@ -495,7 +497,7 @@ DEV void replay_instance(const RunsArgs &A, const int32_t *__restrict__ order, u
     if (A.wide && A.done[id]) return;
     const DevInst &I = A.inst[id];
     const DevRunTrace &R = A.traces[I.run_trace];
-    if (A.tflag[I.run_trace] || A.bflag[2 * R.buf]) return;
+    if (A.tflag[I.run_trace] || A.bflag[2 * R.buf] || A.cmax[I.run_trace] >= I.n_contracts) return;
     const DevTrace &T = A.tr[I.trace];
     LDS_AS uint32_t *lds = (LDS_AS uint32_t *)runs_smem;
     RunParams P;

@@ -353,7 +353,7 @@ Analysis analyse(const uint64_t *keys, int64_t n, const std::vector<TraceIn> &ts
                 const bool before = !seen.emplace(T.prefix[r], 1).second;
                 A.req.push_back({(uint32_t)(T.off[r + 1] - T.off[r]),
                                  T.group[r] | ((uint32_t)T.contract[r] << 8) | (before ? 1u << 16 : 0u) |
-                                     (L.np <= pcr::kRunsMaxPieces ? L.np : 255u) << 24,
+                                     L.np << 24,
                                  T.prefix[r], (uint32_t)(T.tick ? T.tick[r] - (r ? T.tick[r - 1] : 0) : r ? 1 : 0),
                                  (uint32_t)T.off[r], L.nn, {}});
             }
@@ -369,7 +369,7 @@ bool all_requests(X &R, const Analysis &A, int64_t n, int64_t n_prefix, int32_t 
         const pcr::RunReq &q = A.req[r];
         V<uint32_t> id = splat<uint32_t>(0), len = splat<uint32_t>(0);
         const uint32_t np = q.info >> 24;
-        for (uint32_t i = 0; i < 64 && np > 0 && np <= 64; ++i) {
+        for (uint32_t i = 0; i < 64 && np > 0; ++i) {
             const pcr::RunPiece &p = A.piece[q.ko + (i < np ? i : 0)];
             id.v[i] = p.id;
             len.v[i] = p.len;
@@ -422,7 +422,8 @@ bool replay_in(const Analysis &A, const pcr::RunParams &P, int64_t n_prefix, int
 // The oracle's signature; `window` overrides the windows' size (0 and -1: the
 // planner's, the widest).  The key buffer has n_keys keys; off2 (or null): a
 // second trace that reads it, listed behind the first, or ahead of it
-// (ahead2).  Returns 1 when the instance is left.
+// (ahead2).  Returns 1 when the replay leaves the
+// instance, 2 when the analysis does.
 extern "C" int runs_host_replay(const uint64_t *keys, const int64_t *off, const uint8_t *group,
                                 const uint8_t *contract, const uint32_t *prefix, const int64_t *tick, int64_t n_req,
                                 int32_t G, int64_t n_prefix, int32_t policy, int64_t C, int32_t flags, int32_t K,
@@ -433,7 +434,9 @@ extern "C" int runs_host_replay(const uint64_t *keys, const int64_t *off, const 
     std::vector<TraceIn> ts{{off, n_req, group, contract, prefix, tick}};
     if (off2) ts.insert(ahead2 ? ts.begin() : ts.end(), {off2, n_req2, nullptr, nullptr, nullptr, nullptr});
     const Analysis A = analyse(keys, n_keys, ts, off2 && ahead2 ? 1 : 0, interleave);
-    if (A.left) return 1;
+    if (A.left) return 2;
+    for (int64_t r = 0; r < n_req; ++r)
+        if (contract[r] >= K) return 2;
     pcr::RunParams P{};
     P.C = (int32_t)C;
     P.G = G;

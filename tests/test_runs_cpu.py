@@ -37,7 +37,8 @@ def _ptr(a):
 
 
 def run_host(L, kt, inst, window=0, other=None, ahead=0, interleave=0):
-    """(groups, inst, per_request), or None when left to the general kernel.
+    """(groups, inst, per_request), or when it is left to the general kernel, by
+    whom ("analysis", before any request is replayed, or "replay").
     other: key offsets of a second trace on the same key buffer, analysed
     behind this one or ahead of it."""
     a = [np.ascontiguousarray(x, t) for x, t in ((kt.keys if kt.keys.size else np.zeros(1), np.uint64),
@@ -56,14 +57,14 @@ def run_host(L, kt, inst, window=0, other=None, ahead=0, interleave=0):
                             inst.s3_small_permille, inst.s3_move_threshold, window, kt.keys.size, _ptr(off2),
                             0 if other is None else len(other) - 1, ahead, interleave, _ptr(gs), _ptr(st), _ptr(pr))
     if rc:
-        return None
+        return {1: "replay", 2: "analysis"}[rc]
     return [dict(zip(GROUP_FIELDS, map(int, row))) for row in gs], dict(zip(INST_FIELDS, map(int, st))), pr
 
 
 def compare(L, kt, inst, window=0, label="", **shared):
     """1 if the instance finished, equal to the oracle's; 0 if it was left."""
     got = run_host(L, kt, inst, window, **shared)
-    if got is None:
+    if isinstance(got, str):
         return 0
     o = oracle.replay_key_trace(kt, inst, per_request=True)
     what = f"{label} {tg.POLICY_NAMES[inst.policy]} C={inst.capacity} flags={inst.flags}"
@@ -262,3 +263,28 @@ def test_equal_starts_with_different_ends(host, ahead):
                     done += compare(host, kt, tg.Instance(0, pol, cap), 0, "shared", other=other.key_off, ahead=ahead)
                     n += 1
     assert done >= n // 2
+
+
+@pytest.mark.parametrize("pieces", [64, 65])
+def test_too_many_pieces_are_left_by_the_analysis(host, pieces):
+    """One request that takes single blocks of many earlier ones, at the end of
+    the trace: 64 pieces finish on runs, 65 are left before the first request."""
+    reqs = [np.arange(100 * r, 100 * r + 9) for r in range(pieces)]
+    reqs.append(np.array([100 * r for r in range(pieces)]))
+    n = len(reqs)
+    kt = tg.KeyTrace(np.concatenate(reqs).astype(np.uint64), np.cumsum([0] + [len(x) for x in reqs]).astype(np.int64),
+                     (np.arange(n) % 3).astype(np.uint8), np.zeros(n, np.uint8), np.zeros(n, np.uint32), 3, 1)
+    for pol in POLICIES:
+        if pieces == 64:
+            assert compare(host, kt, tg.Instance(0, pol, 200)) == 1
+        else:
+            assert run_host(host, kt, tg.Instance(0, pol, 200)) == "analysis"
+
+
+def test_contracts_out_of_range_are_left_by_the_analysis(host):
+    kt = chunk_trace(3, n_req=50)
+    kt.contract[49] = 2
+    one = (tg.Q16, 20 * tg.Q16)
+    for pol in POLICIES:
+        assert compare(host, kt, tg.Instance(0, pol, 90, contracts=[one] * 3)) == 1
+        assert run_host(host, kt, tg.Instance(0, pol, 90, contracts=[one] * 2)) == "analysis"
