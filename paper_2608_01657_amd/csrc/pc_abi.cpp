@@ -134,15 +134,19 @@ constexpr bool kHaveRuns = false;
 constexpr bool kHaveRuns = true;
 #endif
 
-// What the replay on runs takes: positions and table slots below 2^31, and
-// prefix bitmaps and requests that one wavefront goes through in a moment.  A
+// What the replay on runs takes: positions and table slots below 2^31, prefix
+// bitmaps that one wavefront goes through in a moment, and requests that it
+// lists before the general kernels have replayed the trace: 9 ns a block for
+// the longest one, against 6 us a request at least that runs save (16 requests,
+// C = 4,096: of 120,000 blocks 1.1 ms on runs and 2.0, of 250,000 2.2 and 2.0;
+// 64 of 250,000 3.3 and 8.4).  A
 // batch whose longest trace is shorter than kRunsMinReq requests may be over
 // before the analysis has paid (48 instances on 16 traces, us, general kernels
 // and on runs: 8 requests of 4 blocks 84 and 98, of 200 blocks 747 and 286; 12
 // of 4 blocks 106 and 105; 16 of 4 blocks 127 and 107, of 200 blocks 2782 and
 // 1037).
 constexpr int64_t kRunsMaxKeys = (int64_t)1 << 30, kRunsMaxPrefix = (int64_t)1 << 22;
-constexpr int32_t kRunsMaxBlocks = 1 << 20;
+constexpr int32_t kRunsMaxBlocks = 1 << 20, kRunsMaxBlocksFew = 1 << 17;
 constexpr int64_t kRunsMinReq = 16;
 constexpr int64_t kRunsMaxBytes = (int64_t)16 << 30;
 // (a launch holds less than 2^32 work items; blocks of the analysis have 256)
@@ -163,7 +167,8 @@ void plan_runs(const pc_trace_desc *traces, int32_t n_traces, const pc_instance_
     auto fits = [&](int i) {
         const pc_trace_desc &t = traces[i];
         return used[i] && t.n_req >= 1 && t.n_req <= kRunsMaxKeys && t.n_keys <= kRunsMaxKeys &&
-               t.n_prefix <= kRunsMaxPrefix && t.max_req_blocks <= kRunsMaxBlocks;
+               t.n_prefix <= kRunsMaxPrefix && t.max_req_blocks <= kRunsMaxBlocks &&
+               (t.max_req_blocks <= kRunsMaxBlocksFew || t.max_req_blocks <= 512 * t.n_req);
     };
     struct Buf {
         int64_t reads = 0;       // keys that its traces read at most

@@ -153,6 +153,13 @@ def test_analysis_is_sized_by_what_the_traces_can_read():
     assert size(big, [(1_000_000, 512), (100, 512)]) < whole + (1 << 20)
 
 
+def test_no_analysis_of_requests_that_are_listed_slower_than_replayed():
+    def size(n_req, blocks):
+        return _ws(_trace(n_req=n_req, n_keys=1 << 21, max_req_blocks=blocks), _inst())
+    for n_req, most in ((16, 1 << 17), (256, 1 << 17), (1024, 1 << 19), (5000, 1 << 20)):
+        assert size(n_req, most) > 12 << 21 and 0 < size(n_req, most + 1) < 1 << 20
+
+
 def test_batch_that_has_no_room_for_the_analysis(monkeypatch):
     """The least workspace lacks the analysis alone, one byte less is refused,
     and ReplayBatch takes it where the full one does not fit."""
