@@ -166,8 +166,8 @@ typedef struct {
  * They include the trace analysis of the replay on runs: some 12 bytes per
  * key of every distinct key buffer, or, where its traces can read only part of
  * it, per key that they can (n_req * max_req_blocks); and 32 per request; where
- * that is at most 16 GiB.  pc_replay_batch also takes a workspace that only lacks this part
- * and then replays with the general kernels alone. */
+ * that is at most 16 GiB.  pc_replay_batch also takes a workspace that only
+ * lacks this part and then replays with the general kernels alone. */
 int64_t pc_replay_workspace_bytes(const pc_trace_desc *traces, int32_t n_traces,
                                   const pc_instance_desc *inst, int32_t n_inst);
 
@@ -177,6 +177,16 @@ int64_t pc_replay_workspace_bytes(const pc_trace_desc *traces, int32_t n_traces,
  * the same results in a multiple of the time. */
 int64_t pc_replay_workspace_min_bytes(const pc_trace_desc *traces, int32_t n_traces,
                                       const pc_instance_desc *inst, int32_t n_inst);
+
+/* Where pc_replay_batch, given a workspace of workspace_bytes, leaves how it
+ * replayed the instances: the byte offset of int32[n_inst] in the workspace
+ * (the results do not depend on it), or 0: with the general kernels all. */
+#define PC_ROUTE_GENERAL 0
+#define PC_ROUTE_RUNS 1             /* one wavefront, on runs of blocks             */
+#define PC_ROUTE_RUNS_WIDE 2        /* the same, with the widest windows            */
+int64_t pc_replay_route_offset(const pc_trace_desc *traces, int32_t n_traces,
+                               const pc_instance_desc *inst, int32_t n_inst,
+                               int64_t workspace_bytes);
 
 /* Per-instance replay state (the cache metadata: block keys and metadata,
  * stamps, the free-queue log, the block and ghost tables, per-request
@@ -197,12 +207,12 @@ int32_t pc_replay_state_bytes(const pc_trace_desc *traces, int32_t n_traces,
                               int64_t *bytes_out, int32_t *layout_out);
 
 /* Replay every instance over its trace, one wavefront or workgroup per
- * instance; queued on `stream` (instances of different LDS footprints run as separate
- * launches on library streams that fork from and join back into it).  Per request it runs the hooks of Alg. 1 (OnRequest, OnTouch
- * with the debt gate of Eq. 4, OnCacheFullBlocks metering Eqs. 1-3) and,
- * when the cache is full, the reclamation of Alg. 2 (PrefixShield: Eqs. 5-9;
- * LRU, S3-FIFO and StaticQuota: the baselines of Sec. V-A) under the same
- * debt accounting.
+ * instance; queued on `stream` (instances of different LDS footprints run as
+ * separate launches on library streams that fork from and join back into it).
+ * Per request it runs the hooks of Alg. 1 (OnRequest, OnTouch with the debt
+ * gate of Eq. 4, OnCacheFullBlocks metering Eqs. 1-3) and, when the cache is
+ * full, the reclamation of Alg. 2 (PrefixShield: Eqs. 5-9; LRU, S3-FIFO and
+ * StaticQuota: the baselines of Sec. V-A) under the same debt accounting.
  *   d_workspace   device memory of pc_replay_workspace_bytes() bytes or more
  *                 (see there), 256-byte aligned; its contents need not be
  *                 zeroed.

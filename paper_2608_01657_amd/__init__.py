@@ -31,6 +31,7 @@ PC_MAX_GROUPS, PC_MAX_CONTRACTS, PC_MAX_CAPACITY = 64, 4, 32767
 PC_LRU, PC_S3FIFO, PC_PREFIXSHIELD, PC_STATICQUOTA = 0, 1, 2, 3
 PC_FLAG_NO_SEGMENTATION, PC_FLAG_NO_DEBT_GATE = 1, 2
 PC_STATS_RECORD_BYTES = 64 * 136 + 64
+PC_ROUTE_GENERAL, PC_ROUTE_RUNS, PC_ROUTE_RUNS_WIDE = 0, 1, 2
 PC_LAYOUT_LDS, PC_LAYOUT_HYBRID, PC_LAYOUT_WS = 0, 1, 2
 LAYOUT_NAMES = {PC_LAYOUT_LDS: "lds", PC_LAYOUT_HYBRID: "hybrid", PC_LAYOUT_WS: "workspace"}
 
@@ -79,7 +80,8 @@ class pc_instance_stats(ctypes.Structure):
 
 
 EXPORTS = ["pc_last_error", "pc_block_offsets", "pc_hash_blocks", "pc_replay_workspace_bytes",
-           "pc_replay_workspace_min_bytes", "pc_replay_state_bytes", "pc_replay_batch", "pc_replay_batch_static", "pc_get_stats"]
+           "pc_replay_workspace_min_bytes", "pc_replay_route_offset", "pc_replay_state_bytes", "pc_replay_batch",
+           "pc_replay_batch_static", "pc_get_stats"]
 PC_STATIC_WORKSPACE_BYTES = 64 << 20
 
 _lib = None
@@ -134,6 +136,9 @@ def lib():
         for f in (L.pc_replay_workspace_bytes, L.pc_replay_workspace_min_bytes):
             f.restype = i64
             f.argtypes = [ctypes.POINTER(pc_trace_desc), i32, ctypes.POINTER(pc_instance_desc), i32]
+        L.pc_replay_route_offset.restype = i64
+        L.pc_replay_route_offset.argtypes = [ctypes.POINTER(pc_trace_desc), i32, ctypes.POINTER(pc_instance_desc),
+                                             i32, i64]
         L.pc_replay_state_bytes.restype = i32
         L.pc_replay_state_bytes.argtypes = [ctypes.POINTER(pc_trace_desc), i32, ctypes.POINTER(pc_instance_desc),
                                             i32, ctypes.POINTER(ctypes.c_int64), ctypes.POINTER(ctypes.c_int32)]
@@ -209,6 +214,17 @@ def pc_replay_workspace_min_bytes(traces: Sequence[pc_trace_desc], instances: Se
     if v < 0:
         raise PCError(int(v), pc_last_error())
     return int(v)
+
+
+def pc_replay_route_offset(traces: Sequence[pc_trace_desc], instances: Sequence[pc_instance_desc],
+                           workspace_bytes: int) -> int:
+    """Byte offset in the workspace of how each instance was replayed
+    (PC_ROUTE_*, int32); 0: with the general kernels all."""
+    T, I = _descs(traces, instances)
+    v = lib().pc_replay_route_offset(T, len(traces), I, len(instances), workspace_bytes)
+    if v < 0:
+        _check(int(v))
+    return v
 
 
 def pc_replay_state_bytes(traces: Sequence[pc_trace_desc], instances: Sequence[pc_instance_desc]):

@@ -619,6 +619,15 @@ int64_t pc_replay_workspace_min_bytes(const pc_trace_desc *traces, int32_t n_tra
     return P.ws_bytes;
 }
 
+int64_t pc_replay_route_offset(const pc_trace_desc *traces, int32_t n_traces, const pc_instance_desc *inst,
+                               int32_t n_inst, int64_t workspace_bytes) {
+    Plan P;
+    int32_t rc = validate_and_plan(traces, n_traces, inst, n_inst, lds_per_cu(), cu_count(), true, P);
+    if (rc != PC_OK) return rc;
+    ok();
+    return P.runs.on && workspace_bytes >= P.ws_bytes ? P.runs.o_done : 0;
+}
+
 int32_t pc_replay_state_bytes(const pc_trace_desc *traces, int32_t n_traces, const pc_instance_desc *inst,
                               int32_t n_inst, int64_t *bytes_out, int32_t *layout_out) {
     if (n_inst > 0 && (!bytes_out || !layout_out)) return fail(PC_EINVAL, "null output");

@@ -252,7 +252,7 @@ struct RunsArgs {
     int32_t *tflag;        // per analysed trace: left to the general kernel
     int32_t *bflag;        // per key buffer: [2 b] no table, [2 b + 1] cuts were added
     int32_t *cmax;         // per analysed trace: its largest contract index
-    int32_t *done;         // per instance: replayed on runs
+    int32_t *done;         // per instance: how it was replayed, PC_ROUTE_*
     int32_t n_bufs, n_traces;
     uint32_t nb_pos;       // blocks of runs_insert and runs_link over positions
     int32_t wide;          // replay: the instances that are not done, with the widest windows

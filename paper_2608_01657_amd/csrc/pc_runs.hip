@@ -20,6 +20,7 @@
 // and analysis, 2.1 to 2.3 us a request; the general kernels, a workgroup of
 // four wavefronts and a step per 256 blocks, take 939 ms (two instances to a
 // CU, 18.8 us a request).
+#include "pc.h"
 #include "pc_internal.h"
 
 #define PC_RUNS_FN __device__ __forceinline__
@@ -516,7 +517,6 @@ DEV void replay_instance(const RunsArgs &A, const int32_t *__restrict__ order, u
         P.beta[c] = I.beta[c];
         P.invw[c] = I.invw[c];
     }
-    P.n_req = T.n_req;
     Feed F;
     F.rec = (const GLOBAL uint32_t *)(A.req + R.req0);
     F.piece = (const GLOBAL uint2 *)(A.table + A.bufs[R.buf].tab0);
@@ -533,7 +533,7 @@ DEV void replay_instance(const RunsArgs &A, const int32_t *__restrict__ order, u
     else if (I.policy == kS3) ok = replay_policy<kS3>(P, F, st, lds);
     else if (I.policy == kSQ) ok = replay_policy<kSQ>(P, F, st, lds);
     else ok = replay_policy<kPS>(P, F, st, lds);
-    if (ok && threadIdx.x == 0) *done = 1;
+    if (ok && threadIdx.x == 0) *done = A.wide ? PC_ROUTE_RUNS_WIDE : PC_ROUTE_RUNS;
 }
 __global__ __launch_bounds__(64) void runs_replay(RunsArgs A, const int32_t *__restrict__ order, uint8_t *ws,
                                                   int64_t *stats, int32_t *per_req) {

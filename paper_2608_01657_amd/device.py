@@ -10,8 +10,8 @@ import numpy as np
 import torch
 
 from . import (make_instance_desc, phase_counters, make_trace_desc, pc_block_offsets, pc_get_stats, pc_hash_blocks,
-               pc_replay_batch, pc_replay_workspace_bytes, pc_replay_workspace_min_bytes, stats_to_dicts,
-               PC_STATS_RECORD_BYTES)
+               pc_replay_batch, pc_replay_route_offset, pc_replay_workspace_bytes, pc_replay_workspace_min_bytes,
+               stats_to_dicts, PC_ROUTE_GENERAL, PC_STATS_RECORD_BYTES)
 
 
 @dataclass
@@ -152,6 +152,14 @@ class ReplayBatch:
         G, S = pc_get_stats(self.stats, len(self.instances), -1, 64, stream)
         ng = [self.dtraces[i.trace].n_groups for i in self.instances]
         return stats_to_dicts(G, S, ng)
+
+    def routes(self) -> List[int]:
+        """How the last launch replayed each instance (PC_ROUTE_*)."""
+        n, at = len(self.instances), pc_replay_route_offset(self.tdesc, self.idesc, self.workspace.numel() * 8)
+        if at == 0:
+            return [PC_ROUTE_GENERAL] * n
+        torch.cuda.synchronize(self.workspace.device)
+        return self.workspace.view(torch.int32)[at // 4:at // 4 + n].tolist()
 
     def phase_counters(self, stream=None) -> List[dict]:
         """Per-instance phase cycles and event counts (phase-counter library

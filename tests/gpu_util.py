@@ -15,10 +15,12 @@ def gpu_hash(trace):
     return t, keys, t.key_off.cpu().numpy()
 
 
-def replay_gpu(dtraces, instances, per_request=False):
+def replay_gpu(dtraces, instances, per_request=False, routes=None):
+    """routes: how each instance has to be replayed (P.PC_ROUTE_*), if given."""
     b = dv.ReplayBatch(dtraces, instances, per_request=per_request)
     b.launch()
     res = b.results()
+    assert routes is None or b.routes() == list(routes)
     pr = b.per_request_arrays() if per_request else None
     return res, pr
 
@@ -43,9 +45,9 @@ def _pad_trace():
                        np.zeros(0, np.uint32), 1, 1)
 
 
-def run_key_traces(kts, instances_per_trace, per_request=True, dense=False):
+def run_key_traces(kts, instances_per_trace, per_request=True, dense=False, routes=None):
     """Replay key traces on both sides; every instance compared in full.
-    dense: in a batch padded beyond the GPU's CUs (see N_DENSE_PAD)."""
+    routes: how each has to be replayed (P.PC_ROUTE_*), if given.  dense: in a batch padded beyond the GPU's CUs (see N_DENSE_PAD)."""
     kts = list(kts)
     instances_per_trace = list(instances_per_trace)
     n_real = sum(len(x) for x in instances_per_trace)
@@ -58,7 +60,7 @@ def run_key_traces(kts, instances_per_trace, per_request=True, dense=False):
         for inst in lst:
             inst.trace = ti
             insts.append(inst)
-    res, pr = replay_gpu(dts, insts, per_request=per_request)
+    res, pr = replay_gpu(dts, insts, per_request=per_request, routes=routes)
     res, insts = res[:n_real], insts[:n_real]
     for k, inst in enumerate(insts):
         kt = kts[inst.trace]

@@ -172,6 +172,9 @@ def test_batch_that_has_no_room_for_the_analysis(monkeypatch):
     T, I = (P.pc_trace_desc * 1)(*b.tdesc), (P.pc_instance_desc * 4)(*b.idesc)
     assert P.lib().pc_replay_batch(T, 1, I, 4, FAKE, least - 1, FAKE, None, None) == P.PC_ENOMEM
     assert str(least) in P.pc_last_error()
+    assert P.pc_replay_route_offset(b.tdesc, b.idesc, full - 1) == 0
+    at = P.pc_replay_route_offset(b.tdesc, b.idesc, full)
+    assert 0 < at <= full - 4 * len(insts) and at % 4 == 0
     empty = torch.empty
 
     def short_of_memory(n, **kw):

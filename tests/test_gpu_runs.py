@@ -15,6 +15,7 @@ from paper_2608_01657_amd import tracegen as tg
 from test_runs_cpu import chunk_trace, ends_inside, partial_repeats, random_cuts
 
 pytestmark = pytest.mark.gpu
+GENERAL, RUNS, WIDE = P.PC_ROUTE_GENERAL, P.PC_ROUTE_RUNS, P.PC_ROUTE_RUNS_WIDE
 
 
 def _insts(caps, pols=POLICIES, contracts=((tg.Q16 * 2, 30 * tg.Q16),)):
@@ -33,18 +34,19 @@ def _trace(reqs, n_groups=3, seed=0):
 
 @pytest.mark.parametrize("seed", range(3))
 def test_unchained_documents_and_duplicates(seed):
-    run_key_traces([chunk_trace(seed, n_req=700)], [_insts((25, 300, 3000))])
+    run_key_traces([chunk_trace(seed, n_req=700)], [_insts((25, 300, 3000))], routes=[RUNS] * 12)
 
 
 @pytest.mark.parametrize("seed", range(3))
 def test_partial_repeats_far_apart_in_a_request(seed):
     """Every request adds cuts to documents that other wavefronts are listing."""
-    run_key_traces([partial_repeats(seed, n_req=3000, docs=1500)], [_insts((60, 700, 4096))])
+    run_key_traces([partial_repeats(seed, n_req=3000, docs=1500)], [_insts((60, 700, 4096))], routes=[RUNS] * 12)
 
 
 @pytest.mark.parametrize("n_req", [1, 15, 16, 17, 63, 64, 65])
 def test_shortest_traces_on_runs(n_req):
-    run_key_traces([chunk_trace(50 + n_req, n_req=n_req)], [_insts((1, 7, 64, 4096))])
+    run_key_traces([chunk_trace(50 + n_req, n_req=n_req)], [_insts((1, 7, 64, 4096))],
+                   routes=[RUNS if n_req >= 16 else GENERAL] * 16)
 
 
 @pytest.mark.parametrize("blocks", [63, 64, 65, 130])
@@ -53,13 +55,15 @@ def test_requests_of_single_block_pieces(blocks):
     pieces on runs, more in the general kernel."""
     rng = np.random.default_rng(blocks)
     reqs = [rng.permutation(400)[:blocks] for _ in range(90)]
-    run_key_traces([_trace(reqs)], [_insts((64, 150, 500))])
+    run_key_traces([_trace(reqs)], [_insts((64, 150, 500))], routes=[RUNS if blocks <= 64 else GENERAL] * 12)
 
 
 def test_more_runs_than_rings_hold():
-    """Single-block prompts: thousands of runs are live at once."""
+    """Single-block prompts: thousands of runs are live at once, and more in
+    the ghost of S3-FIFO than any window holds."""
     reqs = [[10 * r] if r % 3 else [10 * r, 7, 8] for r in range(6000)]
-    run_key_traces([_trace(reqs)], [_insts((500, 4096, 9000))])
+    run_key_traces([_trace(reqs)], [_insts((500, 4096, 9000))],
+                   routes=[RUNS, WIDE, WIDE] + [RUNS, GENERAL, GENERAL] + 2 * [RUNS, WIDE, WIDE])
 
 
 def test_malformed_request_after_many_good_ones():
@@ -70,6 +74,7 @@ def test_malformed_request_after_many_good_ones():
     insts = [tg.Instance(t, p, 100) for t in range(3) for p in POLICIES]
     b = dv.ReplayBatch(dts, insts)
     b.launch()
+    assert b.routes() == [RUNS] * 8 + [GENERAL] * 4
     for (groups, inst, status), x in zip(b.results(), insts):
         if x.trace == 2:
             assert status == P.PC_EINVAL and not any(inst.values())
@@ -101,10 +106,12 @@ def test_traces_that_share_and_overlap_in_one_key_buffer():
                         kt.n_groups, kt.n_prefix)
     o = dv.upload_keys(other)
     o.keys = dt.keys
-    for batch, ks in ((views, kts), (views + [o], kts + [other])):
+    # (the trace of a request that starts inside another's pieces is left)
+    for batch, ks, runs in ((views, kts, range(5)), (views + [o], kts + [other], [4])):
         insts = [tg.Instance(t, p, c) for t in range(len(batch)) for p in POLICIES for c in (60, 700)]
         b = dv.ReplayBatch(batch, insts, per_request=True)
         b.launch()
+        assert b.routes() == [RUNS if x.trace in runs else GENERAL for x in insts]
         pr = b.per_request_arrays()
         for k, (res, x) in enumerate(zip(b.results(), insts)):
             w = oracle.replay_key_trace(ks[x.trace], x, per_request=True)
@@ -130,6 +137,7 @@ def test_small_views_of_a_large_key_buffer():
     insts = [tg.Instance(t, p, c) for t in range(len(views)) for p in POLICIES for c in (60, 700)]
     b = dv.ReplayBatch(views, insts, per_request=True)
     b.launch()
+    assert b.routes() == [RUNS if kts[x.trace] else GENERAL for x in insts]
     pr = b.per_request_arrays()
     for k, (res, x) in enumerate(zip(b.results(), insts)):
         if kts[x.trace] is None:
@@ -144,7 +152,8 @@ def test_small_views_of_a_large_key_buffer():
 def test_equal_starts_with_different_ends(order):
     """The last request of a trace ends inside another trace's request that
     starts where it does; and random cuts of one key buffer."""
-    for kts in ends_inside(), random_cuts(0), random_cuts(1):
+    # (with random cuts requests of one trace start inside the other's pieces)
+    for kts, runs in (ends_inside(), (0, 1)), (random_cuts(0), (1,)), (random_cuts(1), (0,)):
         dts = [dv.upload_keys(k) for k in kts]
         for d in dts:
             d.keys = dts[0].keys
@@ -152,6 +161,7 @@ def test_equal_starts_with_different_ends(order):
         insts = [tg.Instance(t, p, c) for t in range(2) for p in POLICIES for c in (7, 64, 300)]
         b = dv.ReplayBatch(dts, insts, per_request=True)
         b.launch()
+        assert b.routes() == [RUNS if order[x.trace] in runs else GENERAL for x in insts]
         pr = b.per_request_arrays()
         for k, (res, x) in enumerate(zip(b.results(), insts)):
             w = oracle.replay_key_trace(kts[x.trace], x, per_request=True)
@@ -171,8 +181,10 @@ def test_general_kernel_where_the_workspace_has_no_room_for_the_analysis():
     # the run plan adds at least the table and the ids of every key
     small = b.workspace[:(need - 12 * t.n_keys) // 8 // 32 * 32]
     stats = torch.zeros_like(b.stats)
+    assert P.pc_replay_route_offset(b.tdesc, b.idesc, small.numel() * 8) == 0
     P.pc_replay_batch(b.tdesc, b.idesc, small, stats)
     b.launch()
+    assert b.routes() == [RUNS] * 8
     torch.cuda.synchronize()
     assert torch.equal(stats, b.stats)
     big = tg.onetouch_4096(2001, 50000)
@@ -181,6 +193,7 @@ def test_general_kernel_where_the_workspace_has_no_room_for_the_analysis():
     B = dv.ReplayBatch([T], insts[:2])
     assert P.pc_replay_workspace_bytes(B.tdesc, B.idesc) > P.PC_STATIC_WORKSPACE_BYTES
     B.launch()
+    assert B.routes() == [RUNS] * 2
     stats = torch.zeros_like(B.stats)
     P.pc_replay_batch_static(B.tdesc, B.idesc, stats)
     torch.cuda.synchronize()
