@@ -42,7 +42,9 @@
 // 281 with the general kernel instead of that); one that needs more than those
 // is left to the general kernel (pc_replay.hip).  What the analysis can tell
 // is left to it at once: the instances of a trace with a request of more
-// pieces than lanes, and those with fewer contracts than a request names.
+// pieces than lanes, those with fewer contracts than a request names, and
+// those of many short pieces, which the general kernel replays faster
+// (runs_pay).
 #pragma once
 #include <stdint.h>
 
@@ -90,6 +92,11 @@ constexpr RunWindows runs_windows(int policy, int32_t capacity, int wide) {
     if (policy == 1) return capacity <= 4096 ? RunWindows{{1024, 768, 768}} : RunWindows{{1280, 2048, 1024}};
     return {{capacity <= 2048 ? 1024 : capacity <= 4096 ? 1536 : 3072, 0, 0}};
 }
+// Live runs that the first windows are sure to hold (S3-FIFO: by the ghost's).
+constexpr int32_t runs_narrow_room(int policy, int32_t capacity) {
+    const RunWindows w = runs_windows(policy, capacity, 0);
+    return w.n[policy == 1 ? 2 : 0] - 128;
+}
 // PrefixShield keeps its admitted bits in LDS up to this many prefixes.
 constexpr int32_t kRunsLdsPrefix = 1 << 16;
 constexpr int32_t kRunsScratch = 192;     // words that single-lane stores spread over
@@ -98,6 +105,63 @@ constexpr int32_t runs_lds_bytes(int policy, RunWindows w, int64_t n_prefix) {
     const int64_t words = (policy == 1 || policy == 2 ? 3 : 2) * ((int64_t)w.n[0] + w.n[1] + w.n[2]);
     const int64_t bits = policy == 2 && n_prefix <= kRunsLdsPrefix ? (n_prefix + 31) / 32 : 0;
     return (int32_t)(4 * (kRunsScratch + words + bits));
+}
+
+// ------------------------------------------------------------ which form
+// Sums over a sample of a trace's requests: one of every 128th part of the
+// trace, or all (what repeats in a fixed rhythm comes in as often as it is).
+struct RunsSample {
+    uint32_t n, pieces;       // requests; their pieces
+    uint32_t blocks, fresh;   // blocks; pieces that no earlier request holds
+};
+constexpr int64_t kSamples = 128;
+// The request's place in the sample, or -1.
+PC_RUNS_FN int32_t sample_slot(int64_t r, int64_t n_req) {
+    const uint32_t part = (uint32_t)((n_req + kSamples - 1) / kSamples), k = (uint32_t)r / part;
+    // (2^32 over the golden ratio)
+    return (uint32_t)r - k * part == ((k + 1u) * 0x9E3779B1u >> 8) % part ? (int32_t)k : -1;
+}
+// A sampled request's two words (0, 0: the last part is too short for its place).
+constexpr uint32_t sample_word0(uint32_t np, uint32_t fresh) { return 0x80000000u | np | fresh << 8; }
+PC_RUNS_FN uint32_t sample_word1(int64_t nf) { return (uint32_t)(nf < 65535 ? nf : 65535); }
+// Whether an instance is replayed on runs, by the time of a request in either
+// form (us).  On runs every piece is compared with every 256 entries of the
+// windows, so many short pieces cost more than the blocks that they hold cost
+// the general kernel.  Alone on the chip (LRU, C = 4,096, requests of k
+// documents of d blocks; on runs and general kernel): k 4, d 16 2.5 and 4.9;
+// k 16, d 16 6.5 and 5.4; k 24, d 4 15 and 5.1; k 60, d 1 89 and 5.2
+// (C = 16,384: 265 and 7.0).  Over 546 such batches of all policies this is
+// at most 1.3 times slower than the general kernel (always runs: 38 times).
+//   C      capacity
+//   room   blocks that a request may hold
+//   first  with the first windows (which may turn out too small)
+//   runs_load, general_load
+//          how many instances of the batch share what one alone would have
+PC_RUNS_FN bool runs_pay(int policy, int32_t C, int32_t room, bool first, int64_t n_req, const RunsSample &q,
+                         float runs_load, float general_load) {
+    if (q.n == 0 || q.pieces == 0) return true;
+    const float n = (float)q.n, np = (float)q.pieces / n, nf = (float)q.blocks / n;
+    const float cut = nf > (float)room ? (float)room / nf : 1.0f, x = nf * cut / 256.0f;
+    // runs in the cache: what fills it, or all that the trace has; on average
+    // over a trace that fills it as it goes
+    const float total = (float)q.fresh / n * (float)n_req;
+    const float fill = (float)C * np / nf, live = fill < total ? fill : total;
+    const float mean = live - live * live / (2.0f * (total > 1.0f ? total : 1.0f));
+    const float groups = mean > 256.0f ? mean / 256.0f : 1.0f;
+    float a, b, u, gen;
+    if (policy == 1) {
+        a = 1.2f, b = 0.52f, u = 0.13f;
+        gen = 7.0f + 4.5f * x > 11.5f * x ? 7.0f + 4.5f * x : 11.5f * x;
+    } else if (policy == 2) {
+        a = 1.5f, b = 0.15f, u = 0.095f;
+        gen = 6.0f + 8.0f * x > 13.0f * x ? 6.0f + 8.0f * x : 13.0f * x;
+    } else {
+        a = 1.0f, b = 0.2f, u = 0.085f;
+        gen = 4.6f + 0.5f * x > 5.1f * x ? 4.6f + 0.5f * x : 5.1f * x;
+    }
+    float runs = a + np * (b * cut + u * groups);
+    if (first && live > (float)runs_narrow_room(policy, C)) runs *= 1.6f;      // once more with the widest windows
+    return runs * runs_load <= gen * general_load;
 }
 
 // ------------------------------------------------------------ analysis
@@ -123,6 +187,7 @@ PC_RUNS_FN void request_marks(int64_t ko, int64_t nf, bool last, int64_t n_keys,
 }
 struct RunsListed {
     uint32_t np, nn;          // pieces; blocks that are no duplicates
+    uint32_t fresh;           // pieces that begin with a block first seen in this request
     bool cut;                 // added a cut
     bool left;                // not for this form
 };
@@ -143,7 +208,7 @@ PC_RUNS_FN RunsListed list_request(W &wv, const RunsBuf &B, uint32_t ko, uint32_
     using vu = typename W::vu;
     using vb = typename W::vb;
     const vu lane = wv.lane(), zu = wv.vu0(0);
-    RunsListed R{0u, nf, false, false};
+    RunsListed R{0u, nf, 0u, false, false};
     for (uint32_t j0 = 0; j0 < nf; j0 += 64) {
         const vu j = lane + j0;
         const vb in = j < nf;
@@ -193,6 +258,7 @@ PC_RUNS_FN RunsListed list_request(W &wv, const RunsBuf &B, uint32_t ko, uint32_
     const vu own = W::sel(dup, zu, len);
     const vu upto = W::scan(own), before = upto - own;
     R.nn = W::rdl(upto, 63);
+    R.fresh = (uint32_t)W::popc(W::ballot((own > 0u) & (pid >= ko)));
     W::gst2(in, B.piece, at, pid,
             W::vmin(len, wv.vu0(kPieceLen)) | W::sel(dup, wv.vu0(kPieceDup), zu) |
                 (W::vmin(before, wv.vu0(0xFFFFu)) << 16));

@@ -299,10 +299,42 @@ __global__ __launch_bounds__(kT) void runs_link(RunsArgs A) {
     if (pos == 0 || st || before + 1u != x) atomicOr(A.weak + B.bits0 + (x >> 5), 1u << (x & 31));
 }
 
+// For which launches an instance is worth replaying on runs: the first one;
+// the one with the widest windows, a CU to an instance, when all that get
+// there have one at once; when they are more.
+constexpr int32_t kPaysFirst = 1, kPaysWideFew = 2, kPaysWideMany = 4;
+// A wavefront per instance.
+DEV void choose_form(const RunsArgs &A) {
+    const uint32_t lane = threadIdx.x & 63;
+    for (int64_t i = (int64_t)blockIdx.x * (kT / 64) + (threadIdx.x >> 6); i < A.n_inst; i += (int64_t)gridDim.x * (kT / 64)) {
+        const DevInst &I = A.inst[i];
+        if (I.run_trace < 0) continue;
+        const DevTrace &T = A.tr[I.trace];
+        const uint2 *q = A.sample + A.traces[I.run_trace].smp0;
+        RunsSample S{};
+        for (uint32_t k = lane; k < kSamples && k < T.n_req; k += 64) {
+            const uint2 x = q[k];
+            S.n += x.x >> 31;
+            S.pieces += x.x & 0xFFu;
+            S.fresh += (x.x >> 8) & 0xFFu;
+            S.blocks += x.y;
+        }
+        S = {DevWave::wsum(S.n), DevWave::wsum(S.pieces), DevWave::wsum(S.blocks), DevWave::wsum(S.fresh)};
+        const int32_t room = I.policy == kSQ ? I.capacity / T.n_groups : I.capacity;
+        const int32_t rounds = (A.n_run + A.n_cu - 1) / A.n_cu;
+        int32_t p = 0;
+        if (runs_pay(I.policy, I.capacity, room, true, T.n_req, S, 1.0f, A.load)) p |= kPaysFirst;
+        if (runs_pay(I.policy, I.capacity, room, false, T.n_req, S, 1.0f, 1.0f)) p |= kPaysWideFew;
+        if (runs_pay(I.policy, I.capacity, room, false, T.n_req, S, (float)rounds, A.load)) p |= kPaysWideMany;
+        if (lane == 0) A.pays[i] = p;
+    }
+}
+
 // One wavefront per request.  kAgain: only where a first pass added cuts.
 template <bool kAgain>
 __global__ __launch_bounds__(kT) void runs_list(RunsArgs A) {
     __shared__ uint32_t s_list[kT / 64][128];
+    if (kAgain) choose_form(A);      // (the first pass has sampled every trace)
     const int32_t ti = find_block(A.traces, A.n_traces, blockIdx.x, &DevRunTrace::blk1);
     const DevRunTrace &R = A.traces[ti];
     const DevKeyBuf &B = A.bufs[R.buf];
@@ -330,6 +362,10 @@ __global__ __launch_bounds__(kT) void runs_list(RunsArgs A) {
         return;
     }
     if (L.cut && lane == 0) A.bflag[2 * R.buf + 1] = 1;
+    if (!kAgain) {
+        const int32_t k = sample_slot(r, T.n_req);
+        if (k >= 0 && lane == 0) A.sample[R.smp0 + k] = make_uint2(sample_word0(L.np, L.fresh), sample_word1(nf));
+    }
     if (lane == 0) {
         RunReq q;
         q.n_full = (uint32_t)nf;
@@ -496,6 +532,8 @@ DEV void replay_instance(const RunsArgs &A, const int32_t *__restrict__ order, u
     extern __shared__ __align__(16) uint32_t runs_smem[];
     const int id = order[blockIdx.x];
     if (A.wide && A.done[id]) return;
+    const int32_t pays = !A.wide ? kPaysFirst : *A.n_over <= A.n_cu ? kPaysWideFew : kPaysWideMany;
+    if (!(A.pays[id] & pays)) return;
     const DevInst &I = A.inst[id];
     const DevRunTrace &R = A.traces[I.run_trace];
     if (A.tflag[I.run_trace] || A.bflag[2 * R.buf] || A.cmax[I.run_trace] >= I.n_contracts) return;
@@ -528,12 +566,17 @@ DEV void replay_instance(const RunsArgs &A, const int32_t *__restrict__ order, u
     F.n = T.n_req;
     int64_t *st = (int64_t *)DevWave::hold((uint64_t)(stats + (int64_t)id * kRecordWords));
     int32_t *done = (int32_t *)DevWave::hold((uint64_t)(A.done + id));
+    int32_t *over = (int32_t *)DevWave::hold((uint64_t)A.n_over);
+    const int32_t route = DevWave::hold(A.wide ? PC_ROUTE_RUNS_WIDE : PC_ROUTE_RUNS);
     bool ok;
     if (I.policy == kLRU) ok = replay_policy<kLRU>(P, F, st, lds);
     else if (I.policy == kS3) ok = replay_policy<kS3>(P, F, st, lds);
     else if (I.policy == kSQ) ok = replay_policy<kSQ>(P, F, st, lds);
     else ok = replay_policy<kPS>(P, F, st, lds);
-    if (ok && threadIdx.x == 0) *done = A.wide ? PC_ROUTE_RUNS_WIDE : PC_ROUTE_RUNS;
+    if (threadIdx.x == 0) {
+        if (ok) *done = route;
+        else if (route == PC_ROUTE_RUNS) atomicAdd(over, 1);
+    }
 }
 __global__ __launch_bounds__(64) void runs_replay(RunsArgs A, const int32_t *__restrict__ order, uint8_t *ws,
                                                   int64_t *stats, int32_t *per_req) {

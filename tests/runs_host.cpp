@@ -471,3 +471,12 @@ extern "C" int runs_host_replay(const uint64_t *keys, const int64_t *off, const 
         default: return go(std::integral_constant<int, 3>());
     }
 }
+
+// The rule that keeps an instance on runs (its load: none beside it), and which
+// requests it is judged by.
+extern "C" int runs_host_pays(int32_t policy, int32_t C, int32_t G, int64_t n_req, uint32_t n, uint32_t pieces,
+                              uint32_t blocks, uint32_t fresh, int32_t wide, float runs_load, float general_load) {
+    return pcr::runs_pay(policy, C, policy == 3 ? C / G : C, !wide, n_req,
+                         pcr::RunsSample{n, pieces, blocks, fresh}, runs_load, general_load);
+}
+extern "C" int32_t runs_host_sample_slot(int64_t r, int64_t n_req) { return pcr::sample_slot(r, n_req); }

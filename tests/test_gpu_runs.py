@@ -51,11 +51,29 @@ def test_shortest_traces_on_runs(n_req):
 
 @pytest.mark.parametrize("blocks", [63, 64, 65, 130])
 def test_requests_of_single_block_pieces(blocks):
-    """Every block its own piece (no two requests repeat an order): up to 64
-    pieces on runs, more in the general kernel."""
+    """Every block its own piece (no two requests repeat an order): the general
+    kernel replays them several times faster."""
     rng = np.random.default_rng(blocks)
     reqs = [rng.permutation(400)[:blocks] for _ in range(90)]
-    run_key_traces([_trace(reqs)], [_insts((64, 150, 500))], routes=[RUNS if blocks <= 64 else GENERAL] * 12)
+    run_key_traces([_trace(reqs)], [_insts((64, 150, 500))], routes=[GENERAL] * 12)
+
+
+@pytest.mark.parametrize("pieces", [63, 64, 65])
+def test_a_request_of_single_block_pieces(pieces):
+    """The last of many short requests has a piece for each lane, or more."""
+    reqs = [np.arange(10 * r, 10 * r + 7) for r in range(300)] + [10 * np.arange(pieces) * 4 + 3]
+    run_key_traces([_trace(reqs)], [_insts((64, 150, 500, 3000))], routes=[RUNS if pieces <= 64 else GENERAL] * 16)
+
+
+def test_form_follows_the_pieces_of_each_trace():
+    """In one batch: long documents, and many short ones (one of the policies'
+    traces a large cache, where a piece is compared with more runs)."""
+    rng = np.random.default_rng(8)
+    def of(d, k, docs, n=1200):
+        return [np.concatenate([100 * x + np.arange(d) for x in rng.integers(0, docs, k)]) for _ in range(n)]
+    run_key_traces([_trace(of(30, 3, 400)), _trace(of(1, 40, 6000)), _trace(of(4, 8, 2000)), _trace(of(2, 12, 12000))],
+                   [_insts((300, 4096)), _insts((300, 4096)), _insts((300,)), _insts((16384,))],
+                   routes=[RUNS] * 8 + [GENERAL] * 8 + [RUNS] * 4 + [GENERAL] * 4)
 
 
 def test_more_runs_than_rings_hold():

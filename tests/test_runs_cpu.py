@@ -29,6 +29,9 @@ def host(tmp_path_factory):
     L.runs_host_replay.restype = ctypes.c_int
     L.runs_host_replay.argtypes = [P, P, P, P, P, P, i64, i32, i64, i32, i64, i32, i32, P, P, i64, i32, i32, i32,
                                    i64, P, i64, i32, i32, P, P, P]
+    u32, f32 = ctypes.c_uint32, ctypes.c_float
+    L.runs_host_pays.argtypes = [i32, i32, i32, i64, u32, u32, u32, u32, i32, f32, f32]
+    L.runs_host_sample_slot.argtypes = [i64, i64]
     return L
 
 
@@ -288,3 +291,43 @@ def test_contracts_out_of_range_are_left_by_the_analysis(host):
     for pol in POLICIES:
         assert compare(host, kt, tg.Instance(0, pol, 90, contracts=[one] * 3)) == 1
         assert run_host(host, kt, tg.Instance(0, pol, 90, contracts=[one] * 2)) == "analysis"
+
+
+# us a request, one instance alone on an MI355X: (policy, C, blocks of a
+# document, documents of a request, on runs, in the general kernels); 1,500
+# requests of documents out of 3 C / d
+MEASURED = [
+    (0, 256, 4, 16, 5.4, 5.9), (0, 1024, 1, 60, 33.5, 5.9), (0, 1024, 8, 24, 7.6, 6.0), (0, 4096, 1, 24, 35.3, 5.1),
+    (0, 4096, 1, 60, 89.0, 5.2), (0, 4096, 4, 24, 15.0, 5.1), (0, 4096, 16, 4, 2.5, 4.9), (0, 4096, 32, 16, 5.4, 10.2),
+    (0, 4096, 32, 60, 16.3, 35.0), (0, 16384, 1, 60, 265.0, 7.0), (0, 16384, 4, 24, 36.5, 7.2),
+    (1, 256, 16, 4, 4.9, 11.1), (1, 1024, 1, 60, 70.1, 11.2), (1, 1024, 32, 16, 13.9, 23.8),
+    (1, 4096, 2, 60, 100.6, 10.4), (1, 4096, 4, 24, 30.5, 9.9), (1, 4096, 32, 60, 44.4, 78.4),
+    (1, 16384, 8, 60, 101.2, 31.2), (2, 256, 16, 16, 6.4, 12.6), (2, 1024, 1, 60, 35.5, 10.4),
+    (2, 4096, 1, 60, 96.0, 9.0), (2, 4096, 8, 8, 6.3, 8.6), (2, 4096, 32, 60, 26.2, 72.0), (2, 16384, 2, 60, 174.6, 17.9),
+    (3, 4096, 1, 60, 86.9, 6.2), (3, 4096, 16, 4, 2.3, 5.5), (3, 4096, 32, 16, 4.9, 14.1)]
+
+
+@pytest.mark.parametrize("policy,cap,d,k,runs,general", MEASURED)
+def test_form_of_many_pieces(host, policy, cap, d, k, runs, general):
+    """The rule takes the faster form where one is much faster, also where the
+    chip is shared: by runs_load and general_load times."""
+    n, distinct = 1500, 3 * cap // d
+    fresh = int(distinct * (1 - (1 - 1 / distinct) ** (n * k)))
+    for rl, gl in ((1, 1), (1, 2.2), (4, 2.2)):
+        on_runs = host.runs_host_pays(policy, cap, 4, n, n, n * k, n * k * d, fresh, rl > 1, rl, gl)
+        if runs * rl > 1.7 * general * gl:
+            assert not on_runs
+        if runs * rl < 0.6 * general * gl:
+            assert on_runs
+
+
+def test_sampled_requests(host):
+    """Every place at most once and inside the sample; as many of every kind of
+    request that comes in a fixed rhythm."""
+    for n in (1, 16, 127, 128, 129, 255, 256, 257, 1000, 5000, 50_000, 65_536):
+        at = np.array([host.runs_host_sample_slot(r, n) for r in range(n)])
+        r = np.flatnonzero(at >= 0)
+        assert len(set(at[r])) == len(r) and at.max() < min(n, 128)
+        assert len(r) == n if n <= 128 else len(r) >= 64
+        if n >= 1000:
+            assert np.bincount(r % 4, minlength=4).min() >= 20 and np.bincount(r % 2, minlength=2).min() >= 45
