@@ -142,10 +142,12 @@ constexpr bool kHaveRuns = true;
 // C = 4,096: of 120,000 blocks 1.1 ms on runs and 2.0, of 250,000 2.2 and 2.0;
 // 64 of 250,000 3.3 and 8.4).  A
 // batch whose longest trace is shorter than kRunsMinReq requests may be over
-// before the analysis has paid (48 instances on 16 traces, us, general kernels
-// and on runs: 8 requests of 4 blocks 84 and 98, of 200 blocks 747 and 286; 12
-// of 4 blocks 106 and 105; 16 of 4 blocks 127 and 107, of 200 blocks 2782 and
-// 1037).
+// before the analysis has paid (48 instances on 16 traces, C = 4,096, a batch
+// alone, us, general kernels and on runs: 8 requests of 4 blocks 122 and 137,
+// 12 140 and 150, 16 157 and 151, 24 193 and 167; 12 of 200 blocks 168 and
+// 162, 16 194 and 162).  It would pay earlier for requests that overflow their
+// cache (8 of 200 blocks, C = 256: 272 and 121), which max_req_blocks alone
+// does not tell.
 constexpr int64_t kRunsMaxKeys = (int64_t)1 << 30, kRunsMaxPrefix = (int64_t)1 << 22;
 constexpr int32_t kRunsMaxBlocks = 1 << 20, kRunsMaxBlocksFew = 1 << 17;
 constexpr int64_t kRunsMinReq = 16;
@@ -237,8 +239,10 @@ void plan_runs(const pc_trace_desc *traces, int32_t n_traces, const pc_instance_
 // each launch deals from the first engine on, so this holds only where no
 // engine is dealt more wavefronts than it has SIMDs: with launches of 16, 16
 // and 992 some waited for whole instances (150 -> 167 ms).  Hence
-//  - one launch, if a quarter of a CU's LDS holds the largest instance:
-//    1,024 one-touch instances 150 -> 132 ms;
+//  - one launch, if all instances fit the chip with the LDS of the largest:
+//    1,024 one-touch instances 150 -> 132 ms; 48 of 8,000 blocks, 16
+//    requests each, back to back 149 -> 90 us (host calls that fork and join
+//    streams);
 //  - else one per class of LDS (ten, six, five or three wavefronts to a CU;
 //    four classes, since four launches run side by side), largest first, each
 //    wavefront alone if the engines have room: 960 conversation instances
@@ -248,43 +252,36 @@ void plan_runs(const pc_trace_desc *traces, int32_t n_traces, const pc_instance_
 void plan_run_launches(Plan &P, const std::vector<double> &cost, int32_t n_inst, int64_t lds_cu, int64_t n_cu) {
     RunsPlan &R = P.runs;
     static const int32_t kClass[] = {16 << 10, 26 << 10, 32 << 10, 54 << 10};
-    auto bytes_of = [&](int32_t i, int wide = 0) {
-        const pcr::DevInst &d = P.di[i];
-        return pcr::runs_lds_bytes(d.policy, pcr::runs_windows(d.policy, d.capacity, wide), P.dt[d.trace].n_prefix);
-    };
-    int64_t n_run = 0;
+    std::vector<int32_t> ids, bytes(n_inst, 0), cls(n_inst, 0);
     int32_t most = 0;
-    for (int i = 0; i < n_inst; ++i)
-        if (P.di[i].run_trace >= 0) {
-            ++n_run;
-            most = std::max(most, bytes_of(i));
-        }
-    const bool one = n_run <= 4 * n_cu && 4 * (int64_t)most <= lds_cu;
-    auto class_of = [&](int32_t i) {
-        if (one) return 0;
-        int c = 0;
-        while (c < 3 && bytes_of(i) > kClass[c]) ++c;
-        return c;
-    };
-    std::vector<int32_t> ids;
-    for (int i = 0; i < n_inst; ++i)
-        if (P.di[i].run_trace >= 0) ids.push_back(i);
+    for (int i = 0; i < n_inst; ++i) {
+        const pcr::DevInst &d = P.di[i];
+        if (d.run_trace < 0) continue;
+        ids.push_back(i);
+        auto with = [&](int wide) {
+            return pcr::runs_lds_bytes(d.policy, pcr::runs_windows(d.policy, d.capacity, wide), P.dt[d.trace].n_prefix);
+        };
+        bytes[i] = with(0);
+        most = std::max(most, bytes[i]);
+        R.wide_lds = std::max(R.wide_lds, with(1));
+    }
+    if ((int64_t)ids.size() > n_cu * std::min<int64_t>(4, lds_cu / most))
+        for (int32_t i : ids)
+            while (cls[i] < 3 && bytes[i] > kClass[cls[i]]) ++cls[i];
     std::sort(ids.begin(), ids.end(), [&](int32_t a, int32_t b) {
-        const int ca = class_of(a), cb = class_of(b);
-        return ca != cb ? ca > cb : cost[a] != cost[b] ? cost[a] > cost[b] : a < b;
+        return cls[a] != cls[b] ? cls[a] > cls[b] : cost[a] != cost[b] ? cost[a] > cost[b] : a < b;
     });
     for (size_t k = 0; k < ids.size();) {
         Launch L;
         L.first = (int32_t)k;
-        while (k < ids.size() && class_of(ids[k]) == class_of(ids[L.first])) {
-            L.lds_bytes = std::max(L.lds_bytes, bytes_of(ids[k]));
+        while (k < ids.size() && cls[ids[k]] == cls[ids[L.first]]) {
+            L.lds_bytes = std::max(L.lds_bytes, bytes[ids[k]]);
             L.est += cost[ids[k]];
             ++k;
         }
         L.count = (int32_t)k - L.first;
         R.launches.push_back(L);
     }
-    for (int32_t i : ids) R.wide_lds = std::max(R.wide_lds, bytes_of(i, 1));
     int64_t per_engine = 0;          // wavefronts that the first engine (8 CUs of 4 SIMDs) is dealt at most
     for (const Launch &L : R.launches) per_engine += (L.count + n_cu / 8 - 1) / (n_cu / 8);
     R.alone = per_engine <= 32;
