@@ -394,7 +394,7 @@ int32_t validate_and_plan(const pc_trace_desc *traces, int32_t n_traces, const p
             maxn = pcr::kFixMaxn;
         d.maxn = (int32_t)maxn;
         d.run_trace = R.on ? R.trace_run[s.trace] : -1;
-        d.log_log2 = ceil_log2(s.capacity + maxn + 128);
+        d.log_log2 = pcr::free_log_log2(s.policy, s.capacity, maxn);
         const bool ghost = s.policy == PC_S3FIFO && d.g_cap > 0;
         if (ghost) {
             d.gnb_log2 = std::max(1, ceil_log2((int64_t)d.g_cap * 3 / 16 + 1));

@@ -107,6 +107,26 @@ constexpr int wg_per_cu(int64_t state, int64_t lds_cu) {
     return (int)(n < kMaxWgPerCu ? n : kMaxWgPerCu);
 }
 
+// Entries (log2) of the free-queue log: every cached block, a request's and
+// some slack between two compactions.  S3-FIFO's reclamation scans kScanStep
+// entries at a time and compacts whenever the log has no room for as many
+// more, which sends its cursors back to the front: with less than kScanStep
+// entries beside a full cache it would compact before every step, and never
+// get to a victim behind the first step's entries.
+constexpr int32_t kScanStep = 256;
+constexpr int32_t free_log_log2(int policy, int64_t C, int64_t maxn) {
+    const int64_t slack = policy == 1 && maxn + 128 < kScanStep ? kScanStep : maxn + 128;
+    return ceil_log2c(C + slack);
+}
+constexpr bool s3_log_has_room() {
+    for (int64_t C = 1; C <= 32767; C += C < 2200 ? 1 : 97)
+        for (int64_t maxn = 1; maxn <= C && maxn <= 128; maxn += 9)
+            if (((int64_t)1 << free_log_log2(1, C, maxn)) < C + kScanStep) return false;
+    return true;
+}
+static_assert(s3_log_has_room() && free_log_log2(1, 300, 55) == 10 && free_log_log2(0, 300, 55) == 9,
+              "free-queue log of S3-FIFO");
+
 // The state of one instance in one layout.  The main table has an even
 // number of 8-entry buckets, between load 2/3 and load 1/2: the largest that
 // keeps the most workgroups per CU (more room means fewer cuckoo

@@ -61,6 +61,7 @@ namespace {
 
 constexpr int kW = 4;              // wavefronts per instance
 constexpr int kB = 64 * kW;        // threads per instance
+static_assert(kB == kScanStep, "free_log_log2 sizes the log for S3-FIFO's scan");
 constexpr int64_t kScale = 65536;
 constexpr uint16_t kNewMark = 0xFFFE;      // posslot: new block, slot not yet assigned
 constexpr int32_t kErrInternal = -5;

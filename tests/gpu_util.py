@@ -1,8 +1,10 @@
 """Helpers shared by the GPU tests: run the HIP path and the oracle on the
 same seeded inputs and compare."""
 import numpy as np
+import torch
 
 import oracle
+import paper_2608_01657_amd as P
 from paper_2608_01657_amd import device as dv
 from paper_2608_01657_amd import tracegen as tg
 
@@ -15,12 +17,31 @@ def gpu_hash(trace):
     return t, keys, t.key_off.cpu().numpy()
 
 
+def same_in_general_kernels(b):
+    """Batches of 16 requests or more are replayed on runs: the general kernels
+    (the layouts that pc_replay_state_bytes tells) replay `b`, already launched,
+    too, and have to leave the same records."""
+    if set(b.routes()) == {P.PC_ROUTE_GENERAL}:
+        return
+    least = P.pc_replay_workspace_min_bytes(b.tdesc, b.idesc)
+    ws = b.workspace[:(least + 255) // 256 * 32]
+    assert P.pc_replay_route_offset(b.tdesc, b.idesc, ws.numel() * 8) == 0
+    stats = torch.full_like(b.stats, -1)
+    pr = None if b.per_request is None else torch.zeros_like(b.per_request)
+    P.pc_replay_batch(b.tdesc, b.idesc, ws, stats, pr)
+    torch.cuda.synchronize()
+    bad = (stats != b.stats).view(len(b.instances), -1).any(1).nonzero().flatten().tolist()
+    assert not bad, f"general kernels differ: instances {bad[:20]}"
+    assert pr is None or torch.equal(pr, b.per_request), "general kernels: per-request outputs differ"
+
+
 def replay_gpu(dtraces, instances, per_request=False, routes=None):
     """routes: how each instance has to be replayed (P.PC_ROUTE_*), if given."""
     b = dv.ReplayBatch(dtraces, instances, per_request=per_request)
     b.launch()
     res = b.results()
     assert routes is None or b.routes() == list(routes)
+    same_in_general_kernels(b)
     pr = b.per_request_arrays() if per_request else None
     return res, pr
 
@@ -47,7 +68,8 @@ def _pad_trace():
 
 def run_key_traces(kts, instances_per_trace, per_request=True, dense=False, routes=None):
     """Replay key traces on both sides; every instance compared in full.
-    routes: how each has to be replayed (P.PC_ROUTE_*), if given.  dense: in a batch padded beyond the GPU's CUs (see N_DENSE_PAD)."""
+    routes: how each has to be replayed (P.PC_ROUTE_*), if given.
+    dense: in a batch padded beyond the GPU's CUs (see N_DENSE_PAD)."""
     kts = list(kts)
     instances_per_trace = list(instances_per_trace)
     n_real = sum(len(x) for x in instances_per_trace)

@@ -20,7 +20,7 @@ import pytest
 import torch
 
 import oracle
-from gpu_util import assert_same
+from gpu_util import assert_same, same_in_general_kernels
 from paper_2608_01657_amd import device as dv
 from paper_2608_01657_amd import tracegen as tg
 
@@ -73,6 +73,7 @@ def _replay_and_compare(traces, insts, dts, okeys, oracle_ids):
     b = dv.ReplayBatch(dts, insts)
     b.launch()
     res = b.results()
+    same_in_general_kernels(b)
 
     def orc(k):
         spec = insts[k]
@@ -159,7 +160,8 @@ def _full_workload(name, n_seeds, policies=tg.ALL_POLICIES, as_set=False):
         b = dv.ReplayBatch(dts, insts)
         b.launch()
         res = b.results()
-        _log(f"{name}: {len(insts)} instances replayed on the GPU ({time.time() - t0:.0f}s)")
+        same_in_general_kernels(b)
+        _log(f"{name}: {len(insts)} instances replayed on the GPU in both forms ({time.time() - t0:.0f}s)")
         for n_done, f in enumerate(orc_futs):
             k, o = f.result()
             spec = insts[k]
@@ -237,6 +239,7 @@ def test_attack_traces_all_variants_per_request():
         b = dv.ReplayBatch(dts, insts, per_request=True)
         b.launch()
         res = b.results()
+        same_in_general_kernels(b)
         pr = b.per_request_arrays()
         for k, spec in enumerate(insts):
             o = oracle.replay_trace(traces[spec.trace], okeys[spec.trace][0], okeys[spec.trace][1], spec,

@@ -84,6 +84,16 @@ def test_more_runs_than_rings_hold():
                    routes=[RUNS, WIDE, WIDE] + [RUNS, GENERAL, GENERAL] + 2 * [RUNS, WIDE, WIDE])
 
 
+@pytest.mark.parametrize("cap", [257, 310, 383, 384, 769, 840, 1793, 1860])
+def test_general_kernels_log_beside_a_full_cache(cap):
+    """Capacities a little above a power of two, short requests: 256 entries of
+    the free-queue log have to stay free beside a full cache, which S3-FIFO
+    scans past (the general kernels replay the batch too)."""
+    kt = chunk_trace(cap, n_req=700, docs=60 if cap < 700 else 250)
+    run_key_traces([kt], [[tg.Instance(0, tg.POLICY_S3FIFO, cap, s3_small_permille=p, s3_move_threshold=t)
+                           for p, t in ((100, 1), (100, 0), (250, 2), (1000, 1))] + _insts((cap,))])
+
+
 def test_malformed_request_after_many_good_ones():
     kt = chunk_trace(9, n_req=200)
     ok, bad = chunk_trace(10, n_req=150), chunk_trace(11, n_req=150)
