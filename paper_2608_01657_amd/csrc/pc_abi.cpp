@@ -102,7 +102,7 @@ struct RunsPlan {
     std::vector<int32_t> trace_run;   // per trace descriptor: index into rt, or -1
     std::vector<int32_t> order;       // instances, launch by launch
     std::vector<Launch> launches;
-    int64_t table_words = 0, id_words = 0, bit_words = 0, first_words = 0, n_req = 0, n_sample = 0;
+    int64_t table_words = 0, id_words = 0, bit_words = 0, first_words = 0, n_req = 0;
     uint32_t nb_pos = 0, nb_req = 0, nb_list = 0;
     int32_t alone = 0;                // a wavefront has its SIMD for itself
     int32_t wide_lds = 0;             // of the second launch (widest windows)
@@ -209,17 +209,15 @@ void plan_runs(const pc_trace_desc *traces, int32_t n_traces, const pc_instance_
         d.buf = shared.at;
         d.req0 = R.n_req;
         d.first0 = R.first_words;
-        d.smp0 = R.n_sample;
         d.blk0 = (uint32_t)nb_req;
         d.blk1 = (uint32_t)nb_list;
         R.n_req += t.n_req;
-        R.n_sample += std::min(t.n_req, pcr::kSamples);
         R.first_words += align_up(t.n_prefix, 4);
         nb_req += (t.n_req + pcr::kRunsBlock - 1) / pcr::kRunsBlock;
         nb_list += (t.n_req + pcr::kRunsListBlock - 1) / pcr::kRunsListBlock;
         R.trace_run[i] = (int32_t)R.rt.size();
         R.rt.push_back(d);
-        bytes = 4 * (R.table_words + R.id_words + 3 * R.bit_words + R.first_words) + 8 * R.n_sample + 32 * R.n_req;
+        bytes = 4 * (R.table_words + R.id_words + 3 * R.bit_words + R.first_words) + 32 * R.n_req;
         if (bytes > kRunsMaxBytes || nb_pos + nb_req > kRunsMaxGrid || nb_list > kRunsMaxGrid) break;
     }
     R.on = longest >= kRunsMinReq && bytes <= kRunsMaxBytes && nb_pos + nb_req <= kRunsMaxGrid &&
@@ -508,7 +506,7 @@ int32_t validate_and_plan(const pc_trace_desc *traces, int32_t n_traces, const p
         R.o_start = take(4 * R.bit_words);
         R.o_weak = take(4 * R.bit_words);
         R.o_cuts = take(4 * R.bit_words);
-        R.o_sample = take(8 * R.n_sample);
+        R.o_sample = take(8 * pcr::kSampleStride * (int64_t)R.rt.size());
         R.o_flags = take(4 * (int64_t)(2 * R.rt.size() + 2 * R.kb.size()));
         R.o_done = take(4 * (2 * (int64_t)n_inst + 1));
         R.zeros = off - R.o_start;
@@ -786,10 +784,10 @@ int32_t launch_planned(const Plan &P, int32_t n_traces, int32_t n_inst, uint8_t 
         A.tflag = (int32_t *)(ws + R.o_flags);
         A.bflag = A.tflag + R.rt.size();
         A.cmax = A.bflag + 2 * R.kb.size();
-        A.sample = (uint2 *)(ws + R.o_sample);
+        A.sample = (uint64_t *)(ws + R.o_sample);
         A.done = (int32_t *)(ws + R.o_done);
-        A.pays = A.done + n_inst;
-        A.n_over = A.pays + n_inst;
+        A.pays = (uint32_t *)(A.done + n_inst);
+        A.n_over = (int32_t *)(A.pays + n_inst);
         A.n_inst = n_inst;
         A.n_run = (int32_t)R.order.size();
         A.n_cu = (int32_t)cu_count();

@@ -259,7 +259,6 @@ struct DevRunTrace {
     int32_t trace, buf;    // trace descriptor, key buffer
     int64_t req0;          // first RunReq
     int64_t first0;        // first word of its prefixes' first requests
-    int64_t smp0;          // its first sampled request
     uint32_t blk0, blk1;   // first block of runs_insert's requests, of runs_list
 };
 struct RunReq;
@@ -273,9 +272,9 @@ struct RunsArgs {
     int32_t *tflag;        // per analysed trace: left to the general kernel
     int32_t *bflag;        // per key buffer: [2 b] no table, [2 b + 1] cuts were added
     int32_t *cmax;         // per analysed trace: its largest contract index
-    uint2 *sample;         // sampled requests of every analysed trace
+    uint64_t *sample;      // per analysed trace: pack_sample, kSampleStride apart
     int32_t *done;         // per instance: how it was replayed, PC_ROUTE_*
-    int32_t *pays;         // per instance: for which launches it is worth replaying on runs
+    uint32_t *pays;        // per instance: which launches on runs it is worth
     int32_t *n_over;       // instances that the first windows were too small for
     int32_t n_bufs, n_traces;
     uint32_t nb_pos;       // blocks of runs_insert and runs_link over positions

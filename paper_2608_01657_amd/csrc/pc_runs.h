@@ -108,38 +108,45 @@ constexpr int32_t runs_lds_bytes(int policy, RunWindows w, int64_t n_prefix) {
 }
 
 // ------------------------------------------------------------ which form
-// Sums over a sample of a trace's requests: one of every 128th part of the
+// Sums over a sample of a trace's requests: one of every 64th part of the
 // trace, or all (what repeats in a fixed rhythm comes in as often as it is).
 struct RunsSample {
     uint32_t n, pieces;       // requests; their pieces
     uint32_t blocks, fresh;   // blocks; pieces that no earlier request holds
 };
-constexpr int64_t kSamples = 128;
-// The request's place in the sample, or -1.
-PC_RUNS_FN int32_t sample_slot(int64_t r, int64_t n_req) {
+constexpr int64_t kSamples = 64;
+PC_RUNS_FN bool is_sampled(int64_t r, int64_t n_req) {
     const uint32_t part = (uint32_t)((n_req + kSamples - 1) / kSamples), k = (uint32_t)r / part;
     // (2^32 over the golden ratio)
-    return (uint32_t)r - k * part == ((k + 1u) * 0x9E3779B1u >> 8) % part ? (int32_t)k : -1;
+    return (uint32_t)r - k * part == ((k + 1u) * 0x9E3779B1u >> 8) % part;
 }
-// A sampled request's two words (0, 0: the last part is too short for its place).
-constexpr uint32_t sample_word0(uint32_t np, uint32_t fresh) { return 0x80000000u | np | fresh << 8; }
-PC_RUNS_FN uint32_t sample_word1(int64_t nf) { return (uint32_t)(nf < 65535 ? nf : 65535); }
-// Whether an instance is replayed on runs, by the time of a request in either
-// form (us).  On runs every piece is compared with every 256 entries of the
-// windows, so many short pieces cost more than the blocks that they hold cost
-// the general kernel.  Alone on the chip (LRU, C = 4,096, requests of k
-// documents of d blocks; on runs and general kernel): k 4, d 16 2.5 and 4.9;
-// k 16, d 16 6.5 and 5.4; k 24, d 4 15 and 5.1; k 60, d 1 89 and 5.2
-// (C = 16,384: 265 and 7.0).  Over 546 such batches of all policies this is
-// at most 1.3 times slower than the general kernel (always runs: 38 times).
+// All four in one word, for one atomic addition a sampled request, each trace's
+// word on a line of its own (8 words): additions to one line follow each other,
+// some 20 to 40 ns each.  n and fresh take at most 64 and 64 * 64, pieces the
+// same, blocks (cut at 65,535 each) less than 2^22.
+constexpr int64_t kSampleStride = 8;
+PC_RUNS_FN uint64_t pack_sample(uint32_t np, uint32_t fresh, int64_t nf) {
+    return 1ull | (uint64_t)np << 7 | (uint64_t)fresh << 20 | (uint64_t)(nf < 65535 ? nf : 65535) << 33;
+}
+PC_RUNS_FN RunsSample unpack_sample(uint64_t w) {
+    return {(uint32_t)w & 0x7Fu, (uint32_t)(w >> 7) & 0x1FFFu, (uint32_t)(w >> 33), (uint32_t)(w >> 20) & 0x1FFFu};
+}
+
+// Estimated time of a request (us), by an instance alone on the chip.  On runs
+// every piece is compared with every 256 entries of the windows, so many short
+// pieces cost more than the blocks that they hold cost the general kernel
+// (LRU, C = 4,096, requests of k documents of d blocks, on runs and general
+// kernel): k 4, d 16 2.5 and 4.9; k 16, d 16 6.5 and 5.4; k 24, d 4 15 and 5.1;
+// k 60, d 1 89 and 5.2 (C = 16,384: 265 and 7.0).  Over 546 such batches of all
+// policies the form that these take is at most 1.3 times slower than the
+// general kernel (always runs: 38 times).
+struct FormTimes {
+    float first, wide, general;      // on runs with the first windows, which may turn out too small; the widest
+};
 //   C      capacity
 //   room   blocks that a request may hold
-//   first  with the first windows (which may turn out too small)
-//   runs_load, general_load
-//          how many instances of the batch share what one alone would have
-PC_RUNS_FN bool runs_pay(int policy, int32_t C, int32_t room, bool first, int64_t n_req, const RunsSample &q,
-                         float runs_load, float general_load) {
-    if (q.n == 0 || q.pieces == 0) return true;
+PC_RUNS_FN FormTimes form_times(int policy, int32_t C, int32_t room, int64_t n_req, const RunsSample &q) {
+    if (q.n == 0 || q.pieces == 0) return {1.0f, 1.0f, 4.0f};
     const float n = (float)q.n, np = (float)q.pieces / n, nf = (float)q.blocks / n;
     const float cut = nf > (float)room ? (float)room / nf : 1.0f, x = nf * cut / 256.0f;
     // runs in the cache: what fills it, or all that the trace has; on average
@@ -148,20 +155,38 @@ PC_RUNS_FN bool runs_pay(int policy, int32_t C, int32_t room, bool first, int64_
     const float fill = (float)C * np / nf, live = fill < total ? fill : total;
     const float mean = live - live * live / (2.0f * (total > 1.0f ? total : 1.0f));
     const float groups = mean > 256.0f ? mean / 256.0f : 1.0f;
-    float a, b, u, gen;
+    FormTimes t;
     if (policy == 1) {
-        a = 1.2f, b = 0.52f, u = 0.13f;
-        gen = 7.0f + 4.5f * x > 11.5f * x ? 7.0f + 4.5f * x : 11.5f * x;
+        t.wide = 1.2f + np * (0.52f * cut + 0.13f * groups);
+        t.general = 7.0f + 4.5f * x > 11.5f * x ? 7.0f + 4.5f * x : 11.5f * x;
     } else if (policy == 2) {
-        a = 1.5f, b = 0.15f, u = 0.095f;
-        gen = 6.0f + 8.0f * x > 13.0f * x ? 6.0f + 8.0f * x : 13.0f * x;
+        t.wide = 1.5f + np * (0.15f * cut + 0.095f * groups);
+        t.general = 6.0f + 8.0f * x > 13.0f * x ? 6.0f + 8.0f * x : 13.0f * x;
     } else {
-        a = 1.0f, b = 0.2f, u = 0.085f;
-        gen = 4.6f + 0.5f * x > 5.1f * x ? 4.6f + 0.5f * x : 5.1f * x;
+        t.wide = 1.0f + np * (0.2f * cut + 0.085f * groups);
+        t.general = 4.6f + 0.5f * x > 5.1f * x ? 4.6f + 0.5f * x : 5.1f * x;
     }
-    float runs = a + np * (b * cut + u * groups);
-    if (first && live > (float)runs_narrow_room(policy, C)) runs *= 1.6f;      // once more with the widest windows
-    return runs * runs_load <= gen * general_load;
+    t.first = live > (float)runs_narrow_room(policy, C) ? 1.6f * t.wide : t.wide;
+    return t;
+}
+// Which launches on runs an instance is worth: the first; the one with the
+// widest windows, a CU to an instance, when all that get there have one at
+// once; when they are more (`load`, `rounds`: how many instances of the batch
+// share what one alone would have, in the general kernels and with the widest
+// windows).
+constexpr uint32_t kPaysFirst = 1, kPaysWideFew = 2, kPaysWideMany = 4, kPaysAll = 7;
+PC_RUNS_FN uint32_t runs_pay(const FormTimes &t, float load, float rounds) {
+    return (t.first <= t.general * load ? kPaysFirst : 0u) | (t.wide <= t.general ? kPaysWideFew : 0u) |
+           (t.wide * rounds <= t.general * load ? kPaysWideMany : 0u);
+}
+// The general kernels begin when the replay on runs has ended, so a batch that
+// needs both takes as long as its longest instance on runs (runs_in) and its
+// longest in the general kernels (general_in): all in the general kernels
+// (general_all), or all on runs that can (runs_all), may be over earlier.
+PC_RUNS_FN uint32_t batch_pays(uint32_t pays, float runs_in, float general_in, float runs_all, float general_all) {
+    const float both = runs_in + general_in;
+    if (general_all < 0.9f * both && general_all <= runs_all) return 0u;
+    return runs_all < 0.9f * both ? kPaysAll : pays;
 }
 
 // ------------------------------------------------------------ analysis

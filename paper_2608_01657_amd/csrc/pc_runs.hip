@@ -7,12 +7,14 @@
 //                 least position of a key stays: its id); request starts
 //                 and each prefix's first request
 //   runs_link     ids of all positions; weak links
-//   runs_list     per request: its pieces, duplicates among them, RunReq
-//   runs_list     again (kAgain) where duplicates added cuts (rare)
+//   runs_list     per request: its pieces, duplicates among them, RunReq, and
+//                 sums over a sample of the requests
+//   runs_list     again (kAgain) for key buffers where duplicates added cuts;
+//                 the form that each instance takes
 // Bound: runs_insert and runs_link make one random table access per key; the
-// rest streams.  16 one-touch traces (800,000 requests, 120 M keys): insert
-// 5.0 ms, link 2.0, list 0.6, fill 0.15; 64 traces of conversations: insert
-// 6.5, link 1.9, list 1.2, fill 0.2.
+// rest streams.  16 one-touch traces of 50,000 requests (119 M keys): insert
+// 5.0 ms, link 2.0, list 0.6, fill 0.15; 64 traces of conversations, 100,000
+// requests each (648 M keys): insert 32.7, link 9.7, list 4.9, fill 1.3.
 //
 // Replay: one wavefront per instance, no barriers; bound by the chain of
 // dependent instructions of a request, whatever its number of blocks.  1,024
@@ -184,6 +186,7 @@ __global__ __launch_bounds__(kT) void runs_fill(uint4 *ones, int64_t n_ones, uin
     for (int64_t i = i0; i < n_zeros; i += step) zeros[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
+// (multipliers: 2^64 over the golden ratio, and splitmix64's first)
 DEV uint32_t key_slot(uint64_t k, uint32_t slots) {
     k ^= k >> 32;
     k *= 0x9E3779B97F4A7C15ull;
@@ -299,34 +302,54 @@ __global__ __launch_bounds__(kT) void runs_link(RunsArgs A) {
     if (pos == 0 || st || before + 1u != x) atomicOr(A.weak + B.bits0 + (x >> 5), 1u << (x & 31));
 }
 
-// For which launches an instance is worth replaying on runs: the first one;
-// the one with the widest windows, a CU to an instance, when all that get
-// there have one at once; when they are more.
-constexpr int32_t kPaysFirst = 1, kPaysWideFew = 2, kPaysWideMany = 4;
-// A wavefront per instance.
+// Which form each instance takes, by one workgroup.
 DEV void choose_form(const RunsArgs &A) {
-    const uint32_t lane = threadIdx.x & 63;
-    for (int64_t i = (int64_t)blockIdx.x * (kT / 64) + (threadIdx.x >> 6); i < A.n_inst; i += (int64_t)gridDim.x * (kT / 64)) {
+    // longest: on runs of those that pay, of all that can; in the general
+    // kernels of the rest, of those that can not, of all
+    // (words of positive floats sort as the floats do)
+    __shared__ uint32_t s_most[kT / 64][6];
+    uint32_t m[6] = {};                  // m[5]: how many are left
+    auto times = [&](const DevInst &I, const DevTrace &T) {
+        return form_times(I.policy, I.capacity, I.policy == kSQ ? I.capacity / T.n_groups : I.capacity, T.n_req,
+                          unpack_sample(A.sample[kSampleStride * I.run_trace]));
+    };
+    FormTimes own{};      // of the thread's first instance
+    const float rounds = (float)((A.n_run + A.n_cu - 1) / A.n_cu);
+    for (int32_t i = (int32_t)threadIdx.x; i < A.n_inst; i += kT) {
         const DevInst &I = A.inst[i];
         if (I.run_trace < 0) continue;
         const DevTrace &T = A.tr[I.trace];
-        const uint2 *q = A.sample + A.traces[I.run_trace].smp0;
-        RunsSample S{};
-        for (uint32_t k = lane; k < kSamples && k < T.n_req; k += 64) {
-            const uint2 x = q[k];
-            S.n += x.x >> 31;
-            S.pieces += x.x & 0xFFu;
-            S.fresh += (x.x >> 8) & 0xFFu;
-            S.blocks += x.y;
-        }
-        S = {DevWave::wsum(S.n), DevWave::wsum(S.pieces), DevWave::wsum(S.blocks), DevWave::wsum(S.fresh)};
-        const int32_t room = I.policy == kSQ ? I.capacity / T.n_groups : I.capacity;
-        const int32_t rounds = (A.n_run + A.n_cu - 1) / A.n_cu;
-        int32_t p = 0;
-        if (runs_pay(I.policy, I.capacity, room, true, T.n_req, S, 1.0f, A.load)) p |= kPaysFirst;
-        if (runs_pay(I.policy, I.capacity, room, false, T.n_req, S, 1.0f, 1.0f)) p |= kPaysWideFew;
-        if (runs_pay(I.policy, I.capacity, room, false, T.n_req, S, (float)rounds, A.load)) p |= kPaysWideMany;
-        if (lane == 0) A.pays[i] = p;
+        const FormTimes t = times(I, T);
+        if (i < kT) own = t;
+        const uint32_t r = __float_as_uint((float)T.n_req * t.first), g = __float_as_uint((float)T.n_req * t.general);
+        const bool can = !A.tflag[I.run_trace] && !A.bflag[2 * A.traces[I.run_trace].buf] &&
+                         A.cmax[I.run_trace] < I.n_contracts;
+        const bool in = can && (runs_pay(t, A.load, rounds) & kPaysFirst);
+        m[0] = DevWave::vmax(m[0], in ? r : 0u);
+        m[1] = DevWave::vmax(m[1], can ? r : 0u);
+        m[2] = DevWave::vmax(m[2], in ? 0u : g);
+        m[3] = DevWave::vmax(m[3], can ? 0u : g);
+        m[4] = DevWave::vmax(m[4], g);
+        m[5] += in ? 0u : 1u;
+    }
+    const int w = (int)threadIdx.x >> 6;
+    for (int k = 0; k < 6; ++k) {
+        const uint32_t x = k < 5 ? DevWave::wmax(m[k]) : DevWave::wsum(m[k]);
+        if ((threadIdx.x & 63) == 0) s_most[w][k] = x;
+    }
+    __syncthreads();
+    float most[5] = {};
+    uint32_t left = 0;
+    for (int q = 0; q < kT / 64; ++q) {
+        for (int k = 0; k < 5; ++k) most[k] = DevWave::vmax(most[k], __uint_as_float(s_most[q][k]));
+        left += s_most[q][5];
+    }
+    const float part = A.load * (float)left / (float)A.n_run, load = part > 1.0f ? part : 1.0f;    // of those left
+    for (int32_t i = (int32_t)threadIdx.x; i < A.n_inst; i += kT) {
+        const DevInst &I = A.inst[i];
+        if (I.run_trace >= 0)
+            A.pays[i] = batch_pays(runs_pay(i < kT ? own : times(I, A.tr[I.trace]), A.load, rounds), most[0],
+                                   most[2] * load, most[1] + most[3] * load, most[4] * A.load);
     }
 }
 
@@ -334,7 +357,7 @@ DEV void choose_form(const RunsArgs &A) {
 template <bool kAgain>
 __global__ __launch_bounds__(kT) void runs_list(RunsArgs A) {
     __shared__ uint32_t s_list[kT / 64][128];
-    if (kAgain) choose_form(A);      // (the first pass has sampled every trace)
+    if (kAgain && blockIdx.x == 0) choose_form(A);      // (the first pass has sampled every trace)
     const int32_t ti = find_block(A.traces, A.n_traces, blockIdx.x, &DevRunTrace::blk1);
     const DevRunTrace &R = A.traces[ti];
     const DevKeyBuf &B = A.bufs[R.buf];
@@ -362,10 +385,9 @@ __global__ __launch_bounds__(kT) void runs_list(RunsArgs A) {
         return;
     }
     if (L.cut && lane == 0) A.bflag[2 * R.buf + 1] = 1;
-    if (!kAgain) {
-        const int32_t k = sample_slot(r, T.n_req);
-        if (k >= 0 && lane == 0) A.sample[R.smp0 + k] = make_uint2(sample_word0(L.np, L.fresh), sample_word1(nf));
-    }
+    if (!kAgain && lane == 0 && is_sampled(r, T.n_req))
+        atomicAdd((unsigned long long *)(A.sample + kSampleStride * ti),
+                  (unsigned long long)pack_sample(L.np, L.fresh, nf));
     if (lane == 0) {
         RunReq q;
         q.n_full = (uint32_t)nf;
@@ -532,7 +554,7 @@ DEV void replay_instance(const RunsArgs &A, const int32_t *__restrict__ order, u
     extern __shared__ __align__(16) uint32_t runs_smem[];
     const int id = order[blockIdx.x];
     if (A.wide && A.done[id]) return;
-    const int32_t pays = !A.wide ? kPaysFirst : *A.n_over <= A.n_cu ? kPaysWideFew : kPaysWideMany;
+    const uint32_t pays = !A.wide ? kPaysFirst : *A.n_over <= A.n_cu ? kPaysWideFew : kPaysWideMany;
     if (!(A.pays[id] & pays)) return;
     const DevInst &I = A.inst[id];
     const DevRunTrace &R = A.traces[I.run_trace];

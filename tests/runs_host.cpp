@@ -472,11 +472,21 @@ extern "C" int runs_host_replay(const uint64_t *keys, const int64_t *off, const 
     }
 }
 
-// The rule that keeps an instance on runs (its load: none beside it), and which
-// requests it is judged by.
-extern "C" int runs_host_pays(int32_t policy, int32_t C, int32_t G, int64_t n_req, uint32_t n, uint32_t pieces,
-                              uint32_t blocks, uint32_t fresh, int32_t wide, float runs_load, float general_load) {
-    return pcr::runs_pay(policy, C, policy == 3 ? C / G : C, !wide, n_req,
-                         pcr::RunsSample{n, pieces, blocks, fresh}, runs_load, general_load);
+// The rule that keeps an instance on runs (kPays*), what a batch makes of it,
+// and which requests an instance is judged by.
+extern "C" uint32_t runs_host_pays(int32_t policy, int32_t C, int32_t G, int64_t n_req, uint32_t n, uint32_t pieces,
+                                   uint32_t blocks, uint32_t fresh, float load, float rounds) {
+    return pcr::runs_pay(pcr::form_times(policy, C, policy == 3 ? C / G : C, n_req,
+                                         pcr::RunsSample{n, pieces, blocks, fresh}), load, rounds);
 }
-extern "C" int32_t runs_host_sample_slot(int64_t r, int64_t n_req) { return pcr::sample_slot(r, n_req); }
+extern "C" void runs_host_sample(const int64_t *req, int64_t n, uint32_t *sums) {
+    uint64_t w = 0;
+    for (int64_t i = 0; i < n; ++i) w += pcr::pack_sample((uint32_t)req[3 * i], (uint32_t)req[3 * i + 1], req[3 * i + 2]);
+    const pcr::RunsSample s = pcr::unpack_sample(w);
+    sums[0] = s.n, sums[1] = s.pieces, sums[2] = s.fresh, sums[3] = s.blocks;
+}
+extern "C" uint32_t runs_host_batch_pays(uint32_t pays, float runs_in, float general_in, float runs_all,
+                                         float general_all) {
+    return pcr::batch_pays(pays, runs_in, general_in, runs_all, general_all);
+}
+extern "C" int32_t runs_host_is_sampled(int64_t r, int64_t n_req) { return pcr::is_sampled(r, n_req); }

@@ -9,7 +9,7 @@ import torch
 
 import oracle
 import paper_2608_01657_amd as P
-from gpu_util import POLICIES, assert_same, run_key_traces
+from gpu_util import POLICIES, _pad_trace, assert_same, run_key_traces
 from paper_2608_01657_amd import device as dv
 from paper_2608_01657_amd import tracegen as tg
 from test_runs_cpu import chunk_trace, ends_inside, partial_repeats, random_cuts
@@ -65,15 +65,27 @@ def test_a_request_of_single_block_pieces(pieces):
     run_key_traces([_trace(reqs)], [_insts((64, 150, 500, 3000))], routes=[RUNS if pieces <= 64 else GENERAL] * 16)
 
 
-def test_form_follows_the_pieces_of_each_trace():
-    """In one batch: long documents, and many short ones (one of the policies'
-    traces a large cache, where a piece is compared with more runs)."""
-    rng = np.random.default_rng(8)
-    def of(d, k, docs, n=1200):
-        return [np.concatenate([100 * x + np.arange(d) for x in rng.integers(0, docs, k)]) for _ in range(n)]
-    run_key_traces([_trace(of(30, 3, 400)), _trace(of(1, 40, 6000)), _trace(of(4, 8, 2000)), _trace(of(2, 12, 12000))],
-                   [_insts((300, 4096)), _insts((300, 4096)), _insts((300,)), _insts((16384,))],
-                   routes=[RUNS] * 8 + [GENERAL] * 8 + [RUNS] * 4 + [GENERAL] * 4)
+def _documents(d, k, docs, n):
+    """n requests of k documents of d blocks."""
+    rng = np.random.default_rng([d, k, docs])
+    return _trace([np.concatenate([100 * x + np.arange(d) for x in rng.integers(0, docs, k)]) for _ in range(n)])
+
+
+@pytest.mark.parametrize("d,k,docs,caps,route", [(30, 3, 400, (300, 4096), RUNS), (4, 8, 2000, (300,), RUNS),
+                                                 (1, 40, 6000, (300, 4096), GENERAL), (2, 12, 12000, (16384,), GENERAL)])
+def test_form_follows_the_pieces(d, k, docs, caps, route):
+    """Long documents, and many short ones (at 16,384 blocks a piece is compared
+    with more runs)."""
+    run_key_traces([_documents(d, k, docs, 800)], [_insts(caps)], routes=[route] * 4 * len(caps))
+
+
+def test_form_of_a_batch_of_both():
+    """The general kernels begin when the replay on runs has ended: a batch takes
+    both forms, or the general kernels for all where that is over earlier."""
+    long, short = _documents(30, 3, 400, 3000), _documents(1, 40, 6000, 200)
+    run_key_traces([long, short], [_insts((300, 4096)), _insts((300, 4096))], routes=[RUNS] * 8 + [GENERAL] * 8)
+    near = _documents(4, 8, 2000, 800)
+    run_key_traces([near, _documents(1, 40, 6000, 800)], [_insts((300,)), _insts((300,))], routes=[GENERAL] * 8)
 
 
 def test_more_runs_than_rings_hold():
@@ -187,9 +199,13 @@ def test_equal_starts_with_different_ends(order):
             d.keys = dts[0].keys
         kts, dts = [kts[i] for i in order], [dts[i] for i in order]
         insts = [tg.Instance(t, p, c) for t in range(2) for p in POLICIES for c in (7, 64, 300)]
-        b = dv.ReplayBatch(dts, insts, per_request=True)
+        # (beside instances of an empty trace, since a batch this small would
+        # take the general kernels for both traces)
+        dts.append(dv.upload_keys(_pad_trace()))
+        full = insts + [tg.Instance(2, tg.POLICY_PREFIXSHIELD, 4096) for _ in range(2000)]
+        b = dv.ReplayBatch(dts, full, per_request=True)
         b.launch()
-        assert b.routes() == [RUNS if order[x.trace] in runs else GENERAL for x in insts]
+        assert b.routes()[:len(insts)] == [RUNS if order[x.trace] in runs else GENERAL for x in insts]
         pr = b.per_request_arrays()
         for k, (res, x) in enumerate(zip(b.results(), insts)):
             w = oracle.replay_key_trace(kts[x.trace], x, per_request=True)

@@ -30,8 +30,10 @@ def host(tmp_path_factory):
     L.runs_host_replay.argtypes = [P, P, P, P, P, P, i64, i32, i64, i32, i64, i32, i32, P, P, i64, i32, i32, i32,
                                    i64, P, i64, i32, i32, P, P, P]
     u32, f32 = ctypes.c_uint32, ctypes.c_float
-    L.runs_host_pays.argtypes = [i32, i32, i32, i64, u32, u32, u32, u32, i32, f32, f32]
-    L.runs_host_sample_slot.argtypes = [i64, i64]
+    L.runs_host_pays.argtypes = [i32, i32, i32, i64, u32, u32, u32, u32, f32, f32]
+    L.runs_host_batch_pays.argtypes = [u32, f32, f32, f32, f32]
+    L.runs_host_sample.argtypes = [P, i64, P]
+    L.runs_host_is_sampled.argtypes = [i64, i64]
     return L
 
 
@@ -310,24 +312,49 @@ MEASURED = [
 @pytest.mark.parametrize("policy,cap,d,k,runs,general", MEASURED)
 def test_form_of_many_pieces(host, policy, cap, d, k, runs, general):
     """The rule takes the faster form where one is much faster, also where the
-    chip is shared: by runs_load and general_load times."""
+    chip is shared (in the general kernels `load` times, with the widest
+    windows `rounds` times)."""
     n, distinct = 1500, 3 * cap // d
     fresh = int(distinct * (1 - (1 - 1 / distinct) ** (n * k)))
-    for rl, gl in ((1, 1), (1, 2.2), (4, 2.2)):
-        on_runs = host.runs_host_pays(policy, cap, 4, n, n, n * k, n * k * d, fresh, rl > 1, rl, gl)
-        if runs * rl > 1.7 * general * gl:
-            assert not on_runs
-        if runs * rl < 0.6 * general * gl:
-            assert on_runs
+    for load, rounds in ((1, 1), (2.2, 4)):
+        pays = host.runs_host_pays(policy, cap, 4, n, n, n * k, n * k * d, fresh, load, rounds)
+        for bit, r, g in ((1, 1, load), (2, 1, 1), (4, rounds, load)):
+            if runs * r > 1.7 * general * g:
+                assert not pays & bit
+            if runs * r < 0.6 * general * g:
+                assert pays & bit
+
+
+def test_form_of_a_batch(host):
+    """Both forms one after the other, or all instances in one of them."""
+    f = host.runs_host_batch_pays
+    # (longest on runs of those that pay, in the general kernels of the rest; of all)
+    for pays in (0, 1, 7):
+        assert f(pays, 4, 7, 30, 12) == pays
+        assert f(pays, 4, 7, 11.5, 12) == pays
+        assert f(pays, 4, 7, 11.5, 7.5) == 0
+        assert f(pays, 0.5, 7, 20, 7) == pays        # (not worth less than a tenth)
+        assert f(pays, 5, 5, 6, 7) == 7
+        assert f(pays, 5, 0, 5, 20) == pays
+        assert f(pays, 0, 9, 40, 9) == pays
 
 
 def test_sampled_requests(host):
-    """Every place at most once and inside the sample; as many of every kind of
-    request that comes in a fixed rhythm."""
-    for n in (1, 16, 127, 128, 129, 255, 256, 257, 1000, 5000, 50_000, 65_536):
-        at = np.array([host.runs_host_sample_slot(r, n) for r in range(n)])
-        r = np.flatnonzero(at >= 0)
-        assert len(set(at[r])) == len(r) and at.max() < min(n, 128)
-        assert len(r) == n if n <= 128 else len(r) >= 64
+    """One of every 64th part, or all; as many of every kind of request that
+    comes in a fixed rhythm."""
+    for n in (1, 16, 63, 64, 65, 127, 128, 129, 1000, 5000, 50_000, 65_536):
+        r = np.flatnonzero([host.runs_host_is_sampled(r, n) for r in range(n)])
+        assert len(r) == n if n <= 64 else 32 <= len(r) <= 64
         if n >= 1000:
-            assert np.bincount(r % 4, minlength=4).min() >= 20 and np.bincount(r % 2, minlength=2).min() >= 45
+            assert np.bincount(r % 4, minlength=4).min() >= 9 and np.bincount(r % 2, minlength=2).min() >= 22
+
+
+def test_sums_of_a_sample(host):
+    """The largest values of 64 requests fit their fields."""
+    sums = np.zeros(4, np.uint32)
+    rng = np.random.default_rng(1)
+    for req in (np.tile([64, 64, 1 << 20], (64, 1)), np.tile([0, 0, 0], (64, 1)), np.zeros((0, 3), int),
+                np.stack([rng.integers(0, 65, 64), rng.integers(0, 65, 64), rng.integers(0, 70_000, 64)], 1)):
+        req = np.ascontiguousarray(req, np.int64)
+        host.runs_host_sample(_ptr(req), len(req), _ptr(sums))
+        assert list(sums) == [len(req), req[:, 0].sum(), req[:, 1].sum(), np.minimum(req[:, 2], 65535).sum()]
