@@ -212,11 +212,14 @@ def main():
     # phase-counter build and instances that do not fit that form take the
     # general kernel of the layout given by layout_instances
     _, layouts = P.pc_replay_state_bytes(batch.tdesc, batch.idesc)
-    lay = max(set(layouts), key=layouts.count)
+    routes = batch.routes()
+    left = [x for x, r in zip(layouts, routes) if r == P.PC_ROUTE_GENERAL]
+    lay = max(set(left or layouts), key=(left or layouts).count)
     general = f"replay_kernel<{lay}> ({P.LAYOUT_NAMES[lay]} layout)"
-    roof = {"kernel": ("hash_kernel" if dominant != "replay" else general if args.phase_profile else
+    roof = {"kernel": ("hash_kernel" if dominant != "replay" else general if 2 * len(left) > len(layouts) else
                        "runs_replay (one wavefront per instance) after the trace analysis"),
-            "layout_instances": {P.LAYOUT_NAMES[x]: layouts.count(x) for x in sorted(set(layouts))},
+            "instances_on_runs": len(layouts) - len(left),
+            "layout_instances": {P.LAYOUT_NAMES[x]: left.count(x) for x in sorted(set(left))},
             "bound": "hbm",
             "achieved": round(replay_gbs if dominant == "replay" else hash_gbs, 3),
             "peak": HBM_PEAK_GBS, "unit": "GB/s",

@@ -468,8 +468,11 @@ hipError_t launch_hash(const int32_t *tokens, int64_t n_tokens, const int64_t *t
     //    44 3.5 -> 3.3), 8 from 384 blocks (96: 8.1 -> 4.2; 4 take 4.5), 16
     //    from 1536 (96 of 16,000 230 -> 55; 8 take 62).
     //  - more: 4 from 512 blocks, 8 from 768 (2048 of 768 22.9 -> 21.5, 8192
-    //    103 -> 88; at 384 equal lengths lose, 4096: 18.6 -> 19.8); not for
-    //    more than 4096 that re-read (8192 of 768: 53 -> 57).
+    //    103 -> 88; at 384 equal lengths lose, 4096: 18.6 -> 19.8).  It stays
+    //    4 to 10 % faster where HBM bounds both (ms; 524,288 of 512 blocks,
+    //    19 GB 3.90 -> 3.71, of 768 5.87 -> 5.58; 131,072 of 4096, 39 GB
+    //    8.03 -> 7.75); past 2^22 a launch would hold 2^32 work items.  Not
+    //    for more than 4096 that re-read (8192 of 768: 53 -> 57).
     if (n_req <= 512 || (avg >= 512 && (stream ? n_req < (1 << 22) : n_req <= 4096))) {
         const dim3 g((unsigned)n_req);
         if (avg >= 1536 && n_req <= 512)
